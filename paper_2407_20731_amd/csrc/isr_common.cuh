@@ -324,31 +324,81 @@ DEV void lookback_wait(u64* lb, long long t, const u32* cntl, int ne, int* flags
 // ---- FP64 fixed-order contraction ---------------------------------------------
 // y[a] = M[a][0]*x[0] + M[a][1]*x[1] + ... left to right, every product and
 // sum rounded separately (the library is built with -ffp-contract=off).
+//
+// The matrix entries are read through the scalar cache into scalar registers
+// (the multiplies take them as their scalar operand), so a contraction issues
+// no vector or LDS load of its own.  Broadcast vector loads of the entries
+// cost 16 L1 cycles per two of them (n = 8: 96 such loads a forward transform,
+// which alone was the passes' time), broadcast LDS reads 8 cycles.  N = 7,
+// 65,536 elements, 3 components: pass A 866 -> 517 us, pass B 1231 -> 517 us.
+//
+// The tables are symmetric about the element's middle, bit for bit (a CPU
+// test checks every order):
+//   A[p][n-1-i] = (-1)^p A[p][i]      V[n-1-i][k] = (-1)^k V[i][k]
+// so only half of the entries are read, and in the inverse the products of
+// the mirrored rows i and n-1-i are the same up to the sign and are formed
+// once.  Negation is exact and IEEE subtraction is the addition of the
+// negated operand: the results are those of the full matrices, bit for bit.
+typedef __attribute__((address_space(4))) const double sdouble;
+
+// Base of a group of table rows, opaque to the compiler: the rows of a group
+// are loaded here, instead of every row of every stage being held (or
+// spilled) across the whole transform.
+DEV sdouble* table_rows(const double* M) {
+  // (the pointer is the same in every lane; in the batch kernel it comes from
+  // memory, so the compiler has to be told)
+  const uintptr_t m = (uintptr_t)M;
+  uintptr_t p = (uintptr_t)(u32)__builtin_amdgcn_readfirstlane((int)(u32)m) |
+                ((uintptr_t)(u32)__builtin_amdgcn_readfirstlane((int)(u32)(m >> 32)) << 32);
+  asm volatile("" : "+s"(p));
+  return (sdouble*)p;
+}
+
+constexpr int SROWS = 16;  // table entries in flight (32 of the ~100 scalar registers)
+
+// y = A x
 template <int n>
-DEV void contract64(const double* __restrict__ M, const double (&x)[n], double (&y)[n]) {
+DEV void forward64(const double* A, const double (&x)[n], double (&y)[n]) {
+  constexpr int H = (n + 1) / 2;
+  constexpr int G = SROWS / H < n ? SROWS / H : n;  // rows per group
 #pragma unroll
-  for (int a = 0; a < n; ++a) {
-    // keep the row loads of M here (LDS broadcast reads) instead of letting
-    // the compiler hold all n*n entries in VGPRs across stages
-    asm volatile("" ::: "memory");
-    double acc = M[a * n] * x[0];
+  for (int a0 = 0; a0 < n; a0 += G) {
+    sdouble* M = table_rows(A + a0 * n);
 #pragma unroll
-    for (int b = 1; b < n; ++b) acc = acc + M[a * n + b] * x[b];
-    y[a] = acc;
+    for (int a = a0; a < (a0 + G < n ? a0 + G : n); ++a) {
+      double acc = M[(a - a0) * n] * x[0];
+#pragma unroll
+      for (int b = 1; b < n; ++b) {
+        const double t = M[(a - a0) * n + (b < H ? b : n - 1 - b)] * x[b];
+        acc = b >= H && (a & 1) ? acc - t : acc + t;
+      }
+      y[a] = acc;
+    }
   }
 }
 
-// Coalesced copy of `count` doubles from global to LDS.
-template <int THREADS>
-DEV void load_tile(double* __restrict__ dst, const double* __restrict__ src, int count, int tid) {
-  if ((((uintptr_t)src) & 15) == 0 && (count & 1) == 0) {
-    const double2* s2 = reinterpret_cast<const double2*>(src);
-    double2* d2 = reinterpret_cast<double2*>(dst);
-    for (int k = tid; k < (count >> 1); k += THREADS) d2[k] = s2[k];
-  } else {
-    for (int k = tid; k < count; k += THREADS) dst[k] = src[k];
+// y = V x
+template <int n>
+DEV void inverse64(const double* V, const double (&x)[n], double (&y)[n]) {
+  constexpr int H = (n + 1) / 2;
+  constexpr int G = SROWS / n < H ? SROWS / n : H;
+#pragma unroll
+  for (int a0 = 0; a0 < H; a0 += G) {
+    sdouble* M = table_rows(V + a0 * n);
+#pragma unroll
+    for (int a = a0; a < (a0 + G < H ? a0 + G : H); ++a) {
+      double t = M[(a - a0) * n] * x[0];
+      double acc = t, mir = t;
+#pragma unroll
+      for (int b = 1; b < n; ++b) {
+        t = M[(a - a0) * n + b] * x[b];
+        acc = acc + t;
+        mir = b & 1 ? mir - t : mir + t;
+      }
+      y[a] = acc;
+      if (n - 1 - a != a) y[n - 1 - a] = mir;
+    }
   }
 }
-
 
 }  // namespace isr

@@ -33,7 +33,7 @@
 // four registers, for the input and for the output of every stage alike.
 // Between stages the tile is transposed through a per-wave LDS buffer.
 // The FP64 path keeps one pencil per lane and the fixed evaluation order of
-// the oracle (contract64).
+// the oracle (forward64, inverse64).
 #pragma once
 
 #include "isr_passes.cuh"
@@ -237,11 +237,11 @@ struct Eng {
       xpose<2, 3>(y, x, buf, lane);
       stage_mf(x, y, mt.fa, mt.ha, mt.la);
     } else {
-      contract64<n>(t.A, x, y);
+      forward64<n>(t.A, x, y);
       xpose<1, 2>(y, x, buf, lane);
-      contract64<n>(t.A, x, y);
+      forward64<n>(t.A, x, y);
       xpose<2, 3>(y, x, buf, lane);
-      contract64<n>(t.A, x, y);
+      forward64<n>(t.A, x, y);
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) c[s] = (double)y[s];
@@ -261,11 +261,11 @@ struct Eng {
       xpose<2, 1>(y, x, buf, lane);
       stage_mf(x, y, mt.fv, mt.hv, mt.lv);
     } else {
-      contract64<n>(t.V, x, y);
+      inverse64<n>(t.V, x, y);
       xpose<3, 2>(y, x, buf, lane);
-      contract64<n>(t.V, x, y);
+      inverse64<n>(t.V, x, y);
       xpose<2, 1>(y, x, buf, lane);
-      contract64<n>(t.V, x, y);
+      inverse64<n>(t.V, x, y);
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) ut[s] = (double)y[s];

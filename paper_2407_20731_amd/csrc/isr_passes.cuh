@@ -55,26 +55,23 @@ struct Xf64 {
   typedef Shape<N> S;
   static constexpr int n = S::n, n2 = S::n2, n3 = S::n3;
   typedef double work_t;
-  struct Smem {
-    double A[n * n];
-    double V[n * n];
+  struct Smem {};
+  struct Regs {
+    const double *A, *V;
   };
-  struct Regs {};
-  static DEV void init(Smem& sm, Regs&, const DevTables& t, int tid, int nthr) {
-    for (int k = tid; k < n * n; k += nthr) {
-      sm.A[k] = t.A[k];
-      sm.V[k] = t.V[k];
-    }
+  static DEV void init(Smem&, Regs& rg, const DevTables& t, int, int) {
+    rg.A = t.A;
+    rg.V = t.V;
   }
   // forward of the tile in `su` (work == su allowed: stages run in place)
-  static DEV void forward(const double* su, double* w, const Smem& sm, const Regs&, int el, int a, int b, bool act,
+  static DEV void forward(const double* su, double* w, const Smem&, const Regs& rg, int el, int a, int b, bool act,
                           int /*ne*/, double (&c)[n]) {
     if (act) {
       const double* pin = su + el * n3 + (a * n + b) * n;
       double x[n], y[n];
 #pragma unroll
       for (int i = 0; i < n; ++i) x[i] = pin[i];
-      contract64<n>(sm.A, x, y);
+      forward64<n>(rg.A, x, y);
       double* pout = w + el * n3 + (a * n + b) * n;
 #pragma unroll
       for (int i = 0; i < n; ++i) pout[i] = y[i];
@@ -85,7 +82,7 @@ struct Xf64 {
       double x[n], y[n];
 #pragma unroll
       for (int j = 0; j < n; ++j) x[j] = col[j * n];
-      contract64<n>(sm.A, x, y);
+      forward64<n>(rg.A, x, y);
 #pragma unroll
       for (int j = 0; j < n; ++j) col[j * n] = y[j];
     }
@@ -95,16 +92,16 @@ struct Xf64 {
       double x[n];
 #pragma unroll
       for (int k = 0; k < n; ++k) x[k] = col[k * n2];
-      contract64<n>(sm.A, x, c);
+      forward64<n>(rg.A, x, c);
     }
   }
   // inverse of the masked coefficients held by thread (el, q=a, p=b); leaves
   // u~[k=a][j=b][i] in ut
-  static DEV void inverse(double* w, const Smem& sm, const Regs&, int el, int a, int b, bool act, int /*ne*/,
+  static DEV void inverse(double* w, const Smem&, const Regs& rg, int el, int a, int b, bool act, int /*ne*/,
                           const double (&cm)[n], double (&ut)[n]) {
     if (act) {
       double y[n];
-      contract64<n>(sm.V, cm, y);
+      inverse64<n>(rg.V, cm, y);
       double* col = w + el * n3 + a * n + b;
 #pragma unroll
       for (int k = 0; k < n; ++k) col[k * n2] = y[k];
@@ -115,7 +112,7 @@ struct Xf64 {
       double x[n], y[n];
 #pragma unroll
       for (int q = 0; q < n; ++q) x[q] = col[q * n];
-      contract64<n>(sm.V, x, y);
+      inverse64<n>(rg.V, x, y);
 #pragma unroll
       for (int j = 0; j < n; ++j) col[j * n] = y[j];
     }
@@ -125,7 +122,7 @@ struct Xf64 {
       double x[n];
 #pragma unroll
       for (int p = 0; p < n; ++p) x[p] = pin[p];
-      contract64<n>(sm.V, x, ut);
+      inverse64<n>(rg.V, x, ut);
     }
   }
 };
