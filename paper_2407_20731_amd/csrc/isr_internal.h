@@ -279,8 +279,10 @@ int resident_fast_fp32(int kind, int order);
 int resident_fast_bf16(int kind, int order);
 // Decompression of FP32 / BF16 blobs with the inverse of the engine that made
 // them (the reconstruction pass B measured): wave-tile or large-order engine
-// (tile 0, by order), or dense-tile engine (j.tile).
+// (tile 0, by order), or dense-tile engine (j.tile).  The wave-tile form also
+// takes FP64 blobs of orders 1..FAST_MAX_ORDER (one inverse order for all).
 enum BlobEngine { ENG_GENERAL = 0, ENG_WAVE = 1, ENG_DENSE = 2 };
+hipError_t launch_decomp_wave_fp64(const Job& j, int gx, hipStream_t s, void* out, int out_fp64);
 hipError_t launch_decomp_wave_fp32(const Job& j, int gx, hipStream_t s, void* out, int out_fp64);
 hipError_t launch_decomp_wave_bf16(const Job& j, int gx, hipStream_t s, void* out, int out_fp64);
 hipError_t launch_decomp_dense_fp32(const Job& j, int gx, hipStream_t s, void* out, int out_fp64);
