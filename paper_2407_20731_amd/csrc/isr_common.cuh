@@ -32,6 +32,9 @@ DEV int lane_id() { return (int)__lane_id(); }
 
 // ---- wave helpers -----------------------------------------------------------
 DEV u64 ballot(bool p) { return (u64)__ballot(p); }
+// this lane's bit of a wave mask, and the set bits below it
+DEV bool lane_bit(u64 m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+DEV u32 lane_rank(u64 m) { return __builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, 0u)); }
 DEV u64 bcast64(u64 v, int src) {
   u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)v, src);
   u32 hi = (u32)__builtin_amdgcn_readlane((int)(u32)(v >> 32), src);

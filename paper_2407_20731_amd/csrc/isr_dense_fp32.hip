@@ -7,8 +7,8 @@ namespace isr {
 
 hipError_t launch_dense_fp32(int kind, const Job& j, int gx, hipStream_t s) { return launch_dense_prec<P_FP32>(kind, j, gx, s); }
 
-hipError_t launch_decomp_dense_fp32(const Job& j, int gx, hipStream_t s, void* out, int out_fp64) {
-  return launch_decompD_prec<P_FP32>(j, gx, s, out, out_fp64);
+hipError_t launch_decomp_dense_fp32(const Job& j, int gx, int cus, hipStream_t s, void* out, int out_fp64) {
+  return launch_decompD_prec<P_FP32>(j, gx, cus, s, out, out_fp64);
 }
 
 int resident_dense_fp32(int kind, int order, int tile) { return resident_dense_prec<P_FP32>(kind, order, tile); }

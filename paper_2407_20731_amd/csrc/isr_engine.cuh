@@ -857,8 +857,6 @@ __global__ __launch_bounds__(256, ISR_FAST_MINB) void k_passB(Job j) {
 // non-temporal (nothing here reads them back; as ordinary stores the same
 // kernel takes 217 and 103 us).  65,536 elements, N = 7, 3 components: FP64 to
 // FP64 358 -> 156 us (5.2 TB/s written), BF16 to FP32 305 -> 85 us (4.7 TB/s).
-DEV bool lane_bit(u64 m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
-DEV u32 lane_rank(u64 m) { return __builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, 0u)); }
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int N, int PREC, bool OUT64>
@@ -995,19 +993,39 @@ __global__ __launch_bounds__(256, 4) void k_decompW(Job j, void* out) {
   }
 }
 
+// Grid of a decompression: gx workgroups per component cover its tiles once;
+// no more than are resident at once are launched (each wavefront then walks
+// several tiles and loads ahead), so that no partial second round is left.
+inline int resident_wgs(const void* kernel) {
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, 256, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    return 2;
+  }
+  return nb > 0 ? nb : 1;
+}
+inline dim3 decomp_grid(const Job& j, int gx, int nb, int cus) {
+  const int most = cus * nb / j.ncomp;
+  return dim3(gx < most ? gx : (most > 0 ? most : 1), j.ncomp);
+}
+
 // ---- launchers ------------------------------------------------------------------
 #define ISR_FAST_ORDERS(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7)
 
 template <int PREC>
-hipError_t launch_decompW_prec(const Job& j, int gx, hipStream_t s, void* out, int out_fp64) {
+hipError_t launch_decompW_prec(const Job& j, int gx, int cus, hipStream_t s, void* out, int out_fp64) {
   switch (j.order) {
 #define CASE(NN)                                                                       \
   case NN:                                                                             \
+  {                                                                                    \
+    static const int nb = resident_wgs((const void*)k_decompW<NN, PREC, true>),        \
+                     nb32 = resident_wgs((const void*)k_decompW<NN, PREC, false>);     \
     if (out_fp64)                                                                      \
-      hipLaunchKernelGGL((k_decompW<NN, PREC, true>), dim3(gx, j.ncomp), dim3(256), 0, s, j, out); \
+      hipLaunchKernelGGL((k_decompW<NN, PREC, true>), decomp_grid(j, gx, nb, cus), dim3(256), 0, s, j, out); \
     else                                                                               \
-      hipLaunchKernelGGL((k_decompW<NN, PREC, false>), dim3(gx, j.ncomp), dim3(256), 0, s, j, out); \
-    break;
+      hipLaunchKernelGGL((k_decompW<NN, PREC, false>), decomp_grid(j, gx, nb32, cus), dim3(256), 0, s, j, out); \
+    break;                                                                             \
+  }
     ISR_FAST_ORDERS(CASE)
 #undef CASE
     default:

@@ -282,11 +282,13 @@ int resident_fast_bf16(int kind, int order);
 // (tile 0, by order), or dense-tile engine (j.tile).  The wave-tile form also
 // takes FP64 blobs of orders 1..FAST_MAX_ORDER (one inverse order for all).
 enum BlobEngine { ENG_GENERAL = 0, ENG_WAVE = 1, ENG_DENSE = 2 };
-hipError_t launch_decomp_wave_fp64(const Job& j, int gx, hipStream_t s, void* out, int out_fp64);
-hipError_t launch_decomp_wave_fp32(const Job& j, int gx, hipStream_t s, void* out, int out_fp64);
-hipError_t launch_decomp_wave_bf16(const Job& j, int gx, hipStream_t s, void* out, int out_fp64);
-hipError_t launch_decomp_dense_fp32(const Job& j, int gx, hipStream_t s, void* out, int out_fp64);
-hipError_t launch_decomp_dense_bf16(const Job& j, int gx, hipStream_t s, void* out, int out_fp64);
+// gx: workgroups of four wavefronts that give every tile of a component its own
+// wavefront; cus: compute units (the launch takes no more than are resident)
+hipError_t launch_decomp_wave_fp64(const Job& j, int gx, int cus, hipStream_t s, void* out, int out_fp64);
+hipError_t launch_decomp_wave_fp32(const Job& j, int gx, int cus, hipStream_t s, void* out, int out_fp64);
+hipError_t launch_decomp_wave_bf16(const Job& j, int gx, int cus, hipStream_t s, void* out, int out_fp64);
+hipError_t launch_decomp_dense_fp32(const Job& j, int gx, int cus, hipStream_t s, void* out, int out_fp64);
+hipError_t launch_decomp_dense_bf16(const Job& j, int gx, int cus, hipStream_t s, void* out, int out_fp64);
 hipError_t launch_gather(const Job& j, int grid_x, hipStream_t s);
 hipError_t launch_count(const Job& j, int grid_x, hipStream_t s);
 constexpr int SCAN_CHUNK = 1024;  // elements per chunk of the element-offset scan

@@ -24,8 +24,8 @@ hipError_t launch_fast_fp64(int kind, const Job& j, int gx, hipStream_t s) {
   return launch_fast_prec<P_FP64>(kind, j, gx, s);
 }
 
-hipError_t launch_decomp_wave_fp64(const Job& j, int gx, hipStream_t s, void* out, int out_fp64) {
-  return launch_decompW_prec<P_FP64>(j, gx, s, out, out_fp64);
+hipError_t launch_decomp_wave_fp64(const Job& j, int gx, int cus, hipStream_t s, void* out, int out_fp64) {
+  return launch_decompW_prec<P_FP64>(j, gx, cus, s, out, out_fp64);
 }
 
 int resident_fast_fp64(int kind, int order) { return resident_fast_prec<P_FP64>(kind, order); }

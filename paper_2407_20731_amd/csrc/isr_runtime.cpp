@@ -1452,36 +1452,27 @@ int isr_decompress(isr_ctx* c, const isr_blob* b, void* d_out, int32_t out_prec,
   const int ofp64 = out_prec == ISR_PREC_FP64;
   hipStream_t s = (hipStream_t)stream;
   const int prec = b->vbytes == 8 ? ISR_PREC_FP64 : b->precision;
-  // wave tiles of orders up to FAST_MAX_ORDER: their own FP32 / BF16 blobs,
-  // and every FP64 blob (the fixed-order inverse is the same in every kernel);
-  // workgroups per component, each wavefront walks several tiles
-  if (b->order <= FAST_MAX_ORDER && (b->engine == ENG_WAVE || prec == ISR_PREC_FP64)) {
-    const long long epw = fast_epw(b->order, 0), tiles = (b->n_elem + epw - 1) / epw;
-    const int gx = (int)std::max<long long>(1, std::min<long long>((tiles + 3) / 4, (long long)c->num_cu * 8 / b->ncomp));
-    HIPCHK(prec == ISR_PREC_FP64   ? launch_decomp_wave_fp64(j, gx, s, d_out, ofp64)
-           : prec == ISR_PREC_FP32 ? launch_decomp_wave_fp32(j, gx, s, d_out, ofp64)
-                                   : launch_decomp_wave_bf16(j, gx, s, d_out, ofp64));
-    return ISR_OK;
-  }
-  if (b->engine == ENG_GENERAL) {
-    // FP64 blobs: the fixed-order FP64 inverse; FP32 / BF16 blobs of the
-    // general passes: their MFMA inverse
+  // one tile (or element) per wavefront in every engine's kernel
+  const bool dense = b->engine == ENG_DENSE, bf = prec == ISR_PREC_BF16;
+  const long long epw = dense ? b->tile : fast_epw(b->order, 0), tiles = (b->n_elem + epw - 1) / epw;
+  const int gx = (int)std::min<long long>((tiles + 3) / 4, 1 << 24), cus = c->num_cu;
+  if (dense) {
+    j.tile = b->tile;
+    HIPCHK(bf ? launch_decomp_dense_bf16(j, gx, cus, s, d_out, ofp64)
+              : launch_decomp_dense_fp32(j, gx, cus, s, d_out, ofp64));
+  } else if (b->order <= FAST_MAX_ORDER && prec == ISR_PREC_FP64) {
+    // every FP64 blob of these orders: the fixed-order inverse is the same in
+    // every kernel
+    HIPCHK(launch_decomp_wave_fp64(j, gx, cus, s, d_out, ofp64));
+  } else if (b->engine == ENG_WAVE) {
+    HIPCHK(bf ? launch_decomp_wave_bf16(j, gx, cus, s, d_out, ofp64)
+              : launch_decomp_wave_fp32(j, gx, cus, s, d_out, ofp64));
+  } else {
+    // workgroup tiles: the FP64 fixed-order inverse, or the general passes'
+    // MFMA inverse
     const long long total = (long long)tiles_per_comp(b->order, b->n_elem) * b->ncomp;
-    const int grid = (int)std::min<long long>(total, (long long)c->num_cu * 8);
-    HIPCHK(launch_pass(K_DECOMP, prec, j, grid, s, d_out, ofp64));
-    return ISR_OK;
+    HIPCHK(launch_pass(K_DECOMP, prec, j, (int)std::min<long long>(total, (long long)cus * 8), s, d_out, ofp64));
   }
-  // FP32 / BF16 blobs of the dense-tile engine and of the large-order engine:
-  // that engine's inverse, one tile (or element) per wavefront
-  j.tile = b->tile;
-  const long long epw = b->engine == ENG_DENSE ? b->tile : fast_epw(b->order, 0);
-  const long long waves = (b->n_elem + epw - 1) / epw * b->ncomp;
-  const int grid = (int)std::max<long long>(1, std::min<long long>((waves + 3) / 4, (long long)c->num_cu * 8));
-  const bool bf = prec == ISR_PREC_BF16;
-  if (b->engine == ENG_DENSE)
-    HIPCHK(bf ? launch_decomp_dense_bf16(j, grid, s, d_out, ofp64) : launch_decomp_dense_fp32(j, grid, s, d_out, ofp64));
-  else
-    HIPCHK(bf ? launch_decomp_wave_bf16(j, grid, s, d_out, ofp64) : launch_decomp_wave_fp32(j, grid, s, d_out, ofp64));
   return ISR_OK;
 }
 

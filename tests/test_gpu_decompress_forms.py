@@ -64,3 +64,36 @@ def test_quantised_blob_to_fp32(order, n_elem):
         torch.cuda.synchronize()
         assert torch.equal(d64.float(), d32)
         blob.free()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("order,tile,n_elem", [(1, 64, 65), (2, 16, 17), (4, 8, 3), (5, 4, 9), (6, 3, 4), (8, 1, 2), (9, 2, 5),
+                                               (10, 1, 3)])
+@pytest.mark.parametrize("tol", [-1.0, 1e-2])
+def test_dense_tile_blob_both_output_types(order, tile, n_elem, tol, prec):
+    u = synth.field(n_elem, order, ncomp=2, seed=5 * order + n_elem)
+    u[1, n_elem // 2] = 0.0
+    n = order + 1
+    with isr.Context(device=0) as ctx:
+        ctx.set_tile(order, prec, tile)
+        blob = ctx.compress(torch.from_numpy(u).cuda(), order, tol, prec)
+        d64 = ctx.decompress(blob)
+        raw = torch.full((u.size + 4,), 7.0, dtype=torch.float32, device="cuda")
+        d32 = raw[2:2 + u.size].view(2, n_elem, n, n, n)  # 8-byte aligned only
+        ctx.decompress(blob, out=d32)
+        torch.cuda.synchronize()
+        assert torch.equal(d64.float(), d32) and torch.equal(d32.double(), d64)
+        assert (raw[:2] == 7.0).all() and (raw[2 + u.size:] == 7.0).all()
+        # the oracle's inverse of the kept values; the transform error of the
+        # BF16 split is about 2^-16 of the coefficients' scale, FP32's 2^-24
+        arr = blob.arrays()
+        T = oracle.tables.gll_tables(order)
+        coef = np.zeros((2, n_elem, n ** 3))
+        for c in range(2):
+            bits = np.unpackbits(arr.bitmap[c].view(np.uint8).reshape(n_elem, -1), axis=1, bitorder="little")
+            coef[c][bits[:, :n ** 3].astype(bool)] = arr.values[c]
+        x = coef.reshape(2, n_elem, n, n, n)
+        full = np.einsum("kr,jq,ip,cerqp->cekji", T.V, T.V, T.V, x, optimize=True)
+        scale = np.einsum("kr,jq,ip,cerqp->cekji", abs(T.V), abs(T.V), abs(T.V), abs(x), optimize=True).max()
+        assert np.abs(d64.cpu().numpy() - full).max() <= (2.0 ** -12 if prec == "bf16" else 2.0 ** -20) * scale
+        blob.free()
