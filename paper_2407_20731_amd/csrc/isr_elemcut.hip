@@ -13,7 +13,7 @@
 // sums: every lane splits its terms by error-free extraction against 2^m >=
 // the wave's largest term into three FP64 sums (exact), their wave totals
 // form one 192-bit integer in a wave big integer (X units of 2^-1075), and
-// the rare remainders (bits far below 2^m) go through 32-bit digits in LDS;
+// the rare terms far below 2^m go through 32-bit digits in LDS;
 // the result is rounded once.  The workgroup adds every element's exact norm
 // and dropped energy into per-component digit totals, and the finishing
 // kernel rounds the component totals.  Compaction, the inverse and the exact
@@ -117,15 +117,16 @@ DEV u64 exact_words(const double (&x)[CNT], const bool (&take)[CNT], u64* D) {
   m = m < XM_MIN ? XM_MIN : (m > XM_MAX ? XM_MAX : m);
   constexpr int h = 7;  // a lane adds at most 64 = 2^(h-1) terms
   const XParm P = xparm(m, h);
-  XAcc A = {0.0, 0.0, 0.0};
+  const XRange R = xrange(P);
+  XRun A = xrun(P);
   bool rem = false;
 #pragma unroll
   for (int k = 0; k < CNT; ++k) {
-    double left;
-    rem = xadd_left(A, P, take[k] ? x[k] : 0.0, left) || rem;
+    const double y = take[k] ? x[k] : 0.0;
+    rem = (xrun_left(A, R, y) && y != 0.0) || rem;
   }
   long long K[3];
-  xints(A, P, K);
+  xints(xrun_sums(A, P), P, K);
   I192 z = {{0ull, 0ull, 0ull}};
   const int sft[3] = {107 - 2 * h, 53 - h, 0};
 #pragma unroll
@@ -142,9 +143,8 @@ DEV u64 exact_words(const double (&x)[CNT], const bool (&take)[CNT], u64* D) {
     ed_clear(D);
 #pragma unroll
     for (int k = 0; k < CNT; ++k) {
-      XAcc scratch = {0.0, 0.0, 0.0};
-      double left = 0.0;
-      if (xadd_left(scratch, P, take[k] ? x[k] : 0.0, left) && left != 0.0) ed_add(D, left);
+      const double y = take[k] ? x[k] : 0.0;
+      if (!xin(R, y) && y != 0.0) ed_add(D, y);
     }
     wb_add(w, ed_words(D));
   }

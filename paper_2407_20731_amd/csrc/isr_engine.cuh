@@ -46,7 +46,7 @@
 // the 65,536-element N = 7 snapshot: the FP64 transforms want 2 (fewer
 // workgroups beat spilling), the MFMA paths 3.
 #ifndef ISR_FAST_MINB_F64
-#define ISR_FAST_MINB_F64 2
+#define ISR_FAST_MINB_F64 4
 #endif
 #ifndef ISR_FAST_MINB_MIX
 #define ISR_FAST_MINB_MIX 3
@@ -138,6 +138,15 @@ struct Eng {
     }
   }
 
+  // Jacobians of this lane's slots (zero outside the tile): one value on the
+  // FP64 path and at n = 8 (a lane's pencils lie in one element there), else
+  // one a slot
+  static constexpr int JS = !MF || n == 8 ? 1 : NS;
+  static DEV void load_jac(const double* __restrict__ jac, int ne, double (&jq)[JS], int lane) {
+#pragma unroll
+    for (int s = 0; s < JS; ++s) jq[s] = valid(s, lane, ne) ? jac[elem(s, lane)] : 0.0;
+  }
+
   // One contraction on every pencil of the tile.
   static DEV void stage_mf(const wt (&x)[NS], wt (&y)[NS], const float (&f)[4], s4 h, s4 l) {
     static_assert(MF, "MFMA stage");
@@ -224,27 +233,37 @@ struct Eng {
   }
 
   // forward: contract i (pattern 1 -> 2), j (2 -> 3), k; slots of the field
-  // tile in, slots of the coefficients (pencil (q, p), index r) out
-  static DEV void forward(const double (&u)[NS], double (&c)[NS], wt* buf, const Mats& mt, const DevTables& t,
-                          int lane) {
-    wt x[NS], y[NS];
+  // tile in, slots of the coefficients (pencil (q, p), index r) out.  In two
+  // parts, so that a pass can reuse the field's registers after the first.
+  static DEV void forward1(const double (&u)[NS], wt (&x)[NS], wt* buf, const Mats& mt, const DevTables& t, int lane) {
+    wt y[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) x[s] = (wt)u[s];
-    if constexpr (MF) {
+    if constexpr (MF)
       stage_mf(x, y, mt.fa, mt.ha, mt.la);
-      xpose<1, 2>(y, x, buf, lane);
+    else
+      forward64<n>(t.A, x, y);
+    xpose<1, 2>(y, x, buf, lane);
+  }
+  static DEV void forward2(wt (&x)[NS], double (&c)[NS], wt* buf, const Mats& mt, const DevTables& t, int lane) {
+    wt y[NS];
+    if constexpr (MF) {
       stage_mf(x, y, mt.fa, mt.ha, mt.la);
       xpose<2, 3>(y, x, buf, lane);
       stage_mf(x, y, mt.fa, mt.ha, mt.la);
     } else {
-      forward64<n>(t.A, x, y);
-      xpose<1, 2>(y, x, buf, lane);
       forward64<n>(t.A, x, y);
       xpose<2, 3>(y, x, buf, lane);
       forward64<n>(t.A, x, y);
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) c[s] = (double)y[s];
+  }
+  static DEV void forward(const double (&u)[NS], double (&c)[NS], wt* buf, const Mats& mt, const DevTables& t,
+                          int lane) {
+    wt x[NS];
+    forward1(u, x, buf, mt, t, lane);
+    forward2(x, c, buf, mt, t, lane);
   }
 
   // inverse: contract r (3 -> 2), q (2 -> 1), p; coefficient slots in, field
@@ -464,6 +483,8 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
   const int wlo = st->win_lo, whi = st->win_hi;
   const XParm PN = xparm(st->xm_norm, j.xh);
   const XParm PE = xparm(wlo - 1023, j.xh);
+  const XRange RN = xrange(PN), RE = xrange(PE);  // FP64 path
+  const u32 hwlo = (u32)wlo << 20, hwhi = (u32)whi << 20;  // the window's edges as high words of energies
   HistBin* gN = j.histN + (size_t)comp * HBINS;
   HistBin* gE = j.histE + (size_t)comp * HBINS;
   u64* list = list_ptr(j, comp, 0);
@@ -475,6 +496,7 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
   tab_load<G>(L.tab, j.tab, tid);
   __syncthreads();
   XAcc an = {0.0, 0.0, 0.0}, ae = {0.0, 0.0, 0.0};
+  XRun rn = xrun(PN), re = xrun(PE);  // FP64 path
   double pe = 0.0;  // fixed-order sum of the energies below the window
   double pn = 0.0;  // MFMA paths: fixed-order sum of the norm terms
   u64 hi_tot = 0ull;
@@ -482,29 +504,46 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
   const double* ub = j.u + (size_t)comp * j.comp_stride;
   const bool vec = ((((uintptr_t)ub) & 15) == 0);
   const long long nw = (long long)nvb * 4;
-  // the next tile's field values are loaded while this one is processed
-  double un[NS];
-  {
-    const long long t0 = (long long)vb * 4 + wv;
-    if (t0 < tiles) G::load(ub + t0 * EPW * n3, (int)((E - t0 * EPW) < EPW ? (E - t0 * EPW) : EPW), vec, un, lane);
-  }
+  // the next tile's field values (and Jacobians) are loaded while this one is
+  // processed: at the top of the tile on the MFMA paths (which wait for memory
+  // more than they issue; 196 us at N = 7 BF16 against 214 with the later
+  // load), on the FP64 path into the same registers once the first contraction
+  // has taken the values (issue bound: 16 registers and copies less).  The wait
+  // for them also waits for every store issued since, so a tile's counts are
+  // stored with the next tile's loads, just ahead of them.
+  constexpr bool EARLY = G::MF;
+  double u[NS], un[EARLY ? NS : 1], jq[G::JS];
+  auto fetch = [&](long long t) {
+    const long long e0 = t * EPW;
+    const int ne = (int)((E - e0) < EPW ? (E - e0) : EPW);
+    if constexpr (EARLY)
+      G::load(ub + e0 * n3, ne, vec, un, lane);
+    else
+      G::load(ub + e0 * n3, ne, vec, u, lane);
+    if (j.jac) G::load_jac(j.jac + e0, ne, jq, lane);
+  };
+  long long cnt_e = -1;  // this lane's element with a count to be stored, and the count
+  u32 cnt_v = 0u;
+  if ((long long)vb * 4 + wv < tiles) fetch((long long)vb * 4 + wv);
   for (long long t = (long long)vb * 4 + wv; t < tiles; t += nw) {
     const long long e0 = t * EPW;
     const int ne = (int)((E - e0) < EPW ? (E - e0) : EPW);
-    double u[NS], c[NS];
+    double c[NS];
+    double jt[G::JS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) u[s] = un[s];
-    if (t + nw < tiles) {
-      const long long e1 = (t + nw) * EPW;
-      G::load(ub + e1 * n3, (int)((E - e1) < EPW ? (E - e1) : EPW), vec, un, lane);
+    for (int s = 0; s < G::JS; ++s) jt[s] = jq[s];
+    if constexpr (EARLY) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) u[s] = un[s];
+      if (cnt_e >= 0) cnt[cnt_e] = cnt_v;
+      if (t + nw < tiles) fetch(t + nw);
     }
     // quadrature weights of the slots (times the element's Jacobian), with the
     // Jacobian test taken once per tile
     double wq[NS];
     if (j.jac) {
 #pragma unroll
-      for (int s = 0; s < NS; ++s)
-        wq[s] = G::valid(s, lane, ne) ? j.jac[e0 + G::elem(s, lane)] * L.tab.w3[s][lane] : 0.0;
+      for (int s = 0; s < NS; ++s) wq[s] = jt[s % G::JS] * L.tab.w3[s][lane];
     } else {
 #pragma unroll
       for (int s = 0; s < NS; ++s) wq[s] = L.tab.w3[s][lane];
@@ -512,12 +551,13 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
     // norm terms: every term split exactly on the FP64 path; on the MFMA
     // paths each lane sums its terms in a fixed FP64 order and only the lane
     // totals are added exactly (as for the energies and the error terms)
+    bool odd = false;  // a term out of the running sums' range
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      const double x = G::valid(s, lane, ne) ? wq[s] * (u[s] * u[s]) : 0.0;
+      const bool v = G::valid(s, lane, ne);
+      const double x = v ? wq[s] * (u[s] * u[s]) : 0.0;
       if constexpr (EXACT) {
-        double r;
-        if (xadd_left(an, PN, x, r)) slow_bin(gN, r);
+        odd = (xrun_left(rn, RN, x) && v) || odd;
         // one slot at a time: interleaving them would hold every slot's
         // temporaries at once and cut the occupancy
         __builtin_amdgcn_sched_barrier(0);
@@ -525,16 +565,32 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
         pn += x;
       }
     }
-    G::forward(u, c, L.buf[wv], mt, j.tab, lane);
+    if constexpr (EXACT) {
+      if (ballot(odd)) {  // rare: one vote a tile keeps this out of the slots' way
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const double x = G::valid(s, lane, ne) ? wq[s] * (u[s] * u[s]) : 0.0;
+          if (!xin(RN, x)) slow_bin(gN, x);
+        }
+      }
+      odd = false;
+    }
+    if constexpr (EXACT) pin(rn);
+    typename G::wt x1[NS];
+    G::forward1(u, x1, L.buf[wv], mt, j.tab, lane);
+    if constexpr (!EARLY) {
+      if (cnt_e >= 0) cnt[cnt_e] = cnt_v;
+      if (t + nw < tiles) fetch(t + nw);
+    }
+    G::forward2(x1, c, L.buf[wv], mt, j.tab, lane);
     if (EPW > 1) {
       if (lane < EPW) L.ecnt[wv][lane] = 0u;
       asm volatile("" ::: "memory");
     }
-    u32 hc = 0u;
+    u32 hc = 0u, hmax = 0u;
     if (j.jac) {
 #pragma unroll
-      for (int s = 0; s < NS; ++s)
-        wq[s] = G::valid(s, lane, ne) ? j.jac[e0 + G::elem(s, lane)] * L.tab.g3[s][lane] : 0.0;
+      for (int s = 0; s < NS; ++s) wq[s] = jt[s % G::JS] * L.tab.g3[s][lane];
     } else {
 #pragma unroll
       for (int s = 0; s < NS; ++s) wq[s] = L.tab.g3[s][lane];
@@ -544,10 +600,12 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
       const bool v = G::valid(s, lane, ne);
       const double en = v ? wq[s] * (c[s] * c[s]) : 0.0;
       const u64 key = dbits(en);
-      const int ex = bits_exp(key);
-      const bool hi = v && ex >= whi;
-      const bool cp = v && ex < whi && ex >= wlo;
-      const bool nf = hi && ex == HBINS - 1;  // Inf/NaN: counted in the flag bin
+      // below, inside or above the window by the high words alone (its edges
+      // are powers of two; Inf and NaN, whatever their sign, are above)
+      const u32 hw = hi_word(en);
+      const bool hi = v && hw >= hwhi;
+      const bool cp = v && hw < hwhi && hw >= hwlo;
+      hmax = hw > hmax ? hw : hmax;
       // the wave votes first: lane flags that stay live across the divergent
       // branches below would be copied through vector registers on every slot
       const u64 bh = ballot(hi);
@@ -566,36 +624,57 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
           cap_flush(L.key[wv], L.idx[wv], ncap, st, list, lidx, j.list_cap, lane);
         }
       }
-      if constexpr (EXACT) {
-        double r = xadd_r(ae, PE, (v && ex < wlo) ? en : 0.0);
-        if (nf) r = en;
-        if (r != 0.0) slow_bin(gE, r);
+      if constexpr (EXACT) {  // (the running sums' range ends at the window)
+        const bool tiny = hw < RE.lo;
+        xrun_add(re, hw < hwlo && !tiny ? en : 0.0);
+        odd = (tiny && v) || odd;
       } else {
-        pe += (v && ex < wlo) ? en : 0.0;
-        if (nf) slow_bin(gE, en);
+        pe += hw < hwlo ? en : 0.0;  // (zero in masked slots)
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (EXACT) pin(re);
+    if constexpr (EXACT) {
+      if (ballot(odd)) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const double en = G::valid(s, lane, ne) ? wq[s] * (c[s] * c[s]) : 0.0;
+          if (hi_word(en) < RE.lo) slow_bin(gE, en);
+        }
+      }
+    }
+    if (hmax >= 0x7ff00000u) slow_bin(gE, __builtin_inf());  // Inf/NaN: counted in the flag bin
     hi_tot += hc;
     if (EPW == 1) {
-      if (lane == 0) cnt[e0] = hc;
+      cnt_e = lane == 0 ? e0 : -1;
+      cnt_v = hc;
     } else {
       asm volatile("" ::: "memory");
-      if (lane < ne) cnt[e0 + lane] = L.ecnt[wv][lane];
+      cnt_e = lane < ne ? e0 + lane : -1;
+      cnt_v = L.ecnt[wv][lane < EPW ? lane : 0];
     }
   }
+  if (cnt_e >= 0) cnt[cnt_e] = cnt_v;
   asm volatile("" ::: "memory");
   cap_flush(L.key[wv], L.idx[wv], ncap, st, list, lidx, j.list_cap, lane);
-  if constexpr (!EXACT) {
-    const double r = xadd_sum(ae, PE, pe);
-    if (r != 0.0) slow_bin(gE, r);
-    const double rn = xadd_sum(an, PN, pn);
-    if (rn != 0.0) slow_bin(gN, rn);
+  // (formed again: held across the loop they cost some twenty scalar registers.
+  // Not read again from st: its line takes every wave's list atomics, and that
+  // read made the kernel 80 us longer)
+  const XParm QN = xparm(again(PN.m), j.xh);
+  const XParm QE = xparm(again(PE.m), j.xh);
+  if constexpr (EXACT) {
+    an = xrun_sums(rn, QN);
+    ae = xrun_sums(re, QE);
+  } else {
+    const double le = xadd_sum(ae, QE, pe);
+    if (le != 0.0) slow_bin(gE, le);
+    const double ln = xadd_sum(an, QN, pn);
+    if (ln != 0.0) slow_bin(gN, ln);
   }
   long long v[7];
   long long kn[3], ke[3];
-  xints(an, PN, kn);
-  xints(ae, PE, ke);
+  xints(an, QN, kn);
+  xints(ae, QE, ke);
   v[0] = kn[0];
   v[1] = kn[1];
   v[2] = kn[2];
@@ -636,18 +715,21 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
   if (st->flags & ST_MISS) return;
   const XParm PR = xparm(st->xm_err, j.xh);
   HistBin* gR = j.histR + (size_t)comp * HBINS;
-  const u64 tk = dbits(st->tau);
+  const double tau = st->tau;
   u64 voff = 0ull;
   for (int cc = 0; cc < comp; ++cc) voff += j.st[cc].kept;
   const u64 vcap = (u64)j.ncomp * (u64)j.n_elem * (u64)n3;
   const long long E = j.n_elem, tiles = (E + EPW - 1) / EPW;
   const u64* eptr = j.elem_ptr + (size_t)comp * (E + 1);
   u64* gbm = j.bitmap + (size_t)comp * E * W;
+  typedef typename Pick<G::MF, float, double>::type vt;  // the blob's values (vbytes)
   typename G::Mats mt;
   G::init(mt, j.tab, lane);
   tab_load<G>(L.tab, j.tab, tid);
   __syncthreads();
   XAcc ar = {0.0, 0.0, 0.0};
+  const XRange RR = xrange(PR);  // FP64 path
+  XRun rr = xrun(PR);
   double pr = 0.0;  // fixed-order sum of the error terms
   bool bad = false;
   const double* ub = j.u + (size_t)comp * j.comp_stride;
@@ -655,21 +737,30 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
   const long long nw = (long long)nvb * 4;
   u64* bm = L.bm[wv];
   u32* wp = L.wp[wv];
-  // the next tile's field values are loaded while this one is processed
-  double un[NS];
+  // the next tile's field values (and Jacobians) are loaded while this one is
+  // processed
+  double un[NS], jn[G::JS];
   {
     const long long t0 = (long long)vb * 4 + wv;
-    if (t0 < tiles) G::load(ub + t0 * EPW * n3, (int)((E - t0 * EPW) < EPW ? (E - t0 * EPW) : EPW), vec, un, lane);
+    if (t0 < tiles) {
+      const int ne0 = (int)((E - t0 * EPW) < EPW ? (E - t0 * EPW) : EPW);
+      G::load(ub + t0 * EPW * n3, ne0, vec, un, lane);
+      if (j.jac) G::load_jac(j.jac + t0 * EPW, ne0, jn, lane);
+    }
   }
   for (long long t = (long long)vb * 4 + wv; t < tiles; t += nw) {
     const long long e0 = t * EPW;
     const int ne = (int)((E - e0) < EPW ? (E - e0) : EPW);
-    double u[NS], c[NS];
+    double u[NS], c[NS], jq[G::JS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) u[s] = un[s];
+#pragma unroll
+    for (int s = 0; s < G::JS; ++s) jq[s] = jn[s];
     if (t + nw < tiles) {
       const long long e1 = (t + nw) * EPW;
-      G::load(ub + e1 * n3, (int)((E - e1) < EPW ? (E - e1) : EPW), vec, un, lane);
+      const int ne1 = (int)((E - e1) < EPW ? (E - e1) : EPW);
+      G::load(ub + e1 * n3, ne1, vec, un, lane);
+      if (j.jac) G::load_jac(j.jac + e1, ne1, jn, lane);
     }
     G::forward(u, c, L.buf[wv], mt, j.tab, lane);
     // energy weights of the slots (times the element's Jacobian), with the
@@ -677,8 +768,7 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
     double wq[NS];
     if (j.jac) {
 #pragma unroll
-      for (int s = 0; s < NS; ++s)
-        wq[s] = G::valid(s, lane, ne) ? j.jac[e0 + G::elem(s, lane)] * L.tab.g3[s][lane] : 0.0;
+      for (int s = 0; s < NS; ++s) wq[s] = jq[s % G::JS] * L.tab.g3[s][lane];
     } else {
 #pragma unroll
       for (int s = 0; s < NS; ++s) wq[s] = L.tab.g3[s][lane];
@@ -688,71 +778,85 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
     for (int s = 0; s < NS; ++s) {
       const bool v = G::valid(s, lane, ne);
       const double en = v ? wq[s] * (c[s] * c[s]) : 0.0;
-      keep[s] = v && dbits(en) >= tk;
+      keep[s] = v && en >= tau;
     }
     if constexpr (G::n == 8) {
       // one element per tile and one 64-bit word per index r: the words come
       // straight from the ballots (wave-uniform, no LDS)
-      u64 B[NS], word[8];
+      u64 B[NS];
 #pragma unroll
       for (int s = 0; s < NS; ++s) B[s] = ballot(keep[s]);
+      // indices 0..3 and 4..7 apart, so that picking one by lane below is a
+      // select and not an indexed access
+      u64 wa[4], wb[4];
       if constexpr (G::MF) {
         // slot s = 4 blk + m on lane 16 g + P: index r = 4 (g & 1) + m, pencil
         // 32 blk + 16 (g >> 1) + P
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const int m = r & 3, gl = r >> 2;
-          u64 w = 0ull;
+        for (int m = 0; m < 4; ++m) {
+          wa[m] = wb[m] = 0ull;
 #pragma unroll
           for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
-            for (int hs = 0; hs < 2; ++hs)
-              w |= ((B[4 * blk + m] >> (16 * (2 * hs + gl))) & 0xFFFFull) << (32 * blk + 16 * hs);
-          word[r] = w;
+            for (int hs = 0; hs < 2; ++hs) {
+              wa[m] |= ((B[4 * blk + m] >> (32 * hs)) & 0xFFFFull) << (32 * blk + 16 * hs);
+              wb[m] |= ((B[4 * blk + m] >> (32 * hs + 16)) & 0xFFFFull) << (32 * blk + 16 * hs);
+            }
         }
       } else {
 #pragma unroll
-        for (int r = 0; r < 8; ++r) word[r] = B[r];
+        for (int m = 0; m < 4; ++m) {
+          wa[m] = B[m];
+          wb[m] = B[4 + m];
+        }
       }
-      u32 pre[8];
+      u32 pa[4], pb[4];
       u32 tot = 0u;
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        pre[r] = tot;
-        tot += (u32)__popcll(word[r]);
+      for (int m = 0; m < 4; ++m) {
+        pa[m] = tot;
+        tot += (u32)__popcll(wa[m]);
+      }
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        pb[m] = tot;
+        tot += (u32)__popcll(wb[m]);
       }
       u64 mine = 0ull;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) mine = lane == r ? word[r] : mine;
-      // bits below this lane's pencil in its words (one mask per pencil block)
-      u64 below[G::NB];
-#pragma unroll
-      for (int blk = 0; blk < G::NB; ++blk) below[blk] = (1ull << G::pencil(blk * G::SPB, lane)) - 1ull;
+      mine = writelane64<0>(wa[0], mine);
+      mine = writelane64<1>(wa[1], mine);
+      mine = writelane64<2>(wa[2], mine);
+      mine = writelane64<3>(wa[3], mine);
+      mine = writelane64<4>(wb[0], mine);
+      mine = writelane64<5>(wb[1], mine);
+      mine = writelane64<6>(wb[2], mine);
+      mine = writelane64<7>(wb[3], mine);
       if (lane < 8) gbm[e0 * 8 + lane] = mine;
       const u64 ebase = eptr[e0];
-      if ((u64)tot != eptr[e0 + 1] - ebase) bad = true;
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        if (!keep[s]) continue;
-        u64 wd;
-        u32 pr;
-        if constexpr (G::MF) {  // index r = 4 (g & 1) + (s & 3): one of two words
+      const u64 vbase = voff + ebase;
+      // offsets that disagree with the bitmap: never write past the values
+      const bool fits = vbase <= vcap && (u64)tot <= vcap - vbase;
+      if ((u64)tot != eptr[e0 + 1] - ebase || !fits) bad = true;
+      if (fits) {
+        // the element's values: a uniform base and a 32-bit rank per lane
+        vt* dst = (vt*)j.values + vbase;
+        if constexpr (G::MF) {
+          // index r = 4 (g & 1) + (s & 3): one of two words; block 0 holds
+          // the pencils of a word's low half, block 1 those of its high half
           const bool up = (lane >> 4) & 1;
-          wd = up ? word[4 + (s & 3)] : word[s & 3];
-          pr = up ? pre[4 + (s & 3)] : pre[s & 3];
+          const u32 below = (1u << (16 * (lane >> 5) + (lane & 15))) - 1u;
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+            const u64 wd = up ? wb[m] : wa[m];
+            const u32 lo = (u32)wd, hi = (u32)(wd >> 32), pr = up ? pb[m] : pa[m];
+            if (keep[m]) dst[pr + (u32)__popc(lo & below)] = (vt)c[m];
+            if (keep[4 + m]) dst[pr + (u32)__popc(lo) + (u32)__popc(hi & below)] = (vt)c[4 + m];
+          }
         } else {
-          wd = word[s];
-          pr = pre[s];
+#pragma unroll
+          for (int s = 0; s < NS; ++s)
+            if (keep[s]) dst[(s < 4 ? pa[s & 3] : pb[s & 3]) + lane_rank(B[s])] = (vt)c[s];
         }
-        const u64 pos = voff + ebase + pr + (u64)__popcll(wd & below[s / G::SPB]);
-        if (pos >= vcap) {  // offsets disagree with the bitmap: never write past the values
-          bad = true;
-          continue;
-        }
-        if (j.vbytes == 8)
-          ((double*)j.values)[pos] = c[s];
-        else
-          ((float*)j.values)[pos] = (float)c[s];
       }
     } else {
       if (lane < EPW * W) bm[lane] = 0ull;
@@ -800,34 +904,48 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
     // quadrature weights of the slots, the same way
     if (j.jac) {
 #pragma unroll
-      for (int s = 0; s < NS; ++s)
-        wq[s] = G::valid(s, lane, ne) ? j.jac[e0 + G::elem(s, lane)] * L.tab.w3[s][lane] : 0.0;
+      for (int s = 0; s < NS; ++s) wq[s] = jq[s % G::JS] * L.tab.w3[s][lane];
     } else {
 #pragma unroll
       for (int s = 0; s < NS; ++s) wq[s] = L.tab.w3[s][lane];
     }
+    bool odd = false;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
+      const bool v = G::valid(s, lane, ne);
       const double d = u[s] - ut[s];
-      const double x = G::valid(s, lane, ne) ? wq[s] * (d * d) : 0.0;
+      const double x = v ? wq[s] * (d * d) : 0.0;
       if constexpr (EXACT) {
-        const double r = xadd_r(ar, PR, x);
-        if (r != 0.0) slow_bin(gR, r);
+        odd = (xrun_left(rr, RR, x) && v) || odd;
         __builtin_amdgcn_sched_barrier(0);
       } else {
         pr += x;
+      }
+    }
+    if constexpr (EXACT) pin(rr);
+    if constexpr (EXACT) {
+      if (ballot(odd)) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const double d = u[s] - ut[s];
+          const double x = G::valid(s, lane, ne) ? wq[s] * (d * d) : 0.0;
+          if (!xin(RR, x)) slow_bin(gR, x);
+        }
       }
     }
   }
   if (ballot(bad)) {
     if (lane == 0) atomicOr(&st->flags, ST_LIST);
   }
-  if constexpr (!EXACT) {
-    const double r = xadd_sum(ar, PR, pr);
+  const XParm QR = xparm(again(PR.m), j.xh);
+  if constexpr (EXACT) {
+    ar = xrun_sums(rr, QR);
+  } else {
+    const double r = xadd_sum(ar, QR, pr);
     if (r != 0.0) slow_bin(gR, r);
   }
   long long v[3];
-  xints(ar, PR, v);
+  xints(ar, QR, v);
   block_sum_i64<3>(v, L.red, tid);
   if (tid < 3) j.slotsB[((size_t)comp * j.gB + vb) * 4 + tid] = L.red[0][tid];
   if (!tail || !last_block(j.done + D_PASSB * 8 + comp, &L.last, nvb)) return;
