@@ -16,12 +16,12 @@
 // the rare terms far below 2^m go through 32-bit digits in LDS;
 // the result is rounded once.  The workgroup adds every element's exact norm
 // and dropped energy into per-component digit totals, and the finishing
-// kernel rounds the component totals.  Compaction, the inverse and the exact
-// error check are pass 3 of the general pipeline, reading the per-element
-// thresholds.
+// kernel rounds the component totals.  The kept counts are known per element
+// by then, so orders 1..7 go on with the offset scan and pass B of the
+// streaming path on the per-element thresholds; higher orders with pass 3 of
+// the general pipeline.
 #include "isr.h"
-#include "isr_common.cuh"
-#include "isr_xsum.cuh"
+#include "isr_engine.cuh"
 
 namespace isr {
 
@@ -98,8 +98,6 @@ DEV void tot_add(u64* T, u64 w) {
   atomicAdd((unsigned long long*)&T[2 * l + 1], (unsigned long long)(w >> 32));
 }
 
-DEV u64 wmax64(u64 v);
-
 // X-unit wave big integer of the exact sum of the terms x[k] with take[k]
 // (finite, >= 0) over the wave's lanes.
 template <int CNT>
@@ -110,7 +108,7 @@ DEV u64 exact_words(const double (&x)[CNT], const bool (&take)[CNT], u64* D) {
     const u64 b = take[k] ? dbits(x[k]) : 0ull;
     mk = b > mk ? b : mk;
   }
-  mk = wmax64(mk);
+  mk = wave_max_dpp(mk);
   if (mk == 0ull) return 0ull;
   // every term is below 2^m (exponent of the largest term plus one)
   int m = (int)(mk >> 52) - 1022;
@@ -131,9 +129,8 @@ DEV u64 exact_words(const double (&x)[CNT], const bool (&take)[CNT], u64* D) {
   const int sft[3] = {107 - 2 * h, 53 - h, 0};
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    __int128 t = (__int128)K[i];
-    for (int mm = 32; mm > 0; mm >>= 1) t += shfl_xor128(t, mm);
-    i192_add_shl(z, t, sft[i]);
+    // (a lane's sum is below 2^53 in magnitude, the wave's below 2^59)
+    i192_add_shl(z, (__int128)(long long)wave_sum_dpp((u64)K[i]), sft[i]);
   }
   // z counts units u3 = 2^(m + 3h - 159), i.e. X units shifted by sh (>= 61)
   const int sh = m + 3 * h - 159 + 1075;
@@ -151,27 +148,6 @@ DEV u64 exact_words(const double (&x)[CNT], const bool (&take)[CNT], u64* D) {
   return w;
 }
 
-DEV double wsum(double v) {
-  for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
-  return v;
-}
-
-DEV u64 wmin64(u64 v) {
-  for (int m = 32; m > 0; m >>= 1) {
-    const u64 o = shfl_xor64(v, m);
-    v = o < v ? o : v;
-  }
-  return v;
-}
-
-DEV u64 wmax64(u64 v) {
-  for (int m = 32; m > 0; m >>= 1) {
-    const u64 o = shfl_xor64(v, m);
-    v = o > v ? o : v;
-  }
-  return v;
-}
-
 // RN(exact sum of the energies whose key is below K) <= B, the same answer
 // in every lane.  Padding slots carry key ~0 and never count.  The FP64 sum
 // of C non-negative terms, in any order, is within (C - 1) 2^-53 of the
@@ -187,7 +163,7 @@ DEV bool ec_feasible(const double (&x)[CNT], const u64 (&key)[CNT], u64 K, doubl
     s = s + (in ? x[k] : 0.0);
     c += __popcll(ballot(in));
   }
-  const double S = wsum(s);
+  const double S = wave_sum_dpp(s);
   const double C = (double)c;
   const double bound = ((2.0 * C) * 0x1p-53) * S;
   if (S + bound <= B) return true;
@@ -205,9 +181,17 @@ struct ElemScale {
 };
 
 template <int N>
+struct ElemXform {};  // transform buffers, one a wavefront
+template <>
+struct ElemXform<7> {
+  double buf[EC_WAVES][Eng<7, P_FP64>::LDSW];
+};
+
+template <int N>
 __global__ __launch_bounds__(256) void k_elemsel(Job j, const double* coef, double* tau_out, u64* G, ElemScale sc) {
   constexpr int n = N + 1, n3 = n * n * n, CNT = (n3 + 63) / 64;
   __shared__ ElemLds L;
+  __shared__ ElemXform<N> X;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   for (int i = tid; i < ISR_MAX_COMP * 2 * GD; i += 256) (&L.tot[0][0][0])[i] = 0ull;
   if (tid < ISR_MAX_COMP) L.kept[tid] = 0ull;
@@ -219,25 +203,42 @@ __global__ __launch_bounds__(256) void k_elemsel(Job j, const double* coef, doub
     const int comp = (int)(p / E);
     const long long e = p - (long long)comp * E;
     const double* ue = j.u + (size_t)comp * j.comp_stride + (size_t)e * n3;
-    const double* ce = coef + (size_t)p * n3;
     double t[CNT], x[CNT];
     u64 key[CNT];
     bool badu = false, bad = false;
+    // norm term of field value f and energy of coefficient f (any lane and
+    // slot each: both sums are exact), slot k of this lane holding dense
+    // position 64 k + lane of the coefficients
+    auto take = [&](int k, double uv, int fu, double cv, int fc) {
+      t[k] = jw1(j.jac, e, j.tab.w3[fu]) * (uv * uv);
+      x[k] = jw1(j.jac, e, j.tab.g3[fc]) * (cv * cv);
+      key[k] = dbits(x[k]);
+      badu = badu || !__builtin_isfinite(uv);
+      bad = bad || !(t[k] >= 0.0 && t[k] <= 0x1.fffffffffffffp+1023) ||
+            !(x[k] >= 0.0 && x[k] <= 0x1.fffffffffffffp+1023);
+    };
+    if constexpr (n == 8) {
+      // the wave-tile engine's transform on the spot (its coefficient slots
+      // are the dense positions): no coefficient array, no kernel before this
+      typedef Eng<N, P_FP64> G;
+      static_assert(G::EPW == 1 && G::NS == CNT, "one element, eight slots");
+      double u[CNT], c[CNT];
+      G::load(ue, 1, (((uintptr_t)ue) & 15) == 0, u, lane);
+      G::forward(u, c, X.buf[wv], typename G::Mats(), j.tab, lane);
 #pragma unroll
-    for (int k = 0; k < CNT; ++k) {
-      const int f = lane + 64 * k;
-      if (f < n3) {
-        const double uv = ue[f], cv = ce[f];
-        t[k] = jw1(j.jac, e, j.tab.w3[f]) * (uv * uv);
-        x[k] = jw1(j.jac, e, j.tab.g3[f]) * (cv * cv);
-        key[k] = dbits(x[k]);
-        badu = badu || !__builtin_isfinite(uv);
-        bad = bad || !(t[k] >= 0.0 && t[k] <= 0x1.fffffffffffffp+1023) ||
-              !(x[k] >= 0.0 && x[k] <= 0x1.fffffffffffffp+1023);
-      } else {
-        t[k] = 0.0;
-        x[k] = 0.0;
-        key[k] = ~0ull;
+      for (int k = 0; k < CNT; ++k) take(k, u[k], G::w3i(k, lane), c[k], G::g3i(k, lane));
+    } else {
+      const double* ce = coef + (size_t)p * n3;
+#pragma unroll
+      for (int k = 0; k < CNT; ++k) {
+        const int f = lane + 64 * k;
+        if (f < n3) {
+          take(k, ue[f], f, ce[f], f);
+        } else {
+          t[k] = 0.0;
+          x[k] = 0.0;
+          key[k] = ~0ull;
+        }
       }
     }
     const u64 ub = ballot(badu), xb = ballot(bad);
@@ -245,6 +246,7 @@ __global__ __launch_bounds__(256) void k_elemsel(Job j, const double* coef, doub
       if (lane == 0) {
         atomicOr(&j.st[comp].flags, ub ? (int)ST_NONFINITE : (int)ST_OVERFLOW);
         tau_out[p] = __builtin_inf();
+        j.cnt[p] = 0u;
       }
       continue;
     }
@@ -270,7 +272,7 @@ __global__ __launch_bounds__(256) void k_elemsel(Job j, const double* coef, doub
           mx = key[k] > mx ? key[k] : mx;
         }
       }
-      u64 lo = wmin64(mn), hi = wmax64(mx) + 1ull;  // S(lo) = 0 <= B; S(hi) = the total > B
+      u64 lo = ~wave_max_dpp(~mn), hi = wave_max_dpp(mx) + 1ull;  // S(lo) = 0 <= B; S(hi) = the total > B
       while (hi - lo > 1ull) {
         // no energy strictly between lo and hi: then S(hi) = S(lo) plus the
         // energies at key lo, and S(lo) <= B < S(hi) makes lo an energy's key
@@ -297,10 +299,11 @@ __global__ __launch_bounds__(256) void k_elemsel(Job j, const double* coef, doub
     }
     w = exact_words<CNT>(x, drop, D);
     tot_add(L.tot[comp][1], w);
-    kc = wave_sum64(kc);
+    kc = wave_sum_dpp(kc);
     if (lane == 0) {
       atomicAdd((unsigned long long*)&L.kept[comp], (unsigned long long)kc);
       tau_out[p] = __longlong_as_double((long long)kt);
+      j.cnt[p] = (u32)kc;
     }
   }
   __syncthreads();
@@ -328,6 +331,9 @@ __global__ __launch_bounds__(64) void k_elemfin(Job j, const u64* G) {
     st->dropped = v[1];
     st->resolved = 1;
     st->bstar = -1;
+    // bound on the error terms of pass B, as for the global cut
+    int m = st->B > 0.0 ? ilogb(st->B) + 6 : (v[0] > 0.0 ? ilogb(v[0]) - 80 : XM_MIN);
+    st->xm_err = m < XM_MIN ? XM_MIN : (m > XM_MAX ? XM_MAX : m);
   }
 }
 

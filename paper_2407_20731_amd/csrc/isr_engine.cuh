@@ -715,7 +715,10 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
   if (st->flags & ST_MISS) return;
   const XParm PR = xparm(st->xm_err, j.xh);
   HistBin* gR = j.histR + (size_t)comp * HBINS;
-  const double tau = st->tau;
+  // the threshold: the component's, or (per-element cut, FP64 path) the
+  // element's, loaded with the tile
+  double tau = st->tau, tn = tau;
+  const double* te = EXACT && j.tau_elem ? j.tau_elem + (size_t)comp * j.n_elem : nullptr;
   u64 voff = 0ull;
   for (int cc = 0; cc < comp; ++cc) voff += j.st[cc].kept;
   const u64 vcap = (u64)j.ncomp * (u64)j.n_elem * (u64)n3;
@@ -746,6 +749,7 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
       const int ne0 = (int)((E - t0 * EPW) < EPW ? (E - t0 * EPW) : EPW);
       G::load(ub + t0 * EPW * n3, ne0, vec, un, lane);
       if (j.jac) G::load_jac(j.jac + t0 * EPW, ne0, jn, lane);
+      if (te && G::valid(0, lane, ne0)) tn = te[t0 * EPW + G::elem(0, lane)];
     }
   }
   for (long long t = (long long)vb * 4 + wv; t < tiles; t += nw) {
@@ -756,11 +760,13 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
     for (int s = 0; s < NS; ++s) u[s] = un[s];
 #pragma unroll
     for (int s = 0; s < G::JS; ++s) jq[s] = jn[s];
+    tau = tn;
     if (t + nw < tiles) {
       const long long e1 = (t + nw) * EPW;
       const int ne1 = (int)((E - e1) < EPW ? (E - e1) : EPW);
       G::load(ub + e1 * n3, ne1, vec, un, lane);
       if (j.jac) G::load_jac(j.jac + e1, ne1, jn, lane);
+      if (te && G::valid(0, lane, ne1)) tn = te[e1 + G::elem(0, lane)];
     }
     G::forward(u, c, L.buf[wv], mt, j.tab, lane);
     // energy weights of the slots (times the element's Jacobian), with the

@@ -197,9 +197,10 @@ hipError_t launch_state_out(const CompState* src, CompState* host_dst, int ncomp
 // component, into err2_out[ncomp] (device)
 hipError_t launch_err_total(const Job& j, double* err2_out, hipStream_t s);
 // per-element cut (isr_elemcut.hip): every element's threshold into
-// tau[ncomp][n_elem] from the FP64 coefficients coef (isr_forward's layout),
-// at budgets ((tol*tol)*U2_e)*scale[comp]; the component totals (U2, the
-// dropped energy) and kept counts into j.st.  G: zeroed digit totals of
+// tau[ncomp][n_elem] and its kept count into j.cnt, from the FP64 coefficients
+// coef (isr_forward's layout; not read at N = 7, where the kernel transforms
+// the element itself), at budgets ((tol*tol)*U2_e)*scale[comp]; the component
+// totals (U2, the dropped energy) and kept counts into j.st.  G: zeroed digit totals of
 // elemcut_digit_bytes(ncomp) bytes; j.st[*].kept and flags start at 0.
 hipError_t launch_elemcut(const Job& j, const double* coef, double* tau, u64* G, const double* scale, int grid,
                           hipStream_t s);
@@ -291,6 +292,8 @@ hipError_t launch_decomp_dense_fp32(const Job& j, int gx, int cus, hipStream_t s
 hipError_t launch_decomp_dense_bf16(const Job& j, int gx, int cus, hipStream_t s, void* out, int out_fp64);
 hipError_t launch_gather(const Job& j, int grid_x, hipStream_t s);
 hipError_t launch_count(const Job& j, int grid_x, hipStream_t s);
+// element offsets from the per-element counts j.cnt (the last step of launch_count)
+hipError_t launch_scan(const Job& j, hipStream_t s);
 constexpr int SCAN_CHUNK = 1024;  // elements per chunk of the element-offset scan
 inline int scan_grid_elems(long long n_elem) {  // its workgroups per component
   const long long nch = (n_elem + SCAN_CHUNK - 1) / SCAN_CHUNK;

@@ -1970,12 +1970,18 @@ int run_compress_elemcut(isr_ctx* c, const isr_field* f, isr_blob** out, isr_sta
   b->dev = c->arena->alloc(b->dev_bytes, true);
   const long long tiles = tiles_per_comp(f->order, E);
   auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
-  const size_t o_coef = 0, o_tau = al(o_coef + (size_t)nc * E * n3 * 8), o_st = al(o_tau + (size_t)nc * E * 8);
+  const size_t o_coef = 0, o_tau = al(o_coef + (f->order == 7 ? 0 : (size_t)nc * E * n3 * 8)), o_st = al(o_tau + (size_t)nc * E * 8);
   const size_t o_zero = al(o_st + (size_t)nc * sizeof(CompState));  // digits, error bins, look-back, ticket
   const size_t o_hist = al(o_zero + elemcut_digit_bytes(nc));
   const size_t o_lb = al(o_hist + (size_t)nc * HBINS * sizeof(HistBin));
   const size_t o_tk = al(o_lb + (size_t)nc * tiles * 8);
-  const size_t scr_bytes = o_tk + 256;
+  const size_t zero_end = o_tk + 256;
+  // kept counts, their scan and the error sums of pass B (orders of the
+  // streaming path)
+  const bool fast = fast_order(f->order, ISR_PREC_FP64);
+  const size_t o_cnt = al(zero_end), o_chunk = al(o_cnt + (size_t)nc * E * 4);
+  const size_t o_slots = al(o_chunk + (size_t)nc * ((E + SCAN_CHUNK - 1) / SCAN_CHUNK) * 8);
+  const size_t scr_bytes = o_slots + (size_t)nc * FAST_GMAX * 4 * 8;
   char* scr = b->dev ? (char*)c->arena->alloc(scr_bytes) : nullptr;
   if (!b->dev || !scr) {
     if (b->dev) c->arena->free(b->dev);
@@ -2010,9 +2016,15 @@ int run_compress_elemcut(isr_ctx* c, const isr_field* f, isr_blob** out, isr_sta
   j.values = b->values();
   j.voff = b->voff();
   j.tau_elem = (const double*)(scr + o_tau);
+  j.cnt = (u32*)(scr + o_cnt);
+  j.chunk = (u64*)(scr + o_chunk);
+  j.nchunk = (E + SCAN_CHUNK - 1) / SCAN_CHUNK;
+  j.slotsB = (long long*)(scr + o_slots);
+  if (fast) fast_setup(c, j, plan_sizes(f, 0));  // pass B's grid and headroom
   double* coef = (double*)(scr + o_coef);
   const int gfwd = (int)std::min<long long>(tiles * nc, (long long)c->num_cu * 8);
-  if (launch_pass(K_FORWARD, ISR_PREC_FP64, j, gfwd, s, coef) != hipSuccess)
+  // (at N = 7 the selection transforms the elements itself)
+  if (f->order != 7 && launch_pass(K_FORWARD, ISR_PREC_FP64, j, gfwd, s, coef) != hipSuccess)
     return give_up(fail(ISR_EDEVICE, "forward transform failed: %s", hipGetErrorString(hipGetLastError())));
   const int gsel = (int)std::max<long long>(1, std::min<long long>((E * nc + 3) / 4, (long long)c->num_cu * 8));
   const int g3 = (int)std::min<long long>(tiles * nc, (long long)c->num_cu * resident_blocks(K_PASS3, ISR_PREC_FP64, f->order));
@@ -2028,9 +2040,11 @@ int run_compress_elemcut(isr_ctx* c, const isr_field* f, isr_blob** out, isr_sta
       hs[k].bstar = -1;
     }
     if (hipMemcpyAsync(j.st, hs, nc * sizeof(CompState), hipMemcpyHostToDevice, s) != hipSuccess ||
-        launch_zero(scr + o_zero, o_tk + 256 - o_zero, s) != hipSuccess ||
+        launch_zero(scr + o_zero, zero_end - o_zero, s) != hipSuccess ||
         launch_elemcut(j, coef, (double*)(scr + o_tau), (u64*)(scr + o_zero), scale, gsel, s) != hipSuccess ||
-        launch_pass(K_PASS3, ISR_PREC_FP64, j, g3, s) != hipSuccess || launch_finalize(j, s) != hipSuccess ||
+        (fast ? launch_scan(j, s) != hipSuccess || launch_fast(F_PASSB, ISR_PREC_FP64, j, j.gB, s) != hipSuccess ||
+                    launch_fast_tail(F_PASSB, j, s) != hipSuccess
+              : launch_pass(K_PASS3, ISR_PREC_FP64, j, g3, s) != hipSuccess || launch_finalize(j, s) != hipSuccess) ||
         hipMemcpyAsync(hs, j.st, nc * sizeof(CompState), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
       return give_up(fail(ISR_EDEVICE, "per-element cut failed: %s", hipGetErrorString(hipGetLastError())));

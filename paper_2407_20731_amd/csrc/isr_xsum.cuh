@@ -219,6 +219,38 @@ DEV void emit_total(HistBin* g, const __int128 (&K)[3], int m, int h, int btop) 
   add_piece(g, btop, hi128);
 }
 
+// Wave sums over data-parallel lane moves (six steps of a few cycles each;
+// the LDS permutes of a shuffle wait some hundred cycles a step), the same
+// value in every lane.  Row shifts sum the rows of 16 into their last lanes,
+// the row broadcasts carry those on to lane 63.
+template <int CTRL, int ROWS>
+DEV u64 dpp64(u64 v) {
+  const u32 lo = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)v, CTRL, ROWS, 0xf, false);
+  const u32 hi = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)(v >> 32), CTRL, ROWS, 0xf, false);
+  return ((u64)hi << 32) | lo;
+}
+template <class OP>
+DEV u64 wave_reduce_dpp(u64 v, OP op) {  // op(x, 0) == x
+  v = op(v, dpp64<0x111, 0xf>(v));  // row_shr 1, 2, 4, 8
+  v = op(v, dpp64<0x112, 0xf>(v));
+  v = op(v, dpp64<0x114, 0xf>(v));
+  v = op(v, dpp64<0x118, 0xf>(v));
+  v = op(v, dpp64<0x142, 0xa>(v));  // row_bcast 15 into rows 1 and 3
+  v = op(v, dpp64<0x143, 0xc>(v));  // row_bcast 31 into rows 2 and 3
+  return bcast64(v, 63);
+}
+DEV double wave_sum_dpp(double v) {
+  return __longlong_as_double((long long)wave_reduce_dpp(dbits(v), [](u64 a, u64 b) {
+    return dbits(__longlong_as_double((long long)a) + __longlong_as_double((long long)b));
+  }));
+}
+DEV u64 wave_sum_dpp(u64 v) {
+  return wave_reduce_dpp(v, [](u64 a, u64 b) { return a + b; });
+}
+DEV u64 wave_max_dpp(u64 v) {
+  return wave_reduce_dpp(v, [](u64 a, u64 b) { return a > b ? a : b; });
+}
+
 DEV long long wave_sum_i64(long long v) { return (long long)wave_sum64((u64)v); }
 
 DEV double wave_sum_f64(double v) {
