@@ -4,10 +4,14 @@
 // threshold rule applied inside one element).  FP64 path.
 //
 // One wavefront per element.  Its norm terms and energies are formed from
-// the field and the FP64 coefficients (isr_forward's), and the element's
-// threshold is found by a binary search over the bit patterns of the
-// energies (monotone for non-negative doubles), which stops once no energy
-// lies strictly inside the interval.  Each probe decides RN(exact sum of
+// the field and the FP64 coefficients, and the element's threshold is found by
+// a binary search over the energies' keys (their bit patterns, monotone for
+// non-negative doubles), between bounds that need no sum: energies of at most
+// the budget over twice their number all fit, one above the budget never does.
+// It stops once no energy lies strictly inside the interval.  Bound by VALU
+// issue: at N = 7 a probe costs ~190 instructions of a wavefront, the exact
+// sums and the transform ~1500 (8,192 elements, 3 components: 362 -> 136 us).
+// Each probe decides RN(exact sum of
 // energies below the key) <= B_e: an FP64 wave sum with a rigorous error
 // bound settles almost every probe, and the rest are summed exactly.  Exact
 // sums: every lane splits its terms by error-free extraction against 2^m >=
@@ -264,30 +268,51 @@ __global__ __launch_bounds__(256) void k_elemsel(Job j, const double* coef, doub
     if (ec_feasible<CNT>(x, key, INF_KEY, B, succB, D)) {
       kt = INF_KEY;  // everything fits the budget: +inf, nothing kept
     } else {
-      u64 mn = ~0ull, mx = 0ull;
+      // Largest key <= `most` and smallest key >= `least` over the wave (0 /
+      // ~0 when there is none; padding slots, key ~0, never count as one).
+      auto last_upto = [&](u64 most) {
+        u64 m = 0ull;
 #pragma unroll
-      for (int k = 0; k < CNT; ++k) {
-        if (lane + 64 * k < n3) {
-          mn = key[k] < mn ? key[k] : mn;
-          mx = key[k] > mx ? key[k] : mx;
+        for (int k = 0; k < CNT; ++k) m = key[k] <= most && key[k] > m ? key[k] : m;
+        return wave_max_dpp(m);
+      };
+      auto first_from = [&](u64 least) {
+        u64 m = ~0ull;
+#pragma unroll
+        for (int k = 0; k < CNT; ++k) m = key[k] >= least && key[k] < m ? key[k] : m;
+        return ~wave_max_dpp(~m);
+      };
+      // S(lo) <= B < S(hi) from the start: energies of at most B over twice
+      // their number all fit, and one above B never does
+      constexpr double SHARE = CNT <= 1 ? 0x1p-7 : CNT <= 2 ? 0x1p-8 : CNT <= 4 ? 0x1p-9 : CNT <= 8 ? 0x1p-10
+                               : CNT <= 16 ? 0x1p-11 : CNT <= 32 ? 0x1p-12 : 0x1p-13;
+      static_assert(CNT <= 64, "energies of an element");
+      const u64 small = last_upto(dbits(B * SHARE));
+      u64 lo = small ? small : first_from(0ull);
+      const u64 over = first_from(dbits(B) + 1ull);
+      u64 hi = (over != ~0ull ? over : last_upto(INF_KEY)) + 1ull;
+      // bisection over the keys themselves: the probe is the first key from
+      // the middle on (log2 of the energies inside, some seven probes; over
+      // the bits alone the last key is only met after about fifty)
+      // (lo < mid <= hi, and mid == hi only when nothing fits between: every
+      // step raises lo, lowers hi or ends)
+      for (;;) {
+        const u64 mid = lo + 1ull + ((hi - lo - 1ull) >> 1);
+        const u64 up = first_from(mid);
+        if (up < hi) {
+          if (ec_feasible<CNT>(x, key, up, B, succB, D))
+            lo = up;
+          else
+            hi = mid;  // (no key in [mid, up))
+        } else {
+          // nothing from the middle on: down to the last key below it (lo is
+          // one: done)
+          const u64 dn = last_upto(mid - 1ull);
+          if (dn <= lo) break;
+          hi = dn + 1ull;
         }
       }
-      u64 lo = ~wave_max_dpp(~mn), hi = wave_max_dpp(mx) + 1ull;  // S(lo) = 0 <= B; S(hi) = the total > B
-      while (hi - lo > 1ull) {
-        // no energy strictly between lo and hi: then S(hi) = S(lo) plus the
-        // energies at key lo, and S(lo) <= B < S(hi) makes lo an energy's key
-        // (the answer); bisection stops here long before the keys run out
-        bool inside = false;
-#pragma unroll
-        for (int k = 0; k < CNT; ++k) inside = inside || (key[k] > lo && key[k] < hi);
-        if (!ballot(inside)) break;
-        const u64 mid = lo + ((hi - lo) >> 1);
-        if (ec_feasible<CNT>(x, key, mid, B, succB, D))
-          lo = mid;
-        else
-          hi = mid;
-      }
-      kt = lo;  // S(lo) <= B < S(lo + 1): lo is the key of an energy
+      kt = lo;  // no energy strictly inside, S(lo) <= B < S(hi): lo is an energy's key
     }
     // dropped energy, exactly, and the kept count
     bool drop[CNT];
