@@ -983,10 +983,88 @@ __global__ __launch_bounds__(256, ISR_FAST_MINB) void k_passB(Job j) {
 // FP64 358 -> 156 us (5.2 TB/s written), BF16 to FP32 305 -> 85 us (4.7 TB/s).
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
+// Calls fn(slot, place, index) for every kept coefficient of this lane's slots
+// (place: among the blob's values; index: flat index in its element), and sets
+// the other slots to zero: cm[s] = kept ? fn(...) : 0.  wcur: the tile's bitmap
+// words, one a lane; base: the place of its first kept value.
+template <int N, int PREC, int NS, class FN>
+DEV void kept_slots(double (&cm)[NS], u64 wcur, u64 base, int ne, u64* bm, u32* wp, int lane, FN fn) {
+  typedef Eng<N, PREC> G;
+  static_assert(NS == G::NS, "a tile's slots");
+  constexpr int n = G::n, n2 = G::n2, W = G::W;
+  if constexpr (n == 8) {
+    // one element, one word per index r: uniform words and prefixes
+    // (indices 0..3 and 4..7 apart, so that picking one by lane is a select
+    // and not an indexed access)
+    u64 wa[4], wb[4];
+    u32 pa[4], pb[4], tot = 0u;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      wa[r] = bcast64(wcur, r);
+      pa[r] = tot;
+      tot += (u32)__popcll(wa[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      wb[r] = bcast64(wcur, 4 + r);
+      pb[r] = tot;
+      tot += (u32)__popcll(wb[r]);
+    }
+    if constexpr (G::MF) {
+      // slot s = 4 blk + m: index r = 4 gl + m, pencil 32 blk + p32
+      const bool up = (lane >> 4) & 1;
+      const int p32 = 16 * (lane >> 5) + (lane & 15);
+      const u32 bit = 1u << p32, below = bit - 1u;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const u64 wd = up ? wb[m] : wa[m];
+        const u32 lo = (u32)wd, hi = (u32)(wd >> 32), pr = up ? pb[m] : pa[m];
+        const int f = (4 * (int)up + m) * 64 + p32;
+        cm[m] = (lo & bit) ? fn(m, base + (pr + (u32)__popc(lo & below)), f) : 0.0;
+        cm[4 + m] =
+            (hi & bit) ? fn(4 + m, base + (pr + (u32)__popc(lo) + (u32)__popc(hi & below)), f + 32) : 0.0;
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const u64 wd = r < 4 ? wa[r & 3] : wb[r & 3];
+        const u32 pr = r < 4 ? pa[r & 3] : pb[r & 3];
+        cm[r] = lane_bit(wd) ? fn(r, base + (pr + lane_rank(wd)), r * 64 + lane) : 0.0;
+      }
+    }
+  } else {
+    // the tile's kept values follow each other in the blob: ranks run over
+    // all of its words
+    const u32 pc = (u32)__popcll(wcur);
+    u32 incl = pc;
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) {
+      const u32 o = (u32)__shfl_up((int)incl, d);
+      incl += lane >= d ? o : 0u;
+    }
+    if (lane < 16) {
+      bm[lane] = wcur;
+      wp[lane] = incl - pc;
+    }
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      cm[s] = 0.0;
+      if (!G::valid(s, lane, ne)) continue;
+      const int PI = G::pencil(s, lane), ax = G::axis(s, lane);
+      const int f = ax * n2 + PI % n2, wi = (PI / n2) * W + (f >> 6);
+      const u64 wd = bm[wi];
+      if ((wd >> (f & 63)) & 1ull)
+        cm[s] = fn(s, base + (wp[wi] + (u32)__popcll(wd & ((1ull << (f & 63)) - 1ull))), f);
+    }
+    asm volatile("" ::: "memory");
+  }
+}
+
 template <int N, int PREC, bool OUT64>
 __global__ __launch_bounds__(256, 4) void k_decompW(Job j, void* out) {
   typedef Eng<N, PREC> G;
-  constexpr int n = G::n, n2 = G::n2, n3 = G::n3, NS = G::NS, EPW = G::EPW, W = G::W;
+  constexpr int n = G::n, n3 = G::n3, NS = G::NS, EPW = G::EPW, W = G::W;
   static_assert(EPW * W <= 16, "tile bitmap fits the LDS slot");
   typedef typename Pick<OUT64, double, float>::type ot;
   __shared__ typename G::wt lbuf[4][G::LDSW];
@@ -1003,13 +1081,6 @@ __global__ __launch_bounds__(256, 4) void k_decompW(Job j, void* out) {
   const u64 voff = j.voff[comp];
   const double qs = !G::MF && j.qstep ? j.qstep[comp] : 0.0;
   ot* ocomp = (ot*)out + (size_t)comp * E * n3;
-  // one kept value (pos: its place among the blob's values; f: its index)
-  auto value = [&](u64 pos, int f) -> double {
-    if constexpr (G::MF) return (double)((const float*)j.values)[pos];
-    if (j.vbytes == 8) return ((const double*)j.values)[pos];
-    // quantisation codes: the value is (code * step) / sqrt(g3)
-    return ((double)((const float*)j.values)[pos] * qs) / __builtin_sqrt(j.tab.g3[f]);
-  };
   long long t = (long long)blockIdx.x * 4 + wv;
   if (t >= tiles) return;
   u64 wnext = 0ull, bnext = 0ull;
@@ -1026,73 +1097,12 @@ __global__ __launch_bounds__(256, 4) void k_decompW(Job j, void* out) {
     const u64 wcur = wnext, base = voff + bnext;
     if (t + nw < tiles) fetch(t + nw);
     double cm[NS], ut[NS];
-    if constexpr (n == 8) {
-      // one element, one word per index r: uniform words and prefixes
-      // (indices 0..3 and 4..7 apart, so that picking one by lane is a select
-      // and not an indexed access)
-      u64 wa[4], wb[4];
-      u32 pa[4], pb[4], tot = 0u;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        wa[r] = bcast64(wcur, r);
-        pa[r] = tot;
-        tot += (u32)__popcll(wa[r]);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        wb[r] = bcast64(wcur, 4 + r);
-        pb[r] = tot;
-        tot += (u32)__popcll(wb[r]);
-      }
-      if constexpr (G::MF) {
-        // slot s = 4 blk + m: index r = 4 gl + m, pencil 32 blk + p32
-        const bool up = (lane >> 4) & 1;
-        const int p32 = 16 * (lane >> 5) + (lane & 15);
-        const u32 bit = 1u << p32, below = bit - 1u;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          const u64 wd = up ? wb[m] : wa[m];
-          const u32 lo = (u32)wd, hi = (u32)(wd >> 32), pr = up ? pb[m] : pa[m];
-          cm[m] = (lo & bit) ? value(base + (pr + (u32)__popc(lo & below)), 0) : 0.0;
-          cm[4 + m] = (hi & bit) ? value(base + (pr + (u32)__popc(lo) + (u32)__popc(hi & below)), 0) : 0.0;
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const u64 wd = r < 4 ? wa[r & 3] : wb[r & 3];
-          const u32 pr = r < 4 ? pa[r & 3] : pb[r & 3];
-          cm[r] = lane_bit(wd) ? value(base + (pr + lane_rank(wd)), r * 64 + lane) : 0.0;
-        }
-      }
-    } else {
-      // the tile's kept values follow each other in the blob: ranks run over
-      // all of its words
-      u64* bm = lbm[wv];
-      u32* wp = lwp[wv];
-      const u32 pc = (u32)__popcll(wcur);
-      u32 incl = pc;
-#pragma unroll
-      for (int d = 1; d < 16; d <<= 1) {
-        const u32 o = (u32)__shfl_up((int)incl, d);
-        incl += lane >= d ? o : 0u;
-      }
-      if (lane < 16) {
-        bm[lane] = wcur;
-        wp[lane] = incl - pc;
-      }
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        cm[s] = 0.0;
-        if (!G::valid(s, lane, ne)) continue;
-        const int PI = G::pencil(s, lane), ax = G::axis(s, lane);
-        const int f = ax * n2 + PI % n2, wi = (PI / n2) * W + (f >> 6);
-        const u64 wd = bm[wi];
-        if ((wd >> (f & 63)) & 1ull)
-          cm[s] = value(base + (wp[wi] + (u32)__popcll(wd & ((1ull << (f & 63)) - 1ull))), f);
-      }
-      asm volatile("" ::: "memory");
-    }
+    kept_slots<N, PREC>(cm, wcur, base, ne, lbm[wv], lwp[wv], lane, [&](int, u64 pos, int f) -> double {
+      if constexpr (G::MF) return (double)((const float*)j.values)[pos];
+      if (j.vbytes == 8) return ((const double*)j.values)[pos];
+      // quantisation codes: the value is (code * step) / sqrt(g3)
+      return ((double)((const float*)j.values)[pos] * qs) / __builtin_sqrt(j.tab.g3[f]);
+    });
     G::inverse(cm, ut, buf, mt, j.tab, lane);
     ot* o = ocomp + e0 * n3;
     if constexpr (n == 8 && G::MF && !OUT64) {
@@ -1115,6 +1125,105 @@ __global__ __launch_bounds__(256, 4) void k_decompW(Job j, void* out) {
       asm volatile("" ::: "memory");
     }
   }
+}
+
+// ---- quantised variant, orders 1..7 ------------------------------------------------
+// The codes of the kept values and the error they leave (k_quantize of
+// isr_passes.cuh, same definition), one tile per wavefront: the next tile's
+// field, words and offset in flight, the error terms into running exact sums
+// instead of LDS histogram atomics.  The per-workgroup sums go to j.slotsB;
+// j.qxm: log2 of the bound on the error terms per component.  10,007 elements,
+// N = 7, 3 components: 218 -> 83 us.
+template <int N>
+struct QuantWLds {
+  typedef Eng<N, P_FP64> G;
+  double buf[4][G::LDSW];
+  double w3[8][64], sq[8][64];  // quadrature weights of field slots, sqrt(g3) of coefficient slots
+  u64 bm[4][16];
+  u32 wp[4][16];
+  long long red[4][8];
+};
+
+template <int N>
+__global__ __launch_bounds__(256, 3) void k_quantW(Job j) {
+  typedef Eng<N, P_FP64> G;
+  constexpr int n3 = G::n3, NS = G::NS, EPW = G::EPW, W = G::W;
+  __shared__ QuantWLds<N> L;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int comp = blockIdx.y;
+  for (int k = tid; k < NS * 64; k += 256) {
+    const int s = k >> 6, l = k & 63;
+    const bool v = G::pvalid(s, l);
+    L.w3[s][l] = v ? j.tab.w3[G::w3i(s, l)] : 0.0;
+    L.sq[s][l] = v ? __builtin_sqrt(j.tab.g3[G::g3i(s, l)]) : 1.0;
+  }
+  __syncthreads();
+  const typename G::Mats mt{};
+  const long long E = j.n_elem, tiles = (E + EPW - 1) / EPW, nw = (long long)gridDim.x * 4;
+  const double* ub = j.u + (size_t)comp * j.comp_stride;
+  const bool vec = ((((uintptr_t)ub) & 15) == 0);
+  const u64* gbm = j.bitmap + (size_t)comp * E * W;
+  const u64* eptr = j.elem_ptr + (size_t)comp * (E + 1);
+  const u64 voff = j.voff[comp];
+  const double step = j.qstep[comp];
+  const XParm PR = xparm(j.qxm[comp], j.xh);
+  const XRange RR = xrange(PR);
+  XRun rr = xrun(PR);
+  HistBin* gR = j.histR + (size_t)comp * HBINS;
+  bool big = false;
+  double un[NS];
+  u64 wnext = 0ull, bnext = 0ull;
+  auto fetch = [&](long long tt) {
+    const long long e0 = tt * EPW;
+    const int ne = (int)((E - e0) < EPW ? (E - e0) : EPW);
+    G::load(ub + e0 * n3, ne, vec, un, lane);
+    wnext = lane < ne * W ? gbm[e0 * W + lane] : 0ull;
+    bnext = eptr[e0];
+  };
+  long long t = (long long)blockIdx.x * 4 + wv;
+  if (t < tiles) fetch(t);
+  for (; t < tiles; t += nw) {
+    const long long e0 = t * EPW;
+    const int ne = (int)((E - e0) < EPW ? (E - e0) : EPW);
+    const u64 wcur = wnext, base = voff + bnext;
+    double u[NS], cm[NS], ut[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) u[s] = un[s];
+    if (t + nw < tiles) fetch(t + nw);
+    kept_slots<N, P_FP64>(cm, wcur, base, ne, L.bm[wv], L.wp[wv], lane, [&](int s, u64 pos, int) -> double {
+      const double c = ((const double*)j.values)[pos];
+      const double sq = L.sq[s][lane];
+      const double q = __builtin_rint((c * sq) / step);
+      if (!(__builtin_fabs(q) < 16777216.0)) big = true;
+      j.qvals[pos] = (float)q;
+      return (q * step) / sq;
+    });
+    G::inverse(cm, ut, L.buf[wv], mt, j.tab, lane);
+    bool odd = false;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const bool v = G::valid(s, lane, ne);
+      const double d = u[s] - ut[s];
+      const double x = v ? L.w3[s][lane] * (d * d) : 0.0;
+      odd = (xrun_left(rr, RR, x) && v) || odd;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    pin(rr);
+    if (ballot(odd)) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const double d = u[s] - ut[s];
+        const double x = G::valid(s, lane, ne) ? L.w3[s][lane] * (d * d) : 0.0;
+        if (!xin(RR, x)) slow_bin(gR, x);
+      }
+    }
+  }
+  if (big) atomicOr(&j.ticket[1], 1u);
+  const XParm QR = xparm(again(PR.m), j.xh);
+  long long v[3];
+  xints(xrun_sums(rr, QR), QR, v);
+  block_sum_i64<3>(v, L.red, tid);
+  if (tid < 3) j.slotsB[((size_t)comp * j.gB + blockIdx.x) * 4 + tid] = L.red[0][tid];
 }
 
 // Grid of a decompression: gx workgroups per component cover its tiles once;
@@ -1150,6 +1259,20 @@ hipError_t launch_decompW_prec(const Job& j, int gx, int cus, hipStream_t s, voi
       hipLaunchKernelGGL((k_decompW<NN, PREC, false>), decomp_grid(j, gx, nb32, cus), dim3(256), 0, s, j, out); \
     break;                                                                             \
   }
+    ISR_FAST_ORDERS(CASE)
+#undef CASE
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+inline hipError_t launch_quantW(const Job& j, hipStream_t s) {
+  switch (j.order) {
+#define CASE(NN)                                                                    \
+  case NN:                                                                          \
+    hipLaunchKernelGGL((k_quantW<NN>), dim3(j.gB, j.ncomp), dim3(256), 0, s, j);    \
+    break;
     ISR_FAST_ORDERS(CASE)
 #undef CASE
     default:

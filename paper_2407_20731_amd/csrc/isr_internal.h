@@ -138,6 +138,7 @@ struct Job {
   // codes written by the quantisation pass (FP32 integers, values' layout)
   const double* qstep;
   float* qvals;
+  int qxm[8];          // log2 of the bound on the error terms, per component (orders of the streaming path)
   // per-element cut: the threshold of every element ([ncomp][n_elem]); null
   // = the component's threshold st[comp].tau
   const double* tau_elem;
@@ -196,6 +197,11 @@ hipError_t launch_state_out(const CompState* src, CompState* host_dst, int ncomp
 // correctly rounded exact totals of the error histograms j.histR, per
 // component, into err2_out[ncomp] (device)
 hipError_t launch_err_total(const Job& j, double* err2_out, hipStream_t s);
+// quantisation pass on wave tiles (orders 1..FAST_MAX_ORDER; j.gB workgroups
+// per component) and its totals: the per-workgroup sums j.slotsB (headroom
+// j.xh, bounds j.qxm) added to j.histR first
+hipError_t launch_quant_wave(const Job& j, hipStream_t s);
+hipError_t launch_quant_total(const Job& j, double* err2_out, hipStream_t s);
 // per-element cut (isr_elemcut.hip): every element's threshold into
 // tau[ncomp][n_elem] and its kept count into j.cnt, from the FP64 coefficients
 // coef (isr_forward's layout; not read at N = 7, where the kernel transforms

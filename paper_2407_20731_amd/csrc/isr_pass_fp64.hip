@@ -28,6 +28,8 @@ hipError_t launch_decomp_wave_fp64(const Job& j, int gx, int cus, hipStream_t s,
   return launch_decompW_prec<P_FP64>(j, gx, cus, s, out, out_fp64);
 }
 
+hipError_t launch_quant_wave(const Job& j, hipStream_t s) { return launch_quantW(j, s); }
+
 int resident_fast_fp64(int kind, int order) { return resident_fast_prec<P_FP64>(kind, order); }
 
 }  // namespace isr

@@ -1839,7 +1839,7 @@ int run_compress_quantized(isr_ctx* c, const isr_field* f, double share, isr_blo
   q->dev_bytes = 256 + q->bitmap_bytes() + q->ptr_bytes() + q->values_bytes();
   q->dev = c->arena->alloc(q->dev_bytes, true);
   const size_t hist_bytes = (size_t)nc * HBINS * sizeof(HistBin);
-  char* scr = (char*)c->arena->alloc(hist_bytes + 512);
+  char* scr = (char*)c->arena->alloc(hist_bytes + 512 + (size_t)nc * FAST_GMAX * 4 * 8);
   auto cleanup = [&]() {
     if (scr) c->arena->free(scr);
     isr_blob_free(b);
@@ -1870,6 +1870,18 @@ int run_compress_quantized(isr_ctx* c, const isr_field* f, double share, isr_blo
   j.histR = (HistBin*)scr;
   j.ticket = (u32*)(scr + hist_bytes);
   double* err_dev = (double*)(scr + hist_bytes + 256);
+  // orders of the streaming path: wave tiles, error terms into running sums
+  // bounded as pass B's; higher orders: workgroup tiles and LDS histograms
+  const bool fast = fast_order(f->order, ISR_PREC_FP64);
+  if (fast) {
+    j.slotsB = (long long*)(scr + hist_bytes + 512);
+    fast_setup(c, j, plan_sizes(f, 0));
+    for (int k = 0; k < nc; ++k) {
+      const double U2 = b->comp[k].U2;
+      const int m = Bf[k] > 0.0 ? std::ilogb(Bf[k]) + 6 : (U2 > 0.0 ? std::ilogb(U2) - 80 : -876);
+      j.qxm[k] = std::max(-876, std::min(800, m));  // (the sums' own limits)
+    }
+  }
   const long long total = (long long)tiles_per_comp(f->order, f->n_elem) * nc;
   const int grid = (int)std::min<long long>(total, (long long)c->num_cu * resident_blocks(K_PASS3, ISR_PREC_FP64, f->order));
   int iters = 0;
@@ -1878,7 +1890,8 @@ int run_compress_quantized(isr_ctx* c, const isr_field* f, double share, isr_blo
     rc = ISR_OK;
     if (launch_zero(scr, hist_bytes + 256, s) != hipSuccess ||
         hipMemcpyAsync((void*)j.qstep, delta, 8 * nc, hipMemcpyHostToDevice, s) != hipSuccess ||
-        launch_pass(K_QUANT, ISR_PREC_FP64, j, grid, s) != hipSuccess || launch_err_total(j, err_dev, s) != hipSuccess ||
+        (fast ? launch_quant_wave(j, s) != hipSuccess || launch_quant_total(j, err_dev, s) != hipSuccess
+              : launch_pass(K_QUANT, ISR_PREC_FP64, j, grid, s) != hipSuccess || launch_err_total(j, err_dev, s) != hipSuccess) ||
         hipMemcpyAsync(err2, err_dev, 8 * nc, hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipMemcpyAsync(&over, j.ticket + 1, 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)

@@ -40,6 +40,25 @@ hipError_t launch_err_total(const Job& j, double* err2_out, hipStream_t s) {
   return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void k_quant_total(Job j, double* err2_out) {
+  __shared__ __int128 r3[4][3];
+  const int comp = blockIdx.x;
+  HistBin* gR = j.histR + (size_t)comp * HBINS;
+  __int128 K[3];
+  block_totals<3>(j.slotsB + (size_t)comp * j.gB * 4, j.gB, 4, K, r3, threadIdx.x);
+  if (threadIdx.x == 0) emit_total(gR, K, j.qxm[comp], j.xh, -1);
+  __threadfence();
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const double e = wb_round(hist_total(gR));
+  if (threadIdx.x == 0) err2_out[comp] = e;
+}
+
+hipError_t launch_quant_total(const Job& j, double* err2_out, hipStream_t s) {
+  hipLaunchKernelGGL(k_quant_total, dim3(j.ncomp), dim3(256), 0, s, j, err2_out);
+  return hipGetLastError();
+}
+
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s) {
   size_t nw = bytes / 8;
   if (nw == 0) return hipSuccess;
