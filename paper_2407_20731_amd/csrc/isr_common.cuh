@@ -135,45 +135,70 @@ DEV void wb_extract128(u64 w, int s, u64& lo, u64& hi, bool& sat) {
 // Significand sum of one exponent bin as a 128-bit integer.
 DEV u128 bin_sum(const HistBin& h) { return ((u128)h.hi << 21) + (u128)h.lo; }
 
-// Lane l's exact sum of exponent bins [32 l, 32 l + 32), relative to
-// X-unit shift base = max(32 l, 1); bin 2047 (non-finite) is excluded.
-DEV void chunk32(const HistBin* H, u64& lo, u64& hi, u64& cnt, int& base) {
-  int l = lane_id();
-  base = 32 * l > 1 ? 32 * l : 1;
-  u128 acc = 0;
-  u64 c = 0;
-  // all 32 bins are loaded before any is used (independent loads in flight)
-  HistBin hb[32];
+// Walks over a histogram's non-empty bins in ascending order, by one wave.
+// The bins' counts are loaded first, 64 neighbouring bins a load and all loads
+// in flight at once; a round of 64 bins is looked at again only when one of its
+// counts is set (two or three of the 32 rounds: exponents sit together).  The
+// code is short on purpose: these walks run once per kernel, on a cold
+// instruction cache, and their unrolled forms (32 bins a lane, 128-bit shifts
+// per bin) spent most of their ~20 us fetching instructions.
+constexpr int HROUNDS = HBINS / 64;
+
+// Lane l's counts of bins 64 k + l; bin 2047 (non-finite) is excluded.
+DEV void hist_counts(const HistBin* H, u64 (&c)[HROUNDS]) {
 #pragma unroll
-  for (int k = 0; k < 32; ++k) {
-    const int b = 32 * l + k;
-    hb[k] = b < HBINS - 1 ? H[b] : HistBin{0ull, 0ull, 0ull};
+  for (int k = 0; k < HROUNDS; ++k) {
+    const int b = 64 * k + lane_id();
+    c[k] = H[b].cnt;  // (HBINS bins: always inside)
   }
+  // all of the loads before the first use (left to itself the compiler waits
+  // for each in turn)
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int k = 0; k < 32; ++k) {
-    const int b = 32 * l + k;
-    if (hb[k].cnt == 0) continue;
-    int sh = (b > 1 ? b : 1) - base;
-    acc += bin_sum(hb[k]) << sh;
-    c += hb[k].cnt;
+  for (int k = 0; k < HROUNDS; k += 8)
+    asm volatile("" : "+v"(c[k]), "+v"(c[k + 1]), "+v"(c[k + 2]), "+v"(c[k + 3]), "+v"(c[k + 4]), "+v"(c[k + 5]),
+                      "+v"(c[k + 6]), "+v"(c[k + 7]));
+  if (lane_id() == 63) c[HROUNDS - 1] = 0ull;  // bin 2047
+}
+// Bit k: round k has a non-empty bin.
+DEV u32 hist_rounds(const u64 (&c)[HROUNDS]) {
+  u32 r = 0u;
+#pragma unroll
+  for (int k = 0; k < HROUNDS; ++k) r |= ballot(c[k] != 0ull) ? (1u << k) : 0u;
+  return r;
+}
+// fn(bin, lo, hi, count) for every non-empty bin, ascending, with the bin's
+// significand sum (lo, hi) and count in every lane; stops when fn is false.
+template <class FN>
+DEV void hist_walk(const HistBin* H, u32 rounds, FN fn) {
+  while (rounds) {
+    const int k = __ffs((int)rounds) - 1;
+    rounds &= rounds - 1u;
+    const int b = 64 * k + lane_id();
+    const HistBin h = b < HBINS - 1 ? H[b] : HistBin{0ull, 0ull, 0ull};
+    const u128 s = bin_sum(h);
+    u64 m = ballot(h.cnt != 0ull);
+    while (m) {
+      const int l = __ffsll((long long)m) - 1;
+      m &= m - 1ull;
+      if (!fn(64 * k + l, bcast64((u64)s, l), bcast64((u64)(s >> 64), l), bcast64(h.cnt, l))) return;
+    }
   }
-  lo = (u64)acc;
-  hi = (u64)(acc >> 64);
-  cnt = c;
 }
 
 // Exact total of a histogram as a wave-distributed big integer.
-DEV u64 hist_total(const HistBin* H) {
-  u64 lo, hi, cnt;
-  int base;
-  chunk32(H, lo, hi, cnt, base);
+DEV u64 hist_sum(const HistBin* H, u32 rounds) {
   u64 acc = 0;
-  for (int l = 0; l < 64; ++l) {
-    u64 cl = bcast64(lo, l), ch = bcast64(hi, l);
-    if ((cl | ch) == 0ull) continue;
-    wb_add(acc, part_at(cl, ch, l == 0 ? 1 : 32 * l));
-  }
+  hist_walk(H, rounds, [&](int bin, u64 lo, u64 hi, u64) {
+    wb_add(acc, part_at(lo, hi, bin > 1 ? bin : 1));
+    return true;
+  });
   return acc;
+}
+DEV u64 hist_total(const HistBin* H) {
+  u64 c[HROUNDS];
+  hist_counts(H, c);
+  return hist_sum(H, hist_rounds(c));
 }
 
 // ---- LDS histogram window of one workgroup ----------------------------------
@@ -250,29 +275,11 @@ DEV void lh_flush(LdsHist& h, HistBin* g, int tid, int nthr) {
 
 // ---- candidate lists -------------------------------------------------------------
 // Per component: list 0 (capacity list_cap) then lists 1 and 2 (list_cap / 2
-// each; they only hold the members of one refinement sub-bin).
+// each; they only hold members about to be sorted, at most CAP).
 DEV u64* list_ptr(const Job& j, int comp, int k) {
   return j.lists + (size_t)comp * 2 * j.list_cap + (k == 0 ? 0 : j.list_cap + (size_t)(k - 1) * (j.list_cap / 2));
 }
 DEV u64 list_capk(const Job& j, int k) { return k == 0 ? j.list_cap : j.list_cap / 2; }
-
-// Wave-aggregated append; the counter may run past cap (then ST_LIST is set
-// and readers clamp to cap).
-DEV void list_append(u64* list, u64* count, u64 cap, bool m, u64 key, int* flag) {
-  const u64 bal = ballot(m);
-  if (bal == 0ull) return;
-  const int leader = __ffsll((long long)bal) - 1;
-  u64 base = 0;
-  if (lane_id() == leader) base = atomicAdd(count, (u64)__popcll(bal));
-  base = shfl64(base, leader);
-  if (m) {
-    const u64 pos = base + (u64)__popcll(bal & ((1ull << lane_id()) - 1ull));
-    if (pos < cap)
-      list[pos] = key;
-    else
-      atomicOr(flag, ST_LIST);
-  }
-}
 
 // ---- decoupled look-back --------------------------------------------------------
 // Descriptor per tile: flag << 62 | value; flag 1 = aggregate, 2 = inclusive

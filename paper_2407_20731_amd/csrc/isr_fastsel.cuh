@@ -41,11 +41,19 @@ DEV void select_sample_body(const Job& j, int comp) {
   const double B = ((tol * tol) * st->samp_u2) * j.cut_scale;
   // (the sampled bins hold rounded sums only: one atomic per bin and
   // workgroup, and a bin of positive energies has a positive sum)
+  double v[32];
+#pragma unroll
+  for (int k = 0; k < 32; ++k) v[k] = __longlong_as_double((long long)H[32 * lane + k].lo);
+  // (all of the loads before the first use)
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < 32; k += 8)
+    asm volatile("" : "+v"(v[k]), "+v"(v[k + 1]), "+v"(v[k + 2]), "+v"(v[k + 3]), "+v"(v[k + 4]), "+v"(v[k + 5]),
+                      "+v"(v[k + 6]), "+v"(v[k + 7]));
+  if (lane == 63) v[31] = 0.0;  // bin 2047
   double cs = 0.0;
-  for (int k = 0; k < 32; ++k) {
-    const int b = 32 * lane + k;
-    if (b < HBINS - 1) cs += __longlong_as_double((long long)H[b].lo);
-  }
+#pragma unroll
+  for (int k = 0; k < 32; ++k) cs += v[k];
   double incl = cs;
   for (int d = 1; d < 64; d <<= 1) {
     const double o = __shfl_up(incl, d);
@@ -57,10 +65,11 @@ DEV void select_sample_body(const Job& j, int comp) {
   if (over) {
     const int fl = __ffsll((long long)over) - 1;
     double cum = __shfl(incl - cs, fl);
+    const u64 mine = lane < 32 ? H[32 * fl + lane].lo : 0ull;  // the crossing chunk, one bin a lane
     for (int k = 0; k < 32; ++k) {
       const int b = 32 * fl + k;
       if (b >= HBINS - 1) break;
-      cum += __longlong_as_double((long long)H[b].lo);
+      cum += __longlong_as_double((long long)bcast64(mine, k));
       if (cum > B) {
         bstar = b;
         break;
@@ -70,13 +79,9 @@ DEV void select_sample_body(const Job& j, int comp) {
     // every sampled energy fits the budget: the top bin (tau is likely +inf,
     // which the general pipeline handles)
     const int fl = 63 - __clzll((long long)nonempty);
-    for (int k = 31; k >= 0; --k) {
-      const int b = 32 * fl + k;
-      if (b < HBINS - 1 && __longlong_as_double((long long)H[b].lo) > 0.0) {
-        bstar = b;
-        break;
-      }
-    }
+    const u64 mine = lane < 32 && 32 * fl + lane < HBINS - 1 ? H[32 * fl + lane].lo : 0ull;
+    const u64 set = ballot(__longlong_as_double((long long)mine) > 0.0);
+    if (set) bstar = 32 * fl + 63 - __clzll((long long)set);
   }
   if (lane == 0) {
     const int wl = bstar - 1 < 1 ? 1 : bstar - 1;
@@ -340,10 +345,7 @@ DEV void passB_tail(const Job& j, int comp, __int128 (*r3)[3]) {
   const XParm PR = xparm(st->xm_err, j.xh);
   __int128 K[3];
   block_totals<3>(j.slotsB + (size_t)comp * j.gB * 4, j.gB, 4, K, r3, tid);
-  if (tid == 0) emit_total(j.histR + (size_t)comp * HBINS, K, PR.m, PR.h, -1);
-  __threadfence();
-  __syncthreads();
-  if (tid < 64) finalize_body(j, comp);
+  if (tid < 64) finalize_body(j, comp, total_words(K, PR.m, PR.h));
 }
 
 }  // namespace isr

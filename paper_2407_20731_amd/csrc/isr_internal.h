@@ -30,15 +30,18 @@ constexpr int WIN = 256;
 constexpr int WIN_HEAD = 16;  // bins kept above the first tile's largest exponent
 
 // Refinement of the threshold inside the boundary exponent bin: the 52
-// fraction bits are resolved 11 at a time (bits 51..41, 40..30, 29..19,
-// 18..8), then 8 (bits 7..0).  Levels are numbered 2..6; level 1 is the
-// exponent.
+// fraction bits are resolved 8 (bits 51..44), then 11 at a time (43..33,
+// 32..22, 21..11, 10..0).  Levels are numbered 2..6; level 1 is the exponent.
+// Few bins first: every workgroup of level 2 adds up to all of its bins to the
+// global ones (three atomics a bin: at 2048 bins they were most of the
+// kernel's 26 us at 100M values), and a sub-bin of 1/256 of the boundary bin
+// usually has few enough members to be sorted.
 constexpr int RBINS = 2048;
 constexpr int NLEV = 6;
 constexpr int CAP = 4096;  // a sub-bin with at most CAP members is resolved by sorting
 
-__host__ __device__ constexpr int level_shift(int L) { return L == 6 ? 0 : 41 - 11 * (L - 2); }
-__host__ __device__ constexpr int level_bits(int L) { return L == 6 ? 8 : 11; }
+__host__ __device__ constexpr int level_shift(int L) { return 44 - 11 * (L - 2); }
+__host__ __device__ constexpr int level_bits(int L) { return L == 2 ? 8 : 11; }
 
 // Per-component selection state, written by the select kernels.
 struct alignas(256) CompState {

@@ -350,16 +350,14 @@ static FastGrids fast_setup(isr_ctx* c, Job& j, const Sizes& z) {
   FastGrids g;
   const long long ss = j.sample_stride > 0 ? j.sample_stride : 1;
   const long long stiles = (ftiles + ss - 1) / ss;
-  // sixteen sampled tiles per workgroup; one per wavefront at N >= 8, whose
-  // tiles are large (1000+ values): there the serial chain of tiles per
-  // wavefront costs more than the extra workgroups' histogram atomics
-  g.gs = (int)std::max<long long>(1, j.order >= 8 ? std::min<long long>(256, (stiles + 3) / 4)
-                                                  : std::min<long long>(64, (stiles + 15) / 16));
-  // list passes over ~2 % of the values; few refinement workgroups (each
-  // flushes up to RBINS sub-bins with global atomics: 32 per component beat
-  // 16 and 64 at 100M values)
+  // one sampled tile per wavefront, up to 64 workgroups (each adds its bins
+  // with global atomics); up to 256 at N >= 8, whose tiles are large (1000+
+  // values): there the serial chain of tiles per wavefront costs more than the
+  // extra workgroups' atomics
+  g.gs = (int)std::max<long long>(1, std::min<long long>(j.order >= 8 ? 256 : 64, (stiles + 3) / 4));
+  // list passes over ~2 % of the values
   g.gl = (int)std::max<long long>(1, std::min<long long>(GATHER_GMAX, (long long)(z.nv >> 17) + 1));
-  g.rgx = std::max(1, std::min(32, (int)(z.nv >> 20) + 1));
+  g.rgx = std::max(1, std::min(64, (int)(z.nv >> 19) + 1));
   g.gsc = scan_grid_elems(j.n_elem);
   return g;
 }

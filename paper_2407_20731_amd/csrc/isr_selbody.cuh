@@ -27,10 +27,18 @@ DEV void select1_body(const Job& j, int comp, int sample) {
   const HistBin* HE = (sample ? j.histEs : j.histE) + (size_t)comp * HBINS;
   const double tol = j.tol;
   int flags = 0;
+  // both histograms' counts in flight before either is used
+  u64 cE[HROUNDS];
+  u32 rN;
+  {
+    u64 cN[HROUNDS];
+    hist_counts(HN, cN);
+    hist_counts(HE, cE);
+    rN = hist_rounds(cN);
+  }
   if (HN[HBINS - 1].cnt) flags |= ST_NONFINITE;
   if (HE[HBINS - 1].cnt) flags |= ST_OVERFLOW;
-  u64 U = hist_total(HN);
-  const double U2 = wb_round(U);
+  const double U2 = wb_round(hist_sum(HN, rN));
   if (sample) {
     if (tol < 0.0) return;
   } else if (lane == 0) {
@@ -74,48 +82,26 @@ DEV void select1_body(const Job& j, int comp, int sample) {
     wb_add(Tw, part_at(1ull, 0ull, sB - 1));
     if (sigB & 1ull) wb_sub(Tw, part_at(1ull, 0ull, 0));
   }
-  // walk the energy bins
-  u64 clo, chi, ccnt;
-  int base;
-  chunk32(HE, clo, chi, ccnt, base);
+  // walk the energy bins up to the one whose sum no longer fits
   u64 R = Tw, P = 0ull;
-  int bstar = -1, lcross = 64;
-  u64 cross_cnt = 0ull;  // this lane's bin of the crossing chunk: its count
+  int bstar = -1;
+  u64 bcnt = 0ull;
   bool found = false;
-  for (int l = 0; l < 64 && !Binf; ++l) {
-    const u64 cc = bcast64(ccnt, l);
-    if (cc == 0ull) continue;
-    const u64 cl = bcast64(clo, l), ch = bcast64(chi, l);
-    const int bl = l == 0 ? 1 : 32 * l;
-    u64 tmp = R;
-    wb_sub(tmp, part_at(cl, ch, bl));
-    if (!wb_neg(tmp)) {
+  if (!Binf) {
+    hist_walk(HE, hist_rounds(cE), [&](int bin, u64 lo, u64 hi, u64 cnt) {
+      const u64 part = part_at(lo, hi, bin > 1 ? bin : 1);
+      u64 tmp = R;
+      wb_sub(tmp, part);
+      if (wb_neg(tmp)) {
+        bstar = bin;
+        bcnt = cnt;
+        found = true;
+        return false;
+      }
       R = tmp;
-      wb_add(P, part_at(cl, ch, bl));
-      continue;
-    }
-    // the crossing chunk, one bin per lane (loads in parallel, then broadcast)
-    const int mybin = 32 * l + lane;
-    const HistBin mine = (lane < 32 && mybin < HBINS - 1) ? HE[mybin] : HistBin{0ull, 0ull, 0ull};
-    lcross = l;
-    cross_cnt = mine.cnt;
-    for (int k = 0; k < 32; ++k) {
-      const int bin = 32 * l + k;
-      if (bin >= HBINS - 1) break;
-      const HistBin h = {bcast64(mine.cnt, k), bcast64(mine.lo, k), bcast64(mine.hi, k)};
-      if (h.cnt == 0ull) continue;
-      bstar = bin;
-      const u128 sb = bin_sum(h);
-      const u64 sl = (u64)sb, sh = (u64)(sb >> 64);
-      const int s = bin > 1 ? bin : 1;
-      u64 t2 = R;
-      wb_sub(t2, part_at(sl, sh, s));
-      if (wb_neg(t2)) break;
-      R = t2;
-      wb_add(P, part_at(sl, sh, s));
-    }
-    found = true;
-    break;
+      wb_add(P, part);
+      return true;
+    });
   }
   if (!sample && st->win_mode) {
     // the streaming pass kept exact sums only inside the window: a boundary
@@ -155,9 +141,10 @@ DEV void select1_body(const Job& j, int comp, int sample) {
     }
     return;
   }
-  // counts above b*: the chunks above the crossing one, and the crossing
-  // chunk's bins above b* (bin HBINS - 1 is in neither)
-  u64 above = (lane > lcross ? ccnt : 0ull) + (lane < 32 && 32 * lcross + lane > bstar ? cross_cnt : 0ull);
+  // counts above b*
+  u64 above = 0ull;
+#pragma unroll
+  for (int k = 0; k < HROUNDS; ++k) above += 64 * k + lane > bstar ? cE[k] : 0ull;
   above = wave_sum64(above);
   const int s = bstar > 1 ? bstar : 1;
   u64 rlo, rhi;
@@ -169,7 +156,7 @@ DEV void select1_body(const Job& j, int comp, int sample) {
     st->B = B;
     st->bstar = bstar;
     st->kept_above = above;
-    st->cur_count = HE[bstar].cnt;
+    st->cur_count = bcnt;
     st->key_prefix = (u64)bstar << 52;
     st->key_mask = 0x7FFull << 52;
     st->r_lo = rlo;
@@ -189,14 +176,14 @@ DEV void select1_body(const Job& j, int comp, int sample) {
 
 // --------------------------------------------------------------------------
 // refine, level L in 2..6: histogram of the next fraction bits of the listed
-// energies that match the current prefix; for L >= 3 the matching keys are
-// also copied to the other list.
+// energies that match the current prefix, or, once a sub-bin has at most CAP
+// members (L >= 3), those members in a list of their own for the selection of
+// the same level to sort.
 
-// List 0 (the candidates of the boundary bin or window) is only read, by
-// levels 2 and 3; levels 3..6 copy the members of the current sub-bin to
-// lists 1, 2, 1, 2, so list 0 stays whole for the per-element kept counts.
+// List 0 (the candidates of the boundary bin or window) is only read, by every
+// level, so that it stays whole for the per-element kept counts; the members
+// go to lists 1, 2, 1, 2 at levels 3..6.
 DEV int list_out(int L) { return (L & 1) ? 1 : 2; }
-DEV int list_in(int L) { return L <= 3 ? 0 : 3 - list_out(L); }
 DEV int list_members(int L) { return L == 2 ? 0 : list_out(L); }
 
 // Worker `item` of `nitems` handles list entries item*256 + tid + k*nitems*256
@@ -208,66 +195,191 @@ DEV void refine_body(const Job& j, int comp, int L, u64 (*h)[2], u64 item, u64 n
   __syncthreads();
   const int nb = 1 << level_bits(L), sh = level_shift(L);
   const u64 fmask = (u64)(nb - 1);
-  for (int k = tid; k < nb; k += 256) h[k][0] = h[k][1] = 0ull;
+  // A sub-bin that the selection will sort (at most CAP members) needs no
+  // histogram: its members are collected in the same LDS (which holds CAP of
+  // them) and appended with one global atomic per workgroup.
+  static_assert(2 * RBINS >= CAP, "the histogram's LDS holds the members");
+  __shared__ u32 nst;
+  __shared__ u64 gbase;
+  const bool gather = L >= 3 && st->cur_count <= (u64)CAP;
+  u64* stage = &h[0][0];
+  if (tid == 0) nst = 0u;
+  if (!gather)
+    for (int k = tid; k < nb; k += 256) h[k][0] = h[k][1] = 0ull;
   __syncthreads();
-  const int li = list_in(L);
-  const u64* in = list_ptr(j, comp, li);
-  const u64 nin = st->list_count[li] < list_capk(j, li) ? st->list_count[li] : list_capk(j, li);
+  const u64* in = list_ptr(j, comp, 0);
+  const u64 nin = st->list_count[0] < list_capk(j, 0) ? st->list_count[0] : list_capk(j, 0);
   const u64 prefix = st->key_prefix, mask = st->key_mask;
   const int bstar = st->bstar;
   const u64 implicit = bstar ? (1ull << 52) : 0ull;
   const int lo_idx = L >= 3 ? list_out(L) : 0;
   u64* out = list_ptr(j, comp, lo_idx);
   const u64 stride = nitems * 256;
-  // the loop trip count is the same for every lane of a wave (ballots inside)
-  const u64 nin_r = (nin + 63) & ~63ull;
   // sixteen entries per lane per step, loaded before any is used (the lists
   // run to millions of entries: more loads in flight per lane)
   constexpr int U = 16;
-  for (u64 i0 = item * 256 + tid; i0 < nin_r; i0 += U * stride) {
-    u64 keys[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const u64 i = i0 + u * stride;
-      keys[u] = i < nin ? in[i] : 0ull;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const u64 i = i0 + u * stride;
-      const u64 key = keys[u];
-      const bool m = i < nin && (key & mask) == prefix;
-      if (m) {
-        const u64 sig = (key & M52) | implicit;
-        const int sb = (int)((key >> sh) & fmask);
-        atomicAdd(&h[sb][0], (1ull << 43) + (sig & M21));
-        atomicAdd(&h[sb][1], sig >> 21);
-      }
-      // (i < nin_r is the same for every lane of a wave: ballots inside)
-      if (L >= 3 && i < nin_r) list_append(out, &st->list_count[lo_idx], list_capk(j, lo_idx), m, key, &st->flags);
-    }
-  }
-  __syncthreads();
   HistBin* g = j.histL + ((size_t)(L - 2) * j.ncomp + comp) * RBINS;
-  for (int k = tid; k < nb; k += 256) {
-    const u64 w0 = h[k][0], w1 = h[k][1];
-    if (w0 | w1) global_bin_add(g, k, w0 >> 43, w0 & M43, w1);
+  // at most 2^20 entries of a worker between two flushes: a bin's count has 21
+  // bits in LDS
+  const u64 seg = nitems << 20;
+  for (u64 s0 = 0; s0 < nin; s0 += seg) {
+    const u64 end = nin - s0 < seg ? nin : s0 + seg;
+    for (u64 i0 = s0 + item * 256 + tid; i0 < end; i0 += U * stride) {
+      u64 keys[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const u64 i = i0 + u * stride;
+        keys[u] = i < end ? in[i] : 0ull;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const u64 i = i0 + u * stride;
+        const u64 key = keys[u];
+        const bool m = i < end && (key & mask) == prefix;
+        if (gather) {
+          if (m) {  // (the bin's count bounds this; a list that disagrees with it is flagged below)
+            const u32 pos = atomicAdd(&nst, 1u);
+            if (pos < (u32)CAP) stage[pos] = key;
+          }
+          continue;
+        }
+        if (m) {
+          const u64 sig = (key & M52) | implicit;
+          const int sb = (int)((key >> sh) & fmask);
+          atomicAdd(&h[sb][0], (1ull << 43) + (sig & M21));
+          atomicAdd(&h[sb][1], sig >> 21);
+        }
+      }
+    }
+    if (gather) continue;
+    __syncthreads();
+    for (int k = tid; k < nb; k += 256) {
+      const u64 w0 = h[k][0], w1 = h[k][1];
+      if (w0 | w1) {
+        global_bin_add(g, k, w0 >> 43, w0 & M43, w1);
+        h[k][0] = h[k][1] = 0ull;
+      }
+    }
+    __syncthreads();
   }
   __syncthreads();
+  if (gather) {
+    const u32 k = nst < (u32)CAP ? nst : (u32)CAP;
+    if (tid == 0) {
+      gbase = k ? atomicAdd(&st->list_count[lo_idx], (u64)nst) : 0ull;
+      if (nst > (u32)CAP) atomicOr(&st->flags, ST_LIST);
+    }
+    __syncthreads();
+    for (u32 i = tid; i < k; i += 256) {
+      if (gbase + i < list_capk(j, lo_idx))
+        out[gbase + i] = stage[i];
+      else
+        atomicOr(&st->flags, ST_LIST);
+    }
+    __syncthreads();
+  }
 }
 
 
-// Resolve tau among <= CAP listed members of the current sub-bin by sorting
-// them and scanning their significands in ascending order.
-DEV void resolve_sorted(const Job& j, CompState* st, int comp, int ml, int L, u64* keys, u64* slo, u64* shi,
-                        int* best) {
+// Resolve tau among <= CAP listed members of the current sub-bin: narrowed in
+// LDS by eight fraction bits at a time (exact sums of 256 bins, scanned by the
+// workgroup) until few are left, which are sorted and scanned in ascending
+// order.  (Sorting some 1500 members took 60 us: 66 bitonic steps of 8 LDS
+// round trips a thread each; narrowing takes ~3 us a step.)
+constexpr int SORT_MAX = 64;
+
+// Inclusive scan of one 128-bit value per thread (Hillis-Steele in LDS).
+DEV u128 block_incl_scan128(u128 v, u64* slo, u64* shi, int tid) {
+  u128 incl = v;
+  for (int d = 1; d < 256; d <<= 1) {
+    slo[tid] = (u64)incl;
+    shi[tid] = (u64)(incl >> 64);
+    __syncthreads();
+    u128 add = 0;
+    if (tid >= d) add = ((u128)shi[tid - d] << 64) | slo[tid - d];
+    __syncthreads();
+    incl += add;
+  }
+  return incl;
+}
+
+struct SelLds {
+  u64 keys[CAP];
+  u64 slo[256], shi[256];
+  u64 hist[256][2];  // (count << 43) + sum of the low 21 significand bits, sum of the rest
+  int best;
+  u32 n, above;
+  u64 exlo, exhi;
+};
+
+DEV void resolve_sorted(const Job& j, CompState* st, int comp, int ml, int L, SelLds& S) {
   const int tid = threadIdx.x;
+  u64* keys = S.keys;
   const u64* list = list_ptr(j, comp, ml);
   const u64 lc = st->list_count[ml];
-  const int cnt = (int)(lc < (u64)CAP ? lc : (u64)CAP);  // == cur_count unless a list overflowed
+  int cnt = (int)(lc < (u64)CAP ? lc : (u64)CAP);  // == cur_count unless a list overflowed
+  const u64 implicit = st->bstar ? (1ull << 52) : 0ull;
+  u128 r = ((u128)st->r_hi << 64) | st->r_lo;
+  u128 w = ((u128)st->w_hi << 64) | st->w_lo;
+  u64 kept_above = st->kept_above;
+  int fixed = L == 2 ? 52 : level_shift(L - 1);  // fraction bits below this one are still open
+  for (int i = tid; i < cnt; i += 256) keys[i] = list[i];
+  __syncthreads();
+  while (cnt > SORT_MAX && fixed > 0) {
+    const int sh = fixed > 8 ? fixed - 8 : 0;
+    const u64 fmask = (1ull << (fixed - sh)) - 1ull;
+    S.hist[tid][0] = S.hist[tid][1] = 0ull;
+    if (tid == 0) {
+      S.n = S.above = 0u;
+      S.best = -1;
+    }
+    __syncthreads();
+    for (int i = tid; i < cnt; i += 256) {
+      const u64 sig = (keys[i] & M52) | implicit;
+      const int sb = (int)((keys[i] >> sh) & fmask);
+      atomicAdd(&S.hist[sb][0], (1ull << 43) + (sig & M21));
+      atomicAdd(&S.hist[sb][1], sig >> 21);
+    }
+    __syncthreads();
+    const u64 w0 = S.hist[tid][0], w1 = S.hist[tid][1];
+    const u128 sum = ((u128)w1 << 21) + (u128)(w0 & M43);
+    const u128 incl = block_incl_scan128(sum, S.slo, S.shi, tid);
+    // the boundary: the first bin whose inclusive sum no longer fits
+    if (incl > r && incl - sum <= r) {
+      S.best = tid;
+      S.exlo = (u64)(incl - sum);
+      S.exhi = (u64)((incl - sum) >> 64);
+    }
+    __syncthreads();
+    const int sb = S.best;
+    if (sb < 0) break;  // everything fits (a list that disagrees with its counts: flagged below)
+    if (tid > sb && w0) atomicAdd(&S.above, (u32)(w0 >> 43));
+    // the boundary bin's members to the front (all read before any is written)
+    u64 mine[CAP / 256];
+#pragma unroll
+    for (int k = 0; k < CAP / 256; ++k) {
+      const int i = tid + 256 * k;
+      mine[k] = i < cnt ? keys[i] : 0ull;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < CAP / 256; ++k)
+      if (tid + 256 * k < cnt && (int)((mine[k] >> sh) & fmask) == sb) keys[atomicAdd(&S.n, 1u)] = mine[k];
+    __syncthreads();
+    const u128 ex = ((u128)S.exhi << 64) | S.exlo;
+    r -= ex;
+    w += ex;
+    kept_above += S.above;
+    cnt = (int)S.n;
+    fixed = sh;
+    __syncthreads();
+  }
+  if (tid == 0) S.best = 0;
+  // (with no bit open the members are one value: any order is sorted)
   int np = 1;
-  while (np < cnt) np <<= 1;
-  for (int i = tid; i < np; i += 256) keys[i] = i < cnt ? list[i] : ~0ull;
-  if (tid == 0) *best = 0;
+  if (fixed > 0)
+    while (np < cnt) np <<= 1;
+  for (int i = cnt + tid; i < np; i += 256) keys[i] = ~0ull;
   __syncthreads();
   for (int k = 2; k <= np; k <<= 1) {
     for (int jj = k >> 1; jj > 0; jj >>= 1) {
@@ -285,27 +397,14 @@ DEV void resolve_sorted(const Job& j, CompState* st, int comp, int ml, int L, u6
       __syncthreads();
     }
   }
-  const u64 implicit = st->bstar ? (1ull << 52) : 0ull;
-  const int per = (np + 255) / 256;
+  const int per = (cnt + 255) / 256;
   const int i0 = tid * per;
   u128 run = 0;
   for (int k = 0; k < per; ++k) {
     const int i = i0 + k;
     if (i < cnt) run += (u128)((keys[i] & M52) | implicit);
   }
-  // inclusive scan of the 256 per-thread sums (Hillis-Steele in LDS)
-  u128 incl = run;
-  for (int d = 1; d < 256; d <<= 1) {
-    slo[tid] = (u64)incl;
-    shi[tid] = (u64)(incl >> 64);
-    __syncthreads();
-    u128 add = 0;
-    if (tid >= d) add = ((u128)shi[tid - d] << 64) | slo[tid - d];
-    __syncthreads();
-    incl += add;
-  }
-  const u128 r = ((u128)st->r_hi << 64) | st->r_lo;
-  u128 ex = incl - run;
+  u128 ex = block_incl_scan128(run, S.slo, S.shi, tid) - run;
   int mybest = -1;
   u128 myex = 0;
   for (int k = 0; k < per; ++k) {
@@ -318,26 +417,20 @@ DEV void resolve_sorted(const Job& j, CompState* st, int comp, int ml, int L, u6
     }
     ex += (u128)((keys[i] & M52) | implicit);
   }
-  if (mybest >= 0) atomicMax(best, mybest);
+  if (mybest >= 0) atomicMax(&S.best, mybest);
   __syncthreads();
-  const int bi = *best;
+  const int bi = S.best;
   if (mybest >= 0 && mybest == bi) {
-    const u128 w = (((u128)st->w_hi << 64) | st->w_lo) + myex;
+    w += myex;
     st->w_lo = (u64)w;
     st->w_hi = (u64)(w >> 64);
     st->tau = __longlong_as_double((long long)keys[bi]);
-    st->kept = st->kept_above + (u64)(cnt - bi);
+    st->kept = kept_above + (u64)(cnt - bi);
     st->resolved = 1;
     st->level = L;
     if (lc != st->cur_count) st->flags |= ST_LIST;
   }
 }
-
-struct SelLds {
-  u64 keys[CAP];
-  u64 slo[256], shi[256];
-  int best;
-};
 
 // blockDim must be 256; the sub-bin walk runs on wave 0.
 // One wave walks the NB = 64 PER sub-bins of level L: lane l sums sub-bins
@@ -441,7 +534,7 @@ DEV void select_body(const Job& j, int comp, int L, SelLds& S) {
   const int ml = list_members(L);
   __syncthreads();
   if (st->cur_count <= (u64)CAP && (L > 2 || st->list0_exact)) {
-    resolve_sorted(j, st, comp, ml, L, S.keys, S.slo, S.shi, &S.best);
+    resolve_sorted(j, st, comp, ml, L, S);
     return;
   }
   if (tid >= 64) return;
@@ -455,11 +548,13 @@ DEV void select_body(const Job& j, int comp, int L, SelLds& S) {
 // --------------------------------------------------------------------------
 // finalize (one wave per component): err2, rel, dropped energy.
 
-// Run by one whole wave.
-DEV void finalize_body(const Job& j, int comp) {
+// Run by one whole wave.  more: what the error sum holds beside the bins (a
+// wave-distributed big integer).
+DEV void finalize_body(const Job& j, int comp, u64 more = 0ull) {
   const int lane = lane_id();
   CompState* st = j.st + comp;
   u64 er = hist_total(j.histR + (size_t)comp * HBINS);
+  wb_add(er, more);
   const double err2 = wb_round(er);
   const double U2 = st->U2;
   const double rel = U2 > 0.0 ? __builtin_sqrt(err2 / U2) : 0.0;

@@ -46,11 +46,10 @@ __global__ __launch_bounds__(256) void k_quant_total(Job j, double* err2_out) {
   HistBin* gR = j.histR + (size_t)comp * HBINS;
   __int128 K[3];
   block_totals<3>(j.slotsB + (size_t)comp * j.gB * 4, j.gB, 4, K, r3, threadIdx.x);
-  if (threadIdx.x == 0) emit_total(gR, K, j.qxm[comp], j.xh, -1);
-  __threadfence();
-  __syncthreads();
   if (threadIdx.x >= 64) return;
-  const double e = wb_round(hist_total(gR));
+  u64 w = hist_total(gR);
+  wb_add(w, total_words(K, j.qxm[comp], j.xh));
+  const double e = wb_round(w);
   if (threadIdx.x == 0) err2_out[comp] = e;
 }
 
@@ -147,8 +146,8 @@ hipError_t launch_refsel(const Job& j, int gx, hipStream_t s) {
   hipLaunchKernelGGL(k_refine, dim3(gx, j.ncomp), dim3(256), 0, s, j, 2);
   hipLaunchKernelGGL(k_select, dim3(j.ncomp), dim3(256), 0, s, j, 2);
   // level 3 matches only the members of one level-2 sub-bin, so its
-  // workgroups flush few bins: more of them, for fewer list loads each
-  const int gx3 = gx * 8 < GATHER_GMAX ? gx * 8 : GATHER_GMAX;
+  // workgroups add little to global memory: twice as many of them
+  const int gx3 = gx * 2 < GATHER_GMAX ? gx * 2 : GATHER_GMAX;
   hipLaunchKernelGGL(k_refine, dim3(gx3, j.ncomp), dim3(256), 0, s, j, 3);
   hipLaunchKernelGGL(k_select_rest, dim3(j.ncomp), dim3(256), 0, s, j);
   return hipGetLastError();

@@ -251,6 +251,19 @@ DEV u64 wave_max_dpp(u64 v) {
   return wave_reduce_dpp(v, [](u64 a, u64 b) { return a > b ? a : b; });
 }
 
+// The same total as a wave-distributed big integer (X units of 2^-1075), from
+// sums that every lane holds.
+DEV u64 total_words(const __int128 (&K)[3], int m, int h) {
+  I192 z = {{0ull, 0ull, 0ull}};
+  i192_add_shl(z, K[0], 107 - 2 * h);
+  i192_add_shl(z, K[1], 53 - h);
+  i192_add_shl(z, K[2], 0);
+  const int sh = m + 3 * h + 916;  // u3 in X units: at least 2^61
+  u64 w = part_at(z.w[0], z.w[1], sh);
+  wb_add(w, part_at(z.w[2], 0ull, sh + 128));
+  return w;
+}
+
 DEV long long wave_sum_i64(long long v) { return (long long)wave_sum64((u64)v); }
 
 DEV double wave_sum_f64(double v) {
