@@ -274,12 +274,15 @@ DEV void lh_flush(LdsHist& h, HistBin* g, int tid, int nthr) {
 }
 
 // ---- candidate lists -------------------------------------------------------------
-// Per component: list 0 (capacity list_cap) then lists 1 and 2 (list_cap / 2
-// each; they only hold members about to be sorted, at most CAP).
-DEV u64* list_ptr(const Job& j, int comp, int k) {
-  return j.lists + (size_t)comp * 2 * j.list_cap + (k == 0 ? 0 : j.list_cap + (size_t)(k - 1) * (j.list_cap / 2));
+// List 0 of every component (capacity list_cap), then lists 1 and 2 of every
+// component (members about to be sorted: at most CAP).
+DEV u64 list_capk(const Job& j, int k) {
+  return k == 0 ? j.list_cap : (j.list_cap / 2 < (u64)CAP ? j.list_cap / 2 : (u64)CAP);
 }
-DEV u64 list_capk(const Job& j, int k) { return k == 0 ? j.list_cap : j.list_cap / 2; }
+DEV u64* list_ptr(const Job& j, int comp, int k) {
+  if (k == 0) return j.lists + (size_t)comp * j.list_cap;
+  return j.lists + (size_t)j.ncomp * j.list_cap + ((size_t)comp * 2 + (k - 1)) * list_capk(j, 1);
+}
 
 // ---- decoupled look-back --------------------------------------------------------
 // Descriptor per tile: flag << 62 | value; flag 1 = aggregate, 2 = inclusive

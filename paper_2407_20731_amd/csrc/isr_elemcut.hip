@@ -21,9 +21,8 @@
 // the result is rounded once.  The workgroup adds every element's exact norm
 // and dropped energy into per-component digit totals, and the finishing
 // kernel rounds the component totals.  The kept counts are known per element
-// by then, so orders 1..7 go on with the offset scan and pass B of the
-// streaming path on the per-element thresholds; higher orders with pass 3 of
-// the general pipeline.
+// by then, so the offset scan and pass B of the streaming path follow, on the
+// per-element thresholds.
 #include "isr.h"
 #include "isr_engine.cuh"
 

@@ -220,14 +220,19 @@ hipError_t launch_select(const Job& j, int level, hipStream_t s);
 hipError_t launch_finalize(const Job& j, hipStream_t s);
 hipError_t launch_refsel(const Job& j, int grid_x, hipStream_t s);  // levels 2..NLEV
 
-// Streaming path (isr_engine.cuh) for orders 1..7.
+// Streaming path: wave tiles (isr_engine.cuh), dense tiles, large orders, and
+// workgroup tiles for FP64 above order 7.
 enum FastKind { F_SAMPLE = 0, F_PASSA = 1, F_PASSB = 2 };
 enum DoneSlot { D_SAMPLE = 0, D_GATHER = 1, D_COUNT = 2, D_PASSB = 3, D_REFSEL = 4 };  // D_REFSEL + level
-constexpr int FAST_MAX_ORDER = 7;     // every precision
+constexpr int FAST_MAX_ORDER = 7;     // wave tiles, every precision
 constexpr int FAST_MAX_ORDER_MF = 11; // FP32 / BF16 (large-order engine, isr_engine_l.cuh)
 inline bool fast_order(int order, int precision) {
-  return order >= 1 && (order <= FAST_MAX_ORDER || (precision != 0 && order <= FAST_MAX_ORDER_MF));
+  return order >= 1 && (precision == 0 ? order <= 15 : order <= FAST_MAX_ORDER_MF);
 }
+// FP64 above the wave tiles: workgroup tiles (isr_engine_g.cuh)
+inline bool wide_order(int order, int precision) { return precision == 0 && order > FAST_MAX_ORDER; }
+hipError_t launch_fast_wide(int kind, const Job& j, int grid_x, hipStream_t s);
+int resident_fast_wide(int kind, int order);
 // Tile shapes compiled for the dense-tile engine (isr_engine_d.cuh, FP32 and
 // BF16): X(order, elements per wavefront tile).
 #define ISR_DENSE_SHAPES(X)                                                                               \

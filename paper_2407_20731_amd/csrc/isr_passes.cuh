@@ -584,11 +584,10 @@ DEV void pass3_tile(const Job& j, int comp, long long t, Pass3Lds<N, PREC>& L,
   bool keep[n];
   X::forward(L.su, L.sw, L.sm, rg, el, a, b, act, ne, c);
   if (act) {
-    const double tau = j.tau_elem ? j.tau_elem[(size_t)comp * E + e] : tau_c;
 #pragma unroll
     for (int r = 0; r < n; ++r) {
       const double en = jw(j.jac, e, j.tab.g3[(r * n + a) * n + b]) * (c[r] * c[r]);
-      keep[r] = en >= tau;
+      keep[r] = en >= tau_c;
       if (keep[r]) {
         const int f = (r * n + a) * n + b;
         atomicOr(&L.bm[el * W + (f >> 6)], 1ull << (f & 63));

@@ -201,7 +201,13 @@ static int check_field(const isr_field* f) {
 
 namespace isr {
 
-Sizes plan_sizes(const isr_field* f, int tile, bool full_lists) {
+// elements of a workgroup tile (Shape<N>::EPI)
+static long long shape_epi(int order) {
+  const long long n2 = (long long)(order + 1) * (order + 1);
+  return 256 / n2 > 0 ? 256 / n2 : 1;
+}
+
+Sizes plan_sizes(const isr_field* f, int tile, bool full_lists, bool stream) {
   Sizes z;
   const long long n = f->order + 1, n3 = n * n * n;
   const int nc = f->ncomp;
@@ -229,17 +235,30 @@ Sizes plan_sizes(const isr_field* f, int tile, bool full_lists) {
   z.off_done = take(16 * 8 * sizeof(u32));
   z.zero_bytes = o;
   z.list_cap = full_lists || z.nv <= (1ull << 20) ? z.nv : std::max<u64>(z.nv / 8, 1ull << 20);
-  z.off_lists = take((size_t)nc * 2 * z.list_cap * 8);  // list 0, then lists 1 and 2 at half size
-  z.fast = fast_order(f->order, f->precision);
+  z.off_lists = take((size_t)nc * 2 * z.list_cap * 8);  // lists 0, then 1 and 2 (at most CAP entries each)
+  z.fast = stream && fast_order(f->order, f->precision);
   z.tile = z.fast && f->precision != ISR_PREC_FP64 && dense_shape(f->order, tile) ? tile : 0;
   if (z.fast) {
-    const long long epw = fast_epw(f->order, z.tile), ftiles = (f->n_elem + epw - 1) / epw;
-    z.sample_stride = std::max<long long>(1, ftiles / 1024);  // about 1024 sampled tiles
-    z.off_lidx = take((size_t)nc * z.list_cap * 4);
-    z.off_cnt = take((size_t)nc * f->n_elem * 4);
-    z.off_slotsA = take((size_t)nc * FAST_GMAX * 8 * 8);
-    z.off_slotsB = take((size_t)nc * FAST_GMAX * 4 * 8);
-    z.off_chunk = take((size_t)nc * ((f->n_elem + 1023) / 1024) * 8);
+    const bool wide = wide_order(f->order, f->precision);
+    const long long epw = wide ? shape_epi(f->order) : fast_epw(f->order, z.tile);
+    const long long ftiles = (f->n_elem + epw - 1) / epw;
+    z.sample_stride = std::max<long long>(1, ftiles / (wide ? 512 : 1024));  // about so many sampled tiles
+    // workgroup tiles: in the unused part of lists 1 and 2 where that holds
+    // them, so that the footprint stays that of the general pipeline
+    size_t sp = z.off_lists + (((size_t)nc * (z.list_cap + 2 * std::min<u64>(CAP, z.list_cap / 2)) * 8 + 255) & ~size_t(255));
+    const size_t sp_end = wide ? z.off_lists + (size_t)nc * 2 * z.list_cap * 8 : 0;
+    auto place = [&](size_t b) {
+      if (sp + b > sp_end) return take(b);
+      const size_t r = sp;
+      sp += (b + 255) & ~size_t(255);
+      return r;
+    };
+    z.off_lidx = place((size_t)nc * z.list_cap * 4);
+    z.off_cnt = place((size_t)nc * f->n_elem * 4);
+    const size_t rows = wide ? std::min<size_t>(FAST_GMAX, ftiles) : FAST_GMAX;  // workgroups at most
+    z.off_slotsA = place((size_t)nc * rows * 8 * 8);
+    z.off_slotsB = place((size_t)nc * rows * 4 * 8);
+    z.off_chunk = place((size_t)nc * ((f->n_elem + 1023) / 1024) * 8);
   }
   z.scratch_bytes = o;
   z.blob_max = 256 + (size_t)nc * f->n_elem * z.W * 8 + (size_t)nc * (f->n_elem + 1) * 8 + (size_t)nc * z.nv * z.vbytes;
@@ -331,19 +350,22 @@ struct FastGrids {
 
 static FastGrids fast_setup(isr_ctx* c, Job& j, const Sizes& z) {
   const int nc = j.ncomp, prec = j.precision;
-  const long long epw = fast_epw(j.order, j.tile);
+  const bool wide = wide_order(j.order, prec);
+  const long long epw = wide ? shape_epi(j.order) : fast_epw(j.order, j.tile);
   const long long ftiles = (j.n_elem + epw - 1) / epw;
+  const long long tpw = wide ? 1 : 4;  // tiles a workgroup works on at once
   auto grid = [&](int kind) {
     const long long slots = (long long)c->num_cu * resident_fast(kind, prec, j.order, j.tile);
     long long g = std::max<long long>(1, slots / nc);
-    g = std::min<long long>(g, (ftiles + 3) / 4);
+    g = std::min<long long>(g, (ftiles + tpw - 1) / tpw);
     return (int)std::max<long long>(1, std::min<long long>(g, FAST_GMAX));
   };
   j.gA = grid(F_PASSA);
   j.gB = grid(F_PASSB);
-  // terms per lane: values per lane per tile times tiles per wave
-  const long long per_wave = (ftiles + 4ll * std::min(j.gA, j.gB) - 1) / (4ll * std::min(j.gA, j.gB));
-  const long long terms = fast_lane_terms(j.order, j.tile) * per_wave;
+  // terms per lane: values per lane per tile (n at most in a workgroup tile)
+  // times tiles per wave (workgroup)
+  const long long per_wave = (ftiles + tpw * std::min(j.gA, j.gB) - 1) / (tpw * std::min(j.gA, j.gB));
+  const long long terms = (wide ? j.order + 1 : fast_lane_terms(j.order, j.tile)) * per_wave;
   int h = 1;
   while ((1ll << (h - 1)) < terms) ++h;
   j.xh = std::max(7, std::min(20, h));
@@ -354,7 +376,7 @@ static FastGrids fast_setup(isr_ctx* c, Job& j, const Sizes& z) {
   // with global atomics); up to 256 at N >= 8, whose tiles are large (1000+
   // values): there the serial chain of tiles per wavefront costs more than the
   // extra workgroups' atomics
-  g.gs = (int)std::max<long long>(1, std::min<long long>(j.order >= 8 ? 256 : 64, (stiles + 3) / 4));
+  g.gs = (int)std::max<long long>(1, std::min<long long>(j.order >= 8 ? 256 : 64, (stiles + tpw - 1) / tpw));
   // list passes over ~2 % of the values
   g.gl = (int)std::max<long long>(1, std::min<long long>(GATHER_GMAX, (long long)(z.nv >> 17) + 1));
   g.rgx = std::max(1, std::min(64, (int)(z.nv >> 19) + 1));
@@ -516,7 +538,8 @@ int ctx_tile(const isr_ctx* c, int order, int precision) {
 
 // Footprint a request needs from the arena (scratch + worst-case blob).
 uint64_t request_footprint(const isr_field* f) {
-  Sizes z = plan_sizes(f, 0, false);
+  // (workgroup tiles run within the general pipeline's footprint if they must)
+  Sizes z = plan_sizes(f, 0, false, !wide_order(f->order, f->precision));
   return (uint64_t)z.scratch_bytes + z.blob_max + 512;
 }
 
@@ -637,6 +660,10 @@ int task_begin(isr_ctx* c, const isr_field* f, hipStream_t s, bool timing, Task*
   t->t_start = now_s();
   t->z = plan_sizes(f, ctx_tile(c, f->order, f->precision), t->full_lists);
   t->scratch = (char*)c->arena->alloc(t->z.scratch_bytes);
+  if (!t->scratch && wide_order(f->order, f->precision)) {  // the general pipeline where only its scratch fits
+    t->z = plan_sizes(f, 0, t->full_lists, false);
+    t->scratch = (char*)c->arena->alloc(t->z.scratch_bytes);
+  }
   if (!t->scratch) return fail(ISR_ENOMEM, "scratch of %zu bytes does not fit the HBM budget", t->z.scratch_bytes);
   t->b = new_blob(c, f, t->z);
   if (!t->b) {
@@ -695,8 +722,13 @@ int task_step(Task* t, isr_blob** out) {
     CompState* const hs_out = t->j.hs_out;
     t->full_lists = true;
     t->c->arena->free(t->scratch);
-    t->z = plan_sizes(f, t->z.tile, true);
+    t->z = plan_sizes(f, t->z.tile, true, t->z.fast);
     t->scratch = (char*)t->c->arena->alloc(t->z.scratch_bytes);
+    if (!t->scratch && wide_order(f->order, f->precision)) {
+      t->z = plan_sizes(f, 0, true, false);
+      t->scratch = (char*)t->c->arena->alloc(t->z.scratch_bytes);
+      t->fast = false;
+    }
     if (!t->scratch) {
       task_release(t);
       return fail(ISR_ENOMEM, "candidate lists for every value (%zu bytes of scratch) do not fit the HBM budget",
@@ -1058,7 +1090,7 @@ int run_batch(isr_ctx* c, const isr_field* fs, int count, isr_blob** outs, isr_s
   for (int i = 0; i < count; ++i) {
     outs[i] = nullptr;
     Snap& x = sn[i];
-    x.z = plan_sizes(&fs[i], 0);
+    x.z = plan_sizes(&fs[i], 0, true, !wide_order(fs[i].order, fs[i].precision));
     x.z.sample_stride = x.z.tiles >= 1024 ? 32 : 0;  // the batch kernel runs the general passes
     x.scratch = (char*)c->arena->alloc(x.z.scratch_bytes);
     x.b = x.scratch ? new_blob(c, &fs[i], x.z) : nullptr;
@@ -1717,7 +1749,11 @@ int run_compress_noalloc(isr_ctx* c, const isr_field* f, char* scratch, size_t s
   if (!d_out) return fail(ISR_EINVAL, "output pointer is NULL");
   if (((uintptr_t)d_out) & 255) return fail(ISR_EINVAL, "output pointer is not 256-byte aligned");
   std::lock_guard<std::mutex> g(c->mu);
-  const Sizes z = plan_sizes(f, ctx_tile(c, f->order, f->precision));
+  Sizes z = plan_sizes(f, ctx_tile(c, f->order, f->precision));
+  // (workgroup tiles on the streaming path: the general pipeline where only
+  // its scratch fits)
+  if (wide_order(f->order, f->precision) && ((z.scratch_bytes + 255) & ~size_t(255)) + 256 > scratch_cap)
+    z = plan_sizes(f, 0, true, false);
   const int nc = f->ncomp;
   const size_t hb = isr_blob::HDR + isr_blob::CHDR * (size_t)nc;
   const size_t bm = (size_t)nc * f->n_elem * z.W * 8, ep = (size_t)nc * (f->n_elem + 1) * 8;
@@ -1870,7 +1906,7 @@ int run_compress_quantized(isr_ctx* c, const isr_field* f, double share, isr_blo
   double* err_dev = (double*)(scr + hist_bytes + 256);
   // orders of the streaming path: wave tiles, error terms into running sums
   // bounded as pass B's; higher orders: workgroup tiles and LDS histograms
-  const bool fast = fast_order(f->order, ISR_PREC_FP64);
+  const bool fast = f->order <= FAST_MAX_ORDER;
   if (fast) {
     j.slotsB = (long long*)(scr + hist_bytes + 512);
     fast_setup(c, j, plan_sizes(f, 0));
@@ -1982,14 +2018,10 @@ int run_compress_elemcut(isr_ctx* c, const isr_field* f, isr_blob** out, isr_sta
   const long long tiles = tiles_per_comp(f->order, E);
   auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
   const size_t o_coef = 0, o_tau = al(o_coef + (f->order == 7 ? 0 : (size_t)nc * E * n3 * 8)), o_st = al(o_tau + (size_t)nc * E * 8);
-  const size_t o_zero = al(o_st + (size_t)nc * sizeof(CompState));  // digits, error bins, look-back, ticket
+  const size_t o_zero = al(o_st + (size_t)nc * sizeof(CompState));  // digits, error bins
   const size_t o_hist = al(o_zero + elemcut_digit_bytes(nc));
-  const size_t o_lb = al(o_hist + (size_t)nc * HBINS * sizeof(HistBin));
-  const size_t o_tk = al(o_lb + (size_t)nc * tiles * 8);
-  const size_t zero_end = o_tk + 256;
-  // kept counts, their scan and the error sums of pass B (orders of the
-  // streaming path)
-  const bool fast = fast_order(f->order, ISR_PREC_FP64);
+  const size_t zero_end = al(o_hist + (size_t)nc * HBINS * sizeof(HistBin));
+  // kept counts, their scan and the error sums of pass B
   const size_t o_cnt = al(zero_end), o_chunk = al(o_cnt + (size_t)nc * E * 4);
   const size_t o_slots = al(o_chunk + (size_t)nc * ((E + SCAN_CHUNK - 1) / SCAN_CHUNK) * 8);
   const size_t scr_bytes = o_slots + (size_t)nc * FAST_GMAX * 4 * 8;
@@ -2020,8 +2052,6 @@ int run_compress_elemcut(isr_ctx* c, const isr_field* f, isr_blob** out, isr_sta
   j.tab = c->tab[f->order];
   j.st = (CompState*)(scr + o_st);
   j.histR = (HistBin*)(scr + o_hist);
-  j.lookback = (u64*)(scr + o_lb);
-  j.ticket = (u32*)(scr + o_tk);
   j.bitmap = b->bitmap();
   j.elem_ptr = b->elem_ptr();
   j.values = b->values();
@@ -2031,14 +2061,13 @@ int run_compress_elemcut(isr_ctx* c, const isr_field* f, isr_blob** out, isr_sta
   j.chunk = (u64*)(scr + o_chunk);
   j.nchunk = (E + SCAN_CHUNK - 1) / SCAN_CHUNK;
   j.slotsB = (long long*)(scr + o_slots);
-  if (fast) fast_setup(c, j, plan_sizes(f, 0));  // pass B's grid and headroom
+  fast_setup(c, j, plan_sizes(f, 0));  // pass B's grid and headroom
   double* coef = (double*)(scr + o_coef);
   const int gfwd = (int)std::min<long long>(tiles * nc, (long long)c->num_cu * 8);
   // (at N = 7 the selection transforms the elements itself)
   if (f->order != 7 && launch_pass(K_FORWARD, ISR_PREC_FP64, j, gfwd, s, coef) != hipSuccess)
     return give_up(fail(ISR_EDEVICE, "forward transform failed: %s", hipGetErrorString(hipGetLastError())));
   const int gsel = (int)std::max<long long>(1, std::min<long long>((E * nc + 3) / 4, (long long)c->num_cu * 8));
-  const int g3 = (int)std::min<long long>(tiles * nc, (long long)c->num_cu * resident_blocks(K_PASS3, ISR_PREC_FP64, f->order));
   double scale[ISR_MAX_COMP];
   for (int k = 0; k < ISR_MAX_COMP; ++k) scale[k] = 1.0;
   CompState hs[ISR_MAX_COMP];
@@ -2053,9 +2082,8 @@ int run_compress_elemcut(isr_ctx* c, const isr_field* f, isr_blob** out, isr_sta
     if (hipMemcpyAsync(j.st, hs, nc * sizeof(CompState), hipMemcpyHostToDevice, s) != hipSuccess ||
         launch_zero(scr + o_zero, zero_end - o_zero, s) != hipSuccess ||
         launch_elemcut(j, coef, (double*)(scr + o_tau), (u64*)(scr + o_zero), scale, gsel, s) != hipSuccess ||
-        (fast ? launch_scan(j, s) != hipSuccess || launch_fast(F_PASSB, ISR_PREC_FP64, j, j.gB, s) != hipSuccess ||
-                    launch_fast_tail(F_PASSB, j, s) != hipSuccess
-              : launch_pass(K_PASS3, ISR_PREC_FP64, j, g3, s) != hipSuccess || launch_finalize(j, s) != hipSuccess) ||
+        launch_scan(j, s) != hipSuccess || launch_fast(F_PASSB, ISR_PREC_FP64, j, j.gB, s) != hipSuccess ||
+        launch_fast_tail(F_PASSB, j, s) != hipSuccess ||
         hipMemcpyAsync(hs, j.st, nc * sizeof(CompState), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
       return give_up(fail(ISR_EDEVICE, "per-element cut failed: %s", hipGetErrorString(hipGetLastError())));

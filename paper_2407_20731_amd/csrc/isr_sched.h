@@ -40,7 +40,8 @@ struct Sizes {
 // first-attempt capacity of an eighth of the values (at least 2^20), which the
 // sampled window rarely exceeds; an overflow sets ST_LIST and the request is
 // rerun with full lists.
-Sizes plan_sizes(const isr_field* f, int tile, bool full_lists = true);
+// stream = false: without the streaming path's scratch (the general pipeline)
+Sizes plan_sizes(const isr_field* f, int tile, bool full_lists = true, bool stream = true);
 int ctx_tile(const isr_ctx* c, int order, int precision);
 
 int enqueue_pipeline(isr_ctx* c, const Job& j, const Sizes& z, hipStream_t s, hipEvent_t* ev, bool fast);

@@ -225,6 +225,7 @@ hipError_t launch_fast(int kind, int precision, const Job& j, int gx, hipStream_
     if (precision == ISR_PREC_BF16) return launch_dense_bf16(kind, j, gx, s);
     return hipErrorInvalidValue;
   }
+  if (wide_order(j.order, precision)) return launch_fast_wide(kind, j, gx, s);
   if (precision == ISR_PREC_FP64) return launch_fast_fp64(kind, j, gx, s);
   if (precision == ISR_PREC_FP32) return launch_fast_fp32(kind, j, gx, s);
   if (precision == ISR_PREC_BF16) return launch_fast_bf16(kind, j, gx, s);
@@ -243,7 +244,9 @@ int resident_fast(int kind, int precision, int order, int tile) {
   }
   int& c = cache[kind][precision][order];
   if (c == 0) {
-    if (precision == ISR_PREC_FP64)
+    if (wide_order(order, precision))
+      c = resident_fast_wide(kind, order);
+    else if (precision == ISR_PREC_FP64)
       c = resident_fast_fp64(kind, order);
     else if (precision == ISR_PREC_FP32)
       c = resident_fast_fp32(kind, order);

@@ -1,0 +1,46 @@
+"""FP64 streaming passes of orders 8..15: one element, ragged last tiles, several
+tiles a workgroup, weights, fields with wide-spread values and exact zeros,
+everything kept and everything dropped; bit for bit against the oracle, and the
+reconstruction against the one whose error was measured."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from paper_2407_20731_amd import isr
+
+pytestmark = pytest.mark.gpu
+
+
+def _field(order, n_elem, kind):
+    if kind == "smooth":
+        return synth.field(n_elem, order, ncomp=2)
+    n = order + 1
+    rng = np.random.default_rng(31 * order + n_elem)
+    shape = (2, n_elem, n, n, n)
+    u = rng.standard_normal(shape) * 2.0 ** rng.integers(-160, 1, size=shape)
+    u[rng.random(shape) < 0.3] = 0.0
+    return u
+
+
+@pytest.mark.parametrize("order,n_elem,jac", [
+    (8, 1, False), (8, 2, True), (8, 31, False), (9, 3, True), (9, 40, False), (10, 5, True), (11, 1, True),
+    (11, 7, False), (12, 4, True), (13, 3, False), (14, 6, True), (15, 1, False), (15, 5, True), (9, 1100, True)])
+def test_wide_tiles(order, n_elem, jac):
+    J = np.linspace(0.25, 8.0, n_elem) if jac else None
+    for kind in ("smooth", "spread") if n_elem < 1000 else ("smooth",):
+        u = np.ascontiguousarray(_field(order, n_elem, kind))
+        for tol in (-1.0, 1e-3, 0.9999999) if n_elem < 1000 else (1e-3,):
+            ref = oracle.compress(u, order, tol, jac=J, keep_arrays=True)
+            with isr.Context(device=0) as ctx:
+                blob = ctx.compress(torch.from_numpy(u).cuda(), order, tol, "fp64",
+                                    jac=torch.from_numpy(J).cuda() if jac else None)
+                s, arr = blob.stats, blob.arrays()
+                for c, r in enumerate(ref.comps):
+                    got = (s["norm2"][c], s["tau"][c], s["dropped"][c], s["err2"][c], s["kept"][c])
+                    assert got == (r.U2, r.tau, r.dropped, r.err2, r.kept), (kind, tol, c)
+                    assert np.array_equal(arr.bitmap[c], r.bitmap), (kind, tol, c)
+                    assert np.array_equal(np.asarray(arr.values[c]), r.values), (kind, tol, c)
+                blob.free()
