@@ -12,8 +12,8 @@
 // are in flight while a tile is transformed.  What bounds it: FP64 VALU issue
 // (6 n multiplies and additions a value and transform) and the LDS round trips
 // between its barriers.
-// N = 9, 4,097 elements, 3 components: pass A 185 + 59 (second pass) -> 89 us, pass B 577 -> 137 us,
-// the whole request with its decompression 1,006 -> 422 us.
+// N = 9, 4,097 elements, 3 components: pass A 185 + 59 (second pass) -> 87 us,
+// pass B 577 -> 124 us, the request with its decompression 1,006 -> 384 us.
 //
 // Rows (n values along i) are n | 1 doubles apart in LDS: for even n the
 // pencils along i would otherwise meet in few banks (n = 16: two).  Field
@@ -121,6 +121,15 @@ struct EngG {
   }
 };
 
+// Workgroups per CU the passes are compiled for: three up to order 12 (168
+// VGPRs; at N = 10 and 12 pass B spills about 30 of them and still takes 116 and
+// 160 us, against 117..121 and 163..168 us with two), two above (75 spills and
+// more with three).
+template <int N>
+constexpr int wide_minb() {
+  return N <= 12 ? 3 : 2;
+}
+
 // this thread's weights: w3 of its dense values, g3 of its pencil's coefficients
 template <class G>
 DEV void g_weights(const DevTables& t, double (&w3)[G::PER], double (&g3)[G::n], int tid, int a, int b) {
@@ -224,7 +233,7 @@ struct PassALdsG {
 };
 
 template <int N>
-__global__ __launch_bounds__(256, 2) void k_passAG(Job j) {
+__global__ __launch_bounds__(256, wide_minb<N>()) void k_passAG(Job j) {
   typedef EngG<N> G;
   constexpr int n = G::n, n2 = G::n2, n3 = G::n3, EPI = G::EPI, PER = G::PER;
   __shared__ PassALdsG<N> L;
@@ -261,18 +270,20 @@ __global__ __launch_bounds__(256, 2) void k_passAG(Job j) {
     const long long e0 = t * EPI;
     const int ne = (int)((E - e0) < EPI ? (E - e0) : EPI);
     const bool act = tid < EPI * n2 && el < ne;
+    int dt = tid;  // (per-tile copy: the indexes made from it are not kept across tiles)
+    asm volatile("" : "+v"(dt));
     // norm terms of the dense values
     bool odd = false;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      const int idx = tid + 256 * k;
+      const int idx = dt + 256 * k;
       const bool v = idx < ne * n3;
       const double x = v ? jw(j.jac, e0 + idx / n3, w3[k]) * (u[k] * u[k]) : 0.0;
       if (xrun_left(rn, RN, x) && v) slow_bin(gN, x);
       __builtin_amdgcn_sched_barrier(0);
     }
     pin(rn);
-    G::store(L.w, u, tid);
+    G::store(L.w, u, dt);
     if (t + gridDim.x < tiles) fetch(t + gridDim.x);
     double c[n];
     G::forward(L.w, j.tab, el, a, b, act, c);
@@ -349,7 +360,7 @@ struct PassBLdsG {
 };
 
 template <int N>
-__global__ __launch_bounds__(256, 2) void k_passBG(Job j) {
+__global__ __launch_bounds__(256, wide_minb<N>()) void k_passBG(Job j) {
   typedef EngG<N> G;
   constexpr int n = G::n, n2 = G::n2, n3 = G::n3, EPI = G::EPI, PER = G::PER, W = G::W;
   __shared__ PassBLdsG<N> L;
@@ -385,11 +396,13 @@ __global__ __launch_bounds__(256, 2) void k_passBG(Job j) {
     const long long e0 = t * EPI;
     const int ne = (int)((E - e0) < EPI ? (E - e0) : EPI);
     const bool act = tid < EPI * n2 && el < ne;
-    double u[PER], c[n];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) u[k] = un[k];
+    // (per-tile copies: the compiler would keep every index and mask made from
+    // these in registers across tiles)
+    int ab = a * n + b, dt = tid;
+    asm volatile("" : "+v"(ab), "+v"(dt));
+    double c[n];
     __syncthreads();  // (the tile before is no longer read)
-    G::store(L.w, u, tid);
+    G::store(L.w, un, tid);
     G::forward(L.w, j.tab, el, a, b, act, c);
     if (t + gridDim.x < tiles) fetch(t + gridDim.x);
     const double je = j.jac && act ? j.jac[e0 + el] : 1.0;
@@ -401,7 +414,7 @@ __global__ __launch_bounds__(256, 2) void k_passBG(Job j) {
       const double en = (je * g3[r]) * (c[r] * c[r]);
       if (act && en >= tau) {
         keep |= 1u << r;
-        const int f = (r * n + a) * n + b;
+        const int f = r * n2 + ab;
         atomicOr((unsigned long long*)&L.bm[el * W + (f >> 6)], 1ull << (f & 63));
       }
     }
@@ -432,7 +445,7 @@ __global__ __launch_bounds__(256, 2) void k_passBG(Job j) {
 #pragma unroll
       for (int r = 0; r < n; ++r) {
         if (!((keep >> r) & 1u)) continue;
-        const int f = (r * n + a) * n + b, wi = el * W + (f >> 6);
+        const int f = r * n2 + ab, wi = el * W + (f >> 6);
         dst[L.wp[wi] + (u32)__popcll(L.bm[wi] & ((1ull << (f & 63)) - 1ull))] = c[r];
       }
     }
@@ -440,11 +453,13 @@ __global__ __launch_bounds__(256, 2) void k_passBG(Job j) {
     for (int r = 0; r < n; ++r) c[r] = (keep >> r) & 1u ? c[r] : 0.0;
     G::inverse(L.w, j.tab, el, a, b, act, c);
     if (tid < 64) L.bm[tid] = 0ull;  // (read before the inverse's first barrier, set again after the next tile's)
+    double u[PER];
+    G::load(ub + e0 * n3, ne * n3, u, tid);
     __syncthreads();
     // error terms of the dense values
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      const int idx = tid + 256 * k;
+      const int idx = dt + 256 * k;
       const bool v = idx < ne * n3;
       const double d = v ? u[k] - L.w[G::at(idx)] : 0.0;
       const double x = v ? jw(j.jac, e0 + idx / n3, w3[k]) * (d * d) : 0.0;
@@ -456,6 +471,178 @@ __global__ __launch_bounds__(256, 2) void k_passBG(Job j) {
   if (ballot(bad)) {
     if (lane == 0) atomicOr(&st->flags, ST_LIST);
   }
+  const XParm QR = xparm(again(PR.m), j.xh);
+  long long v[3];
+  xints(xrun_sums(rr, QR), QR, v);
+  block_sum_i64<3>(v, L.red, tid);
+  if (tid < 3) j.slotsB[((size_t)comp * j.gB + blockIdx.x) * 4 + tid] = L.red[0][tid];
+}
+
+// ---- reading kept values back ----------------------------------------------------
+// Kept coefficients of thread (el, a, b) of a tile whose bitmap words are in
+// L.bm, with L.wp kept values before each (wave 0 puts them there): calls
+// fn(place, r, index) for each kept one, zero for the others.  base: the place
+// of its element's first value.
+template <class G, class LDS>
+DEV void g_words(LDS& L, u64 wcur, int tid) {
+  if (tid >= 64) return;
+  const u32 pc = (u32)__popcll(wcur);
+  u32 incl = pc;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const u32 o = (u32)__shfl_up((int)incl, d);
+    incl += tid >= d ? o : 0u;
+  }
+  L.bm[tid] = wcur;
+  L.wp[tid] = incl - pc;
+}
+template <class G, class LDS, class FN>
+DEV void g_kept(double (&cm)[G::n], const LDS& L, u64 base, int el, int a, int b, bool act, FN fn) {
+  constexpr int n = G::n, W = G::W;
+  const u32 p0 = act ? L.wp[el * W] : 0u;
+#pragma unroll
+  for (int r = 0; r < n; ++r) {
+    cm[r] = 0.0;
+    const int f = (r * n + a) * n + b, wi = el * W + (f >> 6);
+    const u64 wd = act ? L.bm[wi] : 0ull;
+    if ((wd >> (f & 63)) & 1ull)
+      cm[r] = fn(base + (L.wp[wi] - p0 + (u32)__popcll(wd & ((1ull << (f & 63)) - 1ull))), r, f);
+  }
+}
+
+// ---- decompress ------------------------------------------------------------------
+// Blobs of FP64 values and quantisation codes.  A tile's words and offsets are
+// in flight while the one before is inverted; the field leaves from LDS in
+// dense order in non-temporal stores (what it replaces stored a row of n a
+// lane).  Bound by the inverse as pass B is, less its forward.  N = 9, 4,097
+// elements, 3 components, FP64: 71 -> 53 us.
+template <int N>
+struct WordLdsG {
+  double w[EngG<N>::LDSW];
+  u64 bm[64];  // the tile's bitmap words
+  u32 wp[64];  // kept values before each word
+};
+
+template <int N, bool OUT64>
+__global__ __launch_bounds__(256, 2) void k_decompG(Job j, void* out) {
+  typedef EngG<N> G;
+  constexpr int n = G::n, n2 = G::n2, n3 = G::n3, EPI = G::EPI, PER = G::PER, W = G::W;
+  typedef typename Pick<OUT64, double, float>::type ot;
+  __shared__ WordLdsG<N> L;
+  const int tid = threadIdx.x, comp = blockIdx.y;
+  const int el = tid / n2, a = (tid % n2) / n, b = tid % n;
+  const long long E = j.n_elem, tiles = (E + EPI - 1) / EPI;
+  const u64* gbm = j.bitmap + (size_t)comp * E * W;
+  const u64* eptr = j.elem_ptr + (size_t)comp * (E + 1);
+  const u64 voff = j.voff[comp];
+  const double qs = j.qstep ? j.qstep[comp] : 0.0;
+  ot* ocomp = (ot*)out + (size_t)comp * E * n3;
+  u64 wnext = 0ull, bnext = 0ull;
+  auto fetch = [&](long long tt) {
+    const long long e0 = tt * EPI;
+    const int ne = (int)((E - e0) < EPI ? (E - e0) : EPI);
+    wnext = tid < 64 && tid < ne * W ? gbm[e0 * W + tid] : 0ull;
+    bnext = el < ne ? eptr[e0 + el] : 0ull;
+  };
+  long long t = blockIdx.x;
+  if (t < tiles) fetch(t);
+  for (; t < tiles; t += gridDim.x) {
+    const long long e0 = t * EPI;
+    const int ne = (int)((E - e0) < EPI ? (E - e0) : EPI);
+    const bool act = tid < EPI * n2 && el < ne;
+    g_words<G>(L, wnext, tid);
+    const u64 base = voff + bnext;
+    if (t + gridDim.x < tiles) fetch(t + gridDim.x);
+    __syncthreads();
+    double cm[n];
+    g_kept<G>(cm, L, base, el, a, b, act, [&](u64 pos, int, int f) -> double {
+      if (j.vbytes == 8) return ((const double*)j.values)[pos];
+      // quantisation codes: the value is (code * step) / sqrt(g3)
+      return ((double)((const float*)j.values)[pos] * qs) / __builtin_sqrt(j.tab.g3[f]);
+    });
+    G::inverse(L.w, j.tab, el, a, b, act, cm);
+    __syncthreads();
+    ot* o = ocomp + e0 * n3;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int idx = tid + 256 * k;
+      if (idx < ne * n3) __builtin_nontemporal_store((ot)L.w[G::at(idx)], &o[idx]);
+    }
+  }
+}
+
+// ---- quantised variant ------------------------------------------------------------
+// The codes of the kept values and the error they leave, as k_quantW
+// (isr_engine.cuh) does for the smaller orders.  N = 9, 3,333 elements, 3
+// components: 266 -> 92 us.
+template <int N>
+struct QuantLdsG : WordLdsG<N> {
+  long long red[4][8];
+};
+
+template <int N>
+__global__ __launch_bounds__(256, 2) void k_quantG(Job j) {
+  typedef EngG<N> G;
+  constexpr int n = G::n, n2 = G::n2, n3 = G::n3, EPI = G::EPI, PER = G::PER, W = G::W;
+  __shared__ QuantLdsG<N> L;
+  const int tid = threadIdx.x, comp = blockIdx.y;
+  const int el = tid / n2, a = (tid % n2) / n, b = tid % n;
+  const long long E = j.n_elem, tiles = (E + EPI - 1) / EPI;
+  const u64* gbm = j.bitmap + (size_t)comp * E * W;
+  const u64* eptr = j.elem_ptr + (size_t)comp * (E + 1);
+  const u64 voff = j.voff[comp];
+  const double step = j.qstep[comp];
+  const double* ub = j.u + (size_t)comp * j.comp_stride;
+  const XParm PR = xparm(j.qxm[comp], j.xh);
+  const XRange RR = xrange(PR);
+  XRun rr = xrun(PR);
+  HistBin* gR = j.histR + (size_t)comp * HBINS;
+  double w3[PER], sq[n];
+  g_weights<G>(j.tab, w3, sq, tid, a, b);
+#pragma unroll
+  for (int r = 0; r < n; ++r) sq[r] = __builtin_sqrt(sq[r]);
+  bool big = false;
+  u64 wnext = 0ull, bnext = 0ull;
+  auto fetch = [&](long long tt) {
+    const long long e0 = tt * EPI;
+    const int ne = (int)((E - e0) < EPI ? (E - e0) : EPI);
+    wnext = tid < 64 && tid < ne * W ? gbm[e0 * W + tid] : 0ull;
+    bnext = el < ne ? eptr[e0 + el] : 0ull;
+  };
+  long long t = blockIdx.x;
+  if (t < tiles) fetch(t);
+  for (; t < tiles; t += gridDim.x) {
+    const long long e0 = t * EPI;
+    const int ne = (int)((E - e0) < EPI ? (E - e0) : EPI);
+    const bool act = tid < EPI * n2 && el < ne;
+    double u[PER];
+    G::load(ub + e0 * n3, ne * n3, u, tid);
+    g_words<G>(L, wnext, tid);
+    const u64 base = voff + bnext;
+    if (t + gridDim.x < tiles) fetch(t + gridDim.x);
+    __syncthreads();
+    double cm[n];
+    g_kept<G>(cm, L, base, el, a, b, act, [&](u64 pos, int r, int) -> double {
+      const double c = ((const double*)j.values)[pos];
+      const double q = __builtin_rint((c * sq[r]) / step);
+      if (!(__builtin_fabs(q) < 16777216.0)) big = true;
+      j.qvals[pos] = (float)q;
+      return (q * step) / sq[r];
+    });
+    G::inverse(L.w, j.tab, el, a, b, act, cm);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int idx = tid + 256 * k;
+      const bool v = idx < ne * n3;
+      const double d = v ? u[k] - L.w[G::at(idx)] : 0.0;
+      const double x = w3[k] * (d * d);
+      if (xrun_left(rr, RR, x) && v) slow_bin(gR, x);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    pin(rr);
+  }
+  if (big) atomicOr(&j.ticket[1], 1u);
   const XParm QR = xparm(again(PR.m), j.xh);
   long long v[3];
   xints(xrun_sums(rr, QR), QR, v);
@@ -479,6 +666,40 @@ inline hipError_t launch_fast_g(int kind, const Job& j, int gx, hipStream_t s) {
       hipLaunchKernelGGL((k_passBG<NN>), grid, blk, 0, s, j);    \
     else                                                         \
       return hipErrorInvalidValue;                               \
+    break;
+    ISR_FAST_ORDERS_G(CASE)
+#undef CASE
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+inline hipError_t launch_decomp_g(const Job& j, int gx, int cus, hipStream_t s, void* out, int out_fp64) {
+  switch (j.order) {
+#define CASE(NN)                                                                                      \
+  case NN: {                                                                                          \
+    static const int nb = resident_wgs((const void*)k_decompG<NN, true>),                             \
+                     nb32 = resident_wgs((const void*)k_decompG<NN, false>);                          \
+    if (out_fp64)                                                                                     \
+      hipLaunchKernelGGL((k_decompG<NN, true>), decomp_grid(j, gx, nb, cus), dim3(256), 0, s, j, out); \
+    else                                                                                              \
+      hipLaunchKernelGGL((k_decompG<NN, false>), decomp_grid(j, gx, nb32, cus), dim3(256), 0, s, j, out); \
+    break;                                                                                            \
+  }
+    ISR_FAST_ORDERS_G(CASE)
+#undef CASE
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+inline hipError_t launch_quant_g(const Job& j, hipStream_t s) {
+  switch (j.order) {
+#define CASE(NN)                                                                  \
+  case NN:                                                                        \
+    hipLaunchKernelGGL((k_quantG<NN>), dim3(j.gB, j.ncomp), dim3(256), 0, s, j);  \
     break;
     ISR_FAST_ORDERS_G(CASE)
 #undef CASE

@@ -178,7 +178,7 @@ int batch_resident_fp32(size_t lds);
 int batch_resident_bf16(size_t lds);
 
 // Streaming passes (isr_passes.cuh), one instantiation file per precision.
-enum PassKind { K_PASS1 = 0, K_PASS2 = 1, K_PASS3 = 2, K_DECOMP = 3, K_FORWARD = 4, K_QUANT = 5 };
+enum PassKind { K_PASS1 = 0, K_PASS2 = 1, K_PASS3 = 2, K_DECOMP = 3, K_FORWARD = 4 };
 int tiles_per_comp(int order, long long n_elem);
 int words_per_elem(int order);
 // grid: x extent (pass1/pass2 also get y = ncomp); extra: output pointer of
@@ -197,9 +197,6 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 // copy of the per-component states into mapped pinned host memory (host_dst
 // from hipHostMalloc with hipHostMallocMapped), by a kernel
 hipError_t launch_state_out(const CompState* src, CompState* host_dst, int ncomp, hipStream_t s);
-// correctly rounded exact totals of the error histograms j.histR, per
-// component, into err2_out[ncomp] (device)
-hipError_t launch_err_total(const Job& j, double* err2_out, hipStream_t s);
 // quantisation pass on wave tiles (orders 1..FAST_MAX_ORDER; j.gB workgroups
 // per component) and its totals: the per-workgroup sums j.slotsB (headroom
 // j.xh, bounds j.qxm) added to j.histR first
@@ -233,6 +230,8 @@ inline bool fast_order(int order, int precision) {
 inline bool wide_order(int order, int precision) { return precision == 0 && order > FAST_MAX_ORDER; }
 hipError_t launch_fast_wide(int kind, const Job& j, int grid_x, hipStream_t s);
 int resident_fast_wide(int kind, int order);
+hipError_t launch_decomp_wide(const Job& j, int gx, int cus, hipStream_t s, void* out, int out_fp64);
+hipError_t launch_quant_wide(const Job& j, hipStream_t s);
 // Tile shapes compiled for the dense-tile engine (isr_engine_d.cuh, FP32 and
 // BF16): X(order, elements per wavefront tile).
 #define ISR_DENSE_SHAPES(X)                                                                               \

@@ -1490,16 +1490,16 @@ int isr_decompress(isr_ctx* c, const isr_blob* b, void* d_out, int32_t out_prec,
     j.tile = b->tile;
     HIPCHK(bf ? launch_decomp_dense_bf16(j, gx, cus, s, d_out, ofp64)
               : launch_decomp_dense_fp32(j, gx, cus, s, d_out, ofp64));
-  } else if (b->order <= FAST_MAX_ORDER && prec == ISR_PREC_FP64) {
-    // every FP64 blob of these orders: the fixed-order inverse is the same in
-    // every kernel
-    HIPCHK(launch_decomp_wave_fp64(j, gx, cus, s, d_out, ofp64));
+  } else if (prec == ISR_PREC_FP64) {
+    // every FP64 blob: the fixed-order inverse is the same in every kernel
+    const long long wt = std::min<long long>(tiles_per_comp(b->order, b->n_elem), 1 << 24);
+    HIPCHK(wide_order(b->order, prec) ? launch_decomp_wide(j, (int)wt, cus, s, d_out, ofp64)
+                                      : launch_decomp_wave_fp64(j, gx, cus, s, d_out, ofp64));
   } else if (b->engine == ENG_WAVE) {
     HIPCHK(bf ? launch_decomp_wave_bf16(j, gx, cus, s, d_out, ofp64)
               : launch_decomp_wave_fp32(j, gx, cus, s, d_out, ofp64));
   } else {
-    // workgroup tiles: the FP64 fixed-order inverse, or the general passes'
-    // MFMA inverse
+    // workgroup tiles: the general passes' MFMA inverse
     const long long total = (long long)tiles_per_comp(b->order, b->n_elem) * b->ncomp;
     HIPCHK(launch_pass(K_DECOMP, prec, j, (int)std::min<long long>(total, (long long)cus * 8), s, d_out, ofp64));
   }
@@ -1904,28 +1904,22 @@ int run_compress_quantized(isr_ctx* c, const isr_field* f, double share, isr_blo
   j.histR = (HistBin*)scr;
   j.ticket = (u32*)(scr + hist_bytes);
   double* err_dev = (double*)(scr + hist_bytes + 256);
-  // orders of the streaming path: wave tiles, error terms into running sums
-  // bounded as pass B's; higher orders: workgroup tiles and LDS histograms
-  const bool fast = f->order <= FAST_MAX_ORDER;
-  if (fast) {
-    j.slotsB = (long long*)(scr + hist_bytes + 512);
-    fast_setup(c, j, plan_sizes(f, 0));
-    for (int k = 0; k < nc; ++k) {
-      const double U2 = b->comp[k].U2;
-      const int m = Bf[k] > 0.0 ? std::ilogb(Bf[k]) + 6 : (U2 > 0.0 ? std::ilogb(U2) - 80 : -876);
-      j.qxm[k] = std::max(-876, std::min(800, m));  // (the sums' own limits)
-    }
+  // error terms into running sums bounded as pass B's
+  j.slotsB = (long long*)(scr + hist_bytes + 512);
+  fast_setup(c, j, plan_sizes(f, 0));
+  for (int k = 0; k < nc; ++k) {
+    const double U2 = b->comp[k].U2;
+    const int m = Bf[k] > 0.0 ? std::ilogb(Bf[k]) + 6 : (U2 > 0.0 ? std::ilogb(U2) - 80 : -876);
+    j.qxm[k] = std::max(-876, std::min(800, m));  // (the sums' own limits)
   }
-  const long long total = (long long)tiles_per_comp(f->order, f->n_elem) * nc;
-  const int grid = (int)std::min<long long>(total, (long long)c->num_cu * resident_blocks(K_PASS3, ISR_PREC_FP64, f->order));
   int iters = 0;
   for (;;) {
     uint32_t over = 0;
     rc = ISR_OK;
     if (launch_zero(scr, hist_bytes + 256, s) != hipSuccess ||
         hipMemcpyAsync((void*)j.qstep, delta, 8 * nc, hipMemcpyHostToDevice, s) != hipSuccess ||
-        (fast ? launch_quant_wave(j, s) != hipSuccess || launch_quant_total(j, err_dev, s) != hipSuccess
-              : launch_pass(K_QUANT, ISR_PREC_FP64, j, grid, s) != hipSuccess || launch_err_total(j, err_dev, s) != hipSuccess) ||
+        (wide_order(f->order, ISR_PREC_FP64) ? launch_quant_wide(j, s) : launch_quant_wave(j, s)) != hipSuccess ||
+        launch_quant_total(j, err_dev, s) != hipSuccess ||
         hipMemcpyAsync(err2, err_dev, 8 * nc, hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipMemcpyAsync(&over, j.ticket + 1, 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)

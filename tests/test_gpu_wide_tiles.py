@@ -43,4 +43,9 @@ def test_wide_tiles(order, n_elem, jac):
                     assert got == (r.U2, r.tau, r.dropped, r.err2, r.kept), (kind, tol, c)
                     assert np.array_equal(arr.bitmap[c], r.bitmap), (kind, tol, c)
                     assert np.array_equal(np.asarray(arr.values[c]), r.values), (kind, tol, c)
+                for dtype, np_t in ((torch.float64, np.float64), (torch.float32, np.float32)):
+                    out = ctx.decompress(blob, dtype=dtype)
+                    torch.cuda.synchronize()
+                    for c, r in enumerate(ref.comps):
+                        assert np.array_equal(out[c].cpu().numpy(), r.recon.astype(np_t)), (kind, tol, c)
                 blob.free()
