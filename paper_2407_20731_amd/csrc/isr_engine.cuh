@@ -354,7 +354,6 @@ template <int N, int PREC>
 struct SampleLds {
   typename Eng<N, PREC>::wt buf[4][Eng<N, PREC>::LDSW];
   TabLds tab;
-  u32 hc[SBINS];
   float hs[SBINS];  // sums of energy / 2^(bin exponent), each term in [1, 2)
   double u2[4];
   int maxe;
@@ -367,10 +366,7 @@ DEV void sample_body(const Job& j, int comp, int vb, int nvb, SampleLds<N, PREC>
   constexpr int n3 = G::n3, NS = G::NS, EPW = G::EPW;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   CompState* st = j.st + comp;
-  for (int k = tid; k < SBINS; k += 256) {
-    L.hc[k] = 0u;
-    L.hs[k] = 0.0f;
-  }
+  for (int k = tid; k < SBINS; k += 256) L.hs[k] = 0.0f;
   if (tid == 0) L.maxe = 0;
   typename G::Mats mt;
   G::init(mt, j.tab, lane);
@@ -389,27 +385,32 @@ DEV void sample_body(const Job& j, int comp, int vb, int nvb, SampleLds<N, PREC>
     const long long t = k * ss;
     const long long e0 = t * EPW;
     const int ne = (int)((E - e0) < EPW ? (E - e0) : EPW);
-    double u[NS], c[NS];
+    double u[NS], c[NS], jq[G::JS];
     G::load(ub + e0 * n3, ne, vec, u, lane);
 #pragma unroll
+    for (int s = 0; s < G::JS; ++s) jq[s] = 1.0;  // (1.0 * w is w: no branch per value)
+    if (j.jac) G::load_jac(j.jac + e0, ne, jq, lane);
+#pragma unroll
     for (int s = 0; s < NS; ++s) {
-      if (!G::valid(s, lane, ne)) continue;
-      const double x = jw(j.jac, e0 + G::elem(s, lane), L.tab.w3[s][lane]) * (u[s] * u[s]);
+      const double x = G::valid(s, lane, ne) ? (jq[s % G::JS] * L.tab.w3[s][lane]) * (u[s] * u[s]) : 0.0;
       u2 += x;
       const int ex = bits_exp(dbits(x));
       maxe = ex > maxe ? ex : maxe;
     }
     G::forward(u, c, L.buf[wv], mt, j.tab, lane);
+    // energies first, then their atomics: none of these waits for the next
+    // (rounded sums only place the window)
+    int eb[NS];
+    float em[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      const bool v = G::valid(s, lane, ne);
-      const double en = v ? jw(j.jac, e0 + G::elem(s, lane), L.tab.g3[s][lane]) * (c[s] * c[s]) : 0.0;
-      const int b = bits_exp(dbits(en));
-      if (v && b < HBINS - 1) {  // rounded sums only place the window
-        atomicAdd(&L.hc[b], 1u);
-        atomicAdd(&L.hs[b], (float)ldexp(en, 1023 - b));
-      }
+      const double en = G::valid(s, lane, ne) ? (jq[s % G::JS] * L.tab.g3[s][lane]) * (c[s] * c[s]) : 0.0;
+      eb[s] = bits_exp(dbits(en));
+      em[s] = eb[s] < HBINS - 1 ? (float)ldexp(en, 1023 - eb[s]) : 0.0f;
     }
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (em[s] != 0.0f) atomicAdd(&L.hs[eb[s]], em[s]);
   }
   u2 = wave_sum_f64(u2);
   for (int m = 32; m > 0; m >>= 1) {
@@ -423,7 +424,7 @@ DEV void sample_body(const Job& j, int comp, int vb, int nvb, SampleLds<N, PREC>
   __syncthreads();
   HistBin* H = j.histEs + (size_t)comp * HBINS;
   for (int k = tid; k < SBINS; k += 256) {
-    if (L.hc[k]) {
+    if (L.hs[k] != 0.0f) {
       atomicAdd((double*)&H[k].lo, ldexp((double)L.hs[k], k - 1023));
     }
   }

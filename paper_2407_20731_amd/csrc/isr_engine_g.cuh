@@ -146,7 +146,6 @@ DEV void g_weights(const DevTables& t, double (&w3)[G::PER], double (&g3)[G::n],
 template <int N>
 struct SampleLdsG {
   double w[EngG<N>::LDSW];
-  u32 hc[SBINS];
   float hs[SBINS];  // sums of energy / 2^(bin exponent), each term in [1, 2)
   double u2[4];
   int maxe;
@@ -160,10 +159,7 @@ __global__ __launch_bounds__(256, 2) void k_sampleG(Job j) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, comp = blockIdx.y;
   const int el = tid / n2, a = (tid % n2) / n, b = tid % n;
   CompState* st = j.st + comp;
-  for (int k = tid; k < SBINS; k += 256) {
-    L.hc[k] = 0u;
-    L.hs[k] = 0.0f;
-  }
+  for (int k = tid; k < SBINS; k += 256) L.hs[k] = 0.0f;
   if (tid == 0) L.maxe = 0;
   const long long E = j.n_elem, tiles = (E + EPI - 1) / EPI;
   const long long ss = j.sample_stride > 0 ? j.sample_stride : 1, stiles = (tiles + ss - 1) / ss;
@@ -190,17 +186,20 @@ __global__ __launch_bounds__(256, 2) void k_sampleG(Job j) {
     __syncthreads();
     G::store(L.w, u, tid);
     G::forward(L.w, j.tab, el, a, b, act, c);
-    if (act) {
+    const double je = j.jac && act ? j.jac[e0 + el] : 1.0;
+    // energies first, then their atomics: none of these waits for the next
+    // (rounded sums only place the window)
+    int eb[n];
+    float em[n];
 #pragma unroll
-      for (int r = 0; r < n; ++r) {
-        const double en = jw(j.jac, e0 + el, g3[r]) * (c[r] * c[r]);
-        const int bn = bits_exp(dbits(en));
-        if (bn < HBINS - 1) {  // rounded sums only place the window
-          atomicAdd(&L.hc[bn], 1u);
-          atomicAdd(&L.hs[bn], (float)ldexp(en, 1023 - bn));
-        }
-      }
+    for (int r = 0; r < n; ++r) {
+      const double en = act ? (je * g3[r]) * (c[r] * c[r]) : 0.0;
+      eb[r] = bits_exp(dbits(en));
+      em[r] = eb[r] < HBINS - 1 ? (float)ldexp(en, 1023 - eb[r]) : 0.0f;
     }
+#pragma unroll
+    for (int r = 0; r < n; ++r)
+      if (em[r] != 0.0f) atomicAdd(&L.hs[eb[r]], em[r]);
   }
   u2 = wave_sum_f64(u2);
   for (int m = 32; m > 0; m >>= 1) {
@@ -215,7 +214,7 @@ __global__ __launch_bounds__(256, 2) void k_sampleG(Job j) {
   __syncthreads();
   HistBin* H = j.histEs + (size_t)comp * HBINS;
   for (int k = tid; k < SBINS; k += 256)
-    if (L.hc[k]) atomicAdd((double*)&H[k].lo, ldexp((double)L.hs[k], k - 1023));
+    if (L.hs[k] != 0.0f) atomicAdd((double*)&H[k].lo, ldexp((double)L.hs[k], k - 1023));
   if (tid == 0) {
     atomicAdd(&st->samp_u2, L.u2[0] + L.u2[1] + L.u2[2] + L.u2[3]);
     atomicMax(&st->samp_maxe, L.maxe);
