@@ -405,11 +405,17 @@ static int enqueue_fast(isr_ctx* c, const Job& j0, const Sizes& z, hipStream_t s
   rec(0);
   HIPCHK(launch_fast(F_PASSA, prec, j, j.gA, s));
   rec(1);
-  HIPCHK(launch_gather(j, g.gl, s));
-  rec(2);
-  rec(3);
-  HIPCHK(launch_refsel(j, g.rgx, s));
-  HIPCHK(launch_count(j, g.gl, s));
+  if (chain_small(z.nv, j.n_elem)) {
+    HIPCHK(launch_chain(j, s));
+    rec(2);
+    rec(3);
+  } else {
+    HIPCHK(launch_gather(j, g.gl, s));
+    rec(2);
+    rec(3);
+    HIPCHK(launch_refsel(j, g.rgx, s));
+    HIPCHK(launch_count(j, g.gl, s));
+  }
   rec(4);
   HIPCHK(launch_fast(F_PASSB, prec, j, j.gB, s));
   rec(5);

@@ -129,6 +129,96 @@ __global__ __launch_bounds__(256) void k_select_rest(Job j) {
   }
 }
 
+// From the gather to the offsets of pass B in one workgroup per component, for
+// small components (chain_small): each of the nine launches this replaces costs
+// 4 to 10 us there and has next to nothing to do.  Bound by its chain of
+// barriers and of loads that wait for each other: 37 us at 64 elements, N = 7, 3
+// components, where the nine took 57.
+struct ChainLds {
+  union {
+    GatherLds G;
+    RefselLds R;
+    struct {
+      u32 cnt[SCAN_CHUNK];
+      u64 part[256];
+    } C;
+  } U;
+};
+
+DEV void chain_step() {  // what was written before is seen after
+  __syncthreads();
+  __threadfence();
+  __syncthreads();
+}
+
+// Kept counts and offsets of at most SCAN_CHUNK elements: pass A's counts plus
+// the window's entries at or above tau, counted in LDS.
+DEV void chain_offsets(const Job& j, int comp, u32* cnt, u64* part) {
+  const int tid = threadIdx.x;
+  CompState* st = j.st + comp;
+  if (st->flags & ST_MISS) return;
+  const int E = (int)j.n_elem;
+  for (int e = tid; e < SCAN_CHUNK; e += 256) cnt[e] = e < E ? j.cnt[(size_t)comp * E + e] : 0u;
+  __syncthreads();
+  const u64 tk = dbits(st->tau);
+  const u64* list = list_ptr(j, comp, 0);
+  const u32* lidx = j.lidx + (size_t)comp * j.list_cap;
+  const u64 nl = st->list_count[0] < j.list_cap ? st->list_count[0] : j.list_cap;
+  constexpr int U = 8;
+  for (u64 i0 = tid; i0 < nl; i0 += U * 256) {
+    u64 keys[U];
+    u32 idx[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const u64 i = i0 + u * 256;
+      keys[u] = i < nl ? list[i] : 0ull;
+      idx[u] = i < nl ? lidx[i] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * 256 < nl && keys[u] >= tk) atomicAdd(&cnt[idx[u]], 1u);
+  }
+  __syncthreads();
+  u32 v[4];
+  u64 sum = 0, tot;
+  for (int k = 0; k < 4; ++k) {
+    v[k] = cnt[4 * tid + k];
+    sum += v[k];
+  }
+  u64 run = block_excl_scan(sum, part, tid, &tot);
+  u64* eptr = j.elem_ptr + (size_t)comp * (E + 1);
+  for (int k = 0; k < 4; ++k) {
+    if (4 * tid + k < E) eptr[4 * tid + k] = run;
+    run += v[k];
+  }
+  if (tid == 0) {
+    eptr[E] = tot;
+    if (tot != st->kept) atomicOr(&st->flags, ST_LIST);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_chain(Job j) {
+  __shared__ ChainLds X;
+  const int comp = blockIdx.x;
+  gather_body(j, comp, 0, 1, X.U.G, false);
+  chain_step();
+  gather_tail(j, comp);
+  for (int L = 2; L <= NLEV; ++L) {
+    chain_step();
+    if (j.st[comp].resolved) break;
+    refine_body(j, comp, L, X.U.R.U.h, 0, 1);
+    chain_step();
+    select_body(j, comp, L, X.U.R.U.S);
+  }
+  chain_step();
+  chain_offsets(j, comp, X.U.C.cnt, X.U.C.part);
+}
+
+hipError_t launch_chain(const Job& j, hipStream_t s) {
+  hipLaunchKernelGGL(k_chain, dim3(j.ncomp), dim3(256), 0, s, j);
+  return hipGetLastError();
+}
+
 // the refinement levels 2..NLEV: levels 2 and 3 (over list 0) as refinement
 // kernels over the whole grid, the selections of level 2 and of the rest one
 // workgroup per component
