@@ -231,6 +231,12 @@ def parse_blob(buf: bytes) -> BlobArrays:
                       values)
 
 
+_new_bytes = C.pythonapi.PyBytes_FromStringAndSize
+_new_bytes.argtypes, _new_bytes.restype = [C.c_char_p, C.c_ssize_t], C.py_object
+_bytes_ptr = C.pythonapi.PyBytes_AsString
+_bytes_ptr.argtypes, _bytes_ptr.restype = [C.py_object], C.c_void_p
+
+
 class Blob:
     """A compressed snapshot held in device memory by the library."""
 
@@ -258,10 +264,11 @@ class Blob:
         return n.value
 
     def to_bytes(self) -> bytes:
+        # straight into the bytes object (no zeroed buffer, no copy of it)
         n = self.nbytes()
-        buf = C.create_string_buffer(n)
-        _check(load_library().isr_blob_to_host(self.handle, buf, n), "isr_blob_to_host")
-        return buf.raw
+        out = _new_bytes(None, n)
+        _check(load_library().isr_blob_to_host(self.handle, _bytes_ptr(out), n), "isr_blob_to_host")
+        return out
 
     def arrays(self) -> BlobArrays:
         return parse_blob(self.to_bytes())
