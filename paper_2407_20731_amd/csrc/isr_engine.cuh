@@ -1134,10 +1134,10 @@ __global__ __launch_bounds__(256, 4) void k_decompW(Job j, void* out) {
 // place; the terms w3 (u - u~)^2 of the dequantised (q step) / sqrt(g3) go into
 // the exact error; a code of magnitude 2^24 or more sets j.ticket[1].  Unit
 // Jacobians.  One tile per wavefront: the next tile's field, words and offset
-// in flight, the error terms into running exact sums
-// instead of LDS histogram atomics.  The per-workgroup sums go to j.slotsB;
-// j.qxm: log2 of the bound on the error terms per component.  10,007 elements,
-// N = 7, 3 components: 218 -> 83 us.
+// in flight, the error terms into running exact sums instead of LDS histogram
+// atomics.  The per-workgroup sums go to j.slotsB; j.qxm: log2 of the bound on
+// the error terms per component.  10,007 elements, N = 7, 3 components: 218 ->
+// 83 us.
 template <int N>
 struct QuantWLds {
   typedef Eng<N, P_FP64> G;

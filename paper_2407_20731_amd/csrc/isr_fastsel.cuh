@@ -129,7 +129,10 @@ struct GatherLds {
 DEV void gather_tail(const Job& j, int comp) {
   const int tid = threadIdx.x;
   CompState* st = j.st + comp;
-  if (st->flags & ST_MISS) return;
+  // (read by every wave before the selection may set it)
+  const bool miss = (st->flags & ST_MISS) != 0;
+  __syncthreads();
+  if (miss) return;
   if (tid < 64) select1_body(j, comp, 0);
   __syncthreads();
   if (tid == 0) {

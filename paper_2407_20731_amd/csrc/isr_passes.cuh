@@ -5,7 +5,7 @@
 //   pass2      energies in the boundary bin -> candidate list
 //   pass3      keep e >= tau, bitmaps, decoupled look-back offsets, kept
 //              values, inverse transform of the kept set, exact error terms
-//   decompress blob -> nodal field (FP64 fixed-order inverse)
+//   decompress blob -> nodal field (MFMA inverse of FP32 / BF16 blobs made here)
 //   forward    coefficients only
 //
 // A workgroup handles EPI elements at a time; the next tile is prefetched into

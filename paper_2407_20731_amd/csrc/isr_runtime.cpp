@@ -243,12 +243,12 @@ Sizes plan_sizes(const isr_field* f, int tile, bool full_lists, bool stream) {
     const long long epw = wide ? shape_epi(f->order) : fast_epw(f->order, z.tile);
     const long long ftiles = (f->n_elem + epw - 1) / epw;
     // about 1024 sampled elements, in no fewer than 256 tiles (at N = 5 with
-    // four elements a tile, 1024 tiles took 43 us and these 20, and
-    // the windows were the same)
+    // four elements a tile 1024 tiles took 43 us, these take 20)
     z.sample_stride = std::max<long long>(1, ftiles / std::max<long long>(256, 1024 / epw));
     // workgroup tiles: in the unused part of lists 1 and 2 where that holds
     // them, so that the footprint stays that of the general pipeline
-    size_t sp = z.off_lists + (((size_t)nc * (z.list_cap + 2 * std::min<u64>(CAP, z.list_cap / 2)) * 8 + 255) & ~size_t(255));
+    size_t sp = z.off_lists +
+                (((size_t)nc * (z.list_cap + 2 * std::min<u64>(CAP, z.list_cap / 2)) * 8 + 255) & ~size_t(255));
     const size_t sp_end = wide ? z.off_lists + (size_t)nc * 2 * z.list_cap * 8 : 0;
     auto place = [&](size_t b) {
       if (sp + b > sp_end) return take(b);

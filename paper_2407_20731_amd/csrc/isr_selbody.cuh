@@ -374,6 +374,7 @@ DEV void resolve_sorted(const Job& j, CompState* st, int comp, int ml, int L, Se
     fixed = sh;
     __syncthreads();
   }
+  __syncthreads();  // (a wave may still be reading S.best)
   if (tid == 0) S.best = 0;
   // (with no bit open the members are one value: any order is sorted)
   int np = 1;
@@ -530,10 +531,13 @@ DEV void select_walk(const Job& j, CompState* st, int comp, int L) {
 DEV void select_body(const Job& j, int comp, int L, SelLds& S) {
   const int tid = threadIdx.x;
   CompState* st = j.st + comp;
-  if (st->resolved) return;
+  // (read by every wave before the walk below may change them)
+  const bool done = st->resolved != 0;
+  const bool few = st->cur_count <= (u64)CAP && (L > 2 || st->list0_exact);
   const int ml = list_members(L);
   __syncthreads();
-  if (st->cur_count <= (u64)CAP && (L > 2 || st->list0_exact)) {
+  if (done) return;
+  if (few) {
     resolve_sorted(j, st, comp, ml, L, S);
     return;
   }

@@ -1,6 +1,6 @@
 // Order-independent kernels for gfx950: zero fill, threshold selection
-// (level 1 on exponent bins, levels 2..6 on fraction bits, sort-resolve),
-// and the finalize step.  The threshold rule (arXiv 2407.20731, Sec. IV-B
+// (level 1 on exponent bins, levels 2..6 on fraction bits, narrowing of the last
+// members), and the finalize step.  The threshold rule (arXiv 2407.20731, Sec. IV-B
 // reading): tau is the largest energy value v whose dropped energy
 // S(v) = RN(exact sum of energies < v) does not exceed B = (tol*tol)*U2.
 #include "isr.h"
