@@ -672,12 +672,14 @@ int task_begin(isr_ctx* c, const isr_field* f, hipStream_t s, bool timing, Task*
   t->t_start = now_s();
   t->z = plan_sizes(f, ctx_tile(c, f->order, f->precision), t->full_lists);
   t->scratch = (char*)c->arena->alloc(t->z.scratch_bytes);
-  if (!t->scratch && wide_order(f->order, f->precision)) {  // the general pipeline where only its scratch fits
+  t->b = t->scratch ? new_blob(c, f, t->z) : nullptr;
+  if (!t->b && wide_order(f->order, f->precision)) {  // the general pipeline where only its scratch fits
+    if (t->scratch) c->arena->free(t->scratch);
     t->z = plan_sizes(f, 0, t->full_lists, false);
     t->scratch = (char*)c->arena->alloc(t->z.scratch_bytes);
+    t->b = t->scratch ? new_blob(c, f, t->z) : nullptr;
   }
   if (!t->scratch) return fail(ISR_ENOMEM, "scratch of %zu bytes does not fit the HBM budget", t->z.scratch_bytes);
-  t->b = new_blob(c, f, t->z);
   if (!t->b) {
     c->arena->free(t->scratch);
     t->scratch = nullptr;
@@ -2046,7 +2048,8 @@ int run_compress_elemcut(isr_ctx* c, const isr_field* f, isr_blob** out, isr_sta
   // kept counts, their scan and the error sums of pass B
   const size_t o_cnt = al(zero_end), o_chunk = al(o_cnt + (size_t)nc * E * 4);
   const size_t o_slots = al(o_chunk + (size_t)nc * ((E + SCAN_CHUNK - 1) / SCAN_CHUNK) * 8);
-  const size_t scr_bytes = o_slots + (size_t)nc * FAST_GMAX * 4 * 8;
+  // (pass B has at most E workgroups a component)
+  const size_t scr_bytes = o_slots + (size_t)nc * std::min<long long>(FAST_GMAX, E) * 4 * 8;
   char* scr = b->dev ? (char*)c->arena->alloc(scr_bytes) : nullptr;
   if (!b->dev || !scr) {
     if (b->dev) c->arena->free(b->dev);
