@@ -274,14 +274,12 @@ DEV void lh_flush(LdsHist& h, HistBin* g, int tid, int nthr) {
 }
 
 // ---- candidate lists -------------------------------------------------------------
-// List 0 of every component (capacity list_cap), then lists 1 and 2 of every
-// component (members about to be sorted: at most CAP).
-DEV u64 list_capk(const Job& j, int k) {
-  return k == 0 ? j.list_cap : (j.list_cap / 2 < (u64)CAP ? j.list_cap / 2 : (u64)CAP);
-}
+// List 0 of every component (the candidates, capacity list_cap), then list 1 of
+// every component: the members of the threshold's sub-bin, once they are few
+// enough to be sorted (at most CAP, and never more than there are candidates).
+DEV u64 list_capk(const Job& j, int k) { return k == 0 || j.list_cap < (u64)CAP ? j.list_cap : (u64)CAP; }
 DEV u64* list_ptr(const Job& j, int comp, int k) {
-  if (k == 0) return j.lists + (size_t)comp * j.list_cap;
-  return j.lists + (size_t)j.ncomp * j.list_cap + ((size_t)comp * 2 + (k - 1)) * list_capk(j, 1);
+  return j.lists + (size_t)(k * j.ncomp) * j.list_cap + (size_t)comp * list_capk(j, k);
 }
 
 // ---- decoupled look-back --------------------------------------------------------

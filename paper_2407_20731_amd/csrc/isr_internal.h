@@ -56,7 +56,7 @@ struct alignas(256) CompState {
   u64 cur_count;      // members of the current bin / sub-bin
   u64 r_lo, r_hi;     // 128-bit slack, in significand units of the boundary bin
   u64 w_lo, w_hi;     // 128-bit significand sum dropped inside the boundary bin
-  u64 list_count[3];  // candidate list fill levels
+  u64 list_count[2];  // fill levels of lists 0 and 1
   int32_t bstar;      // boundary exponent bin, -1 when tau is +inf or 0
   int32_t level;      // last level decided
   int32_t resolved;   // tau final

@@ -235,7 +235,7 @@ Sizes plan_sizes(const isr_field* f, int tile, bool full_lists, bool stream) {
   z.off_done = take(16 * 8 * sizeof(u32));
   z.zero_bytes = o;
   z.list_cap = full_lists || z.nv <= (1ull << 20) ? z.nv : std::max<u64>(z.nv / 8, 1ull << 20);
-  z.off_lists = take((size_t)nc * 2 * z.list_cap * 8);  // lists 0, then 1 and 2 (at most CAP entries each)
+  z.off_lists = take((size_t)nc * 2 * z.list_cap * 8);  // lists 0, then lists 1 (at most CAP entries each)
   z.fast = stream && fast_order(f->order, f->precision);
   z.tile = z.fast && f->precision != ISR_PREC_FP64 && dense_shape(f->order, tile) ? tile : 0;
   if (z.fast) {
@@ -248,10 +248,10 @@ Sizes plan_sizes(const isr_field* f, int tile, bool full_lists, bool stream) {
     // (N = 9, BF16, 20,000 elements: 1053 tiles 50 us, 1000 tiles 34)
     const long long most = std::max<long long>(256, 1024 / epw);
     z.sample_stride = std::max<long long>(1, (ftiles + most - 1) / most);
-    // workgroup tiles: in the unused part of lists 1 and 2 where that holds
-    // them, so that the footprint stays that of the general pipeline
+    // workgroup tiles: in the room that list 1 leaves where that holds them, so
+    // that the footprint stays that of the general pipeline
     size_t sp = z.off_lists +
-                (((size_t)nc * (z.list_cap + 2 * std::min<u64>(CAP, z.list_cap / 2)) * 8 + 255) & ~size_t(255));
+                (((size_t)nc * (z.list_cap + std::min<u64>(CAP, z.list_cap)) * 8 + 255) & ~size_t(255));
     const size_t sp_end = wide ? z.off_lists + (size_t)nc * 2 * z.list_cap * 8 : 0;
     auto place = [&](size_t b) {
       if (sp + b > sp_end) return take(b);

@@ -182,9 +182,9 @@ DEV void select1_body(const Job& j, int comp, int sample) {
 
 // List 0 (the candidates of the boundary bin or window) is only read, by every
 // level, so that it stays whole for the per-element kept counts; the members
-// go to lists 1, 2, 1, 2 at levels 3..6.
-DEV int list_out(int L) { return (L & 1) ? 1 : 2; }
-DEV int list_members(int L) { return L == 2 ? 0 : list_out(L); }
+// go to list 1, which the selection of the same level resolves (one list is
+// enough: no level reads another's).
+DEV int list_members(int L) { return L == 2 ? 0 : 1; }
 
 // Worker `item` of `nitems` handles list entries item*256 + tid + k*nitems*256
 // (blockDim must be 256).
@@ -212,7 +212,7 @@ DEV void refine_body(const Job& j, int comp, int L, u64 (*h)[2], u64 item, u64 n
   const u64 prefix = st->key_prefix, mask = st->key_mask;
   const int bstar = st->bstar;
   const u64 implicit = bstar ? (1ull << 52) : 0ull;
-  const int lo_idx = L >= 3 ? list_out(L) : 0;
+  const int lo_idx = list_members(L);
   u64* out = list_ptr(j, comp, lo_idx);
   const u64 stride = nitems * 256;
   // sixteen entries per lane per step, loaded before any is used (the lists
@@ -523,7 +523,7 @@ DEV void select_walk(const Job& j, CompState* st, int comp, int L) {
       st->kept = st->kept_above + st->cur_count;
       st->resolved = 1;
     } else {
-      st->list_count[list_out(L + 1)] = 0ull;
+      st->list_count[1] = 0ull;
     }
   }
 }
