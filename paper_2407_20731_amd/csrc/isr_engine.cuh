@@ -484,8 +484,10 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
   const int wlo = st->win_lo, whi = st->win_hi;
   const XParm PN = xparm(st->xm_norm, j.xh);
   const XParm PE = xparm(wlo - 1023, j.xh);
-  const XRange RN = xrange(PN), RE = xrange(PE);  // FP64 path
   const u32 hwlo = (u32)wlo << 20, hwhi = (u32)whi << 20;  // the window's edges as high words of energies
+  const XRange RN = xrange(PN);  // FP64 path
+  XRange RE = xrange(PE);
+  RE.lo = RE.lo < hwlo ? RE.lo : hwlo;  // (without a window, wlo = 0, nothing is below it)
   HistBin* gN = j.histN + (size_t)comp * HBINS;
   HistBin* gE = j.histE + (size_t)comp * HBINS;
   u64* list = list_ptr(j, comp, 0);

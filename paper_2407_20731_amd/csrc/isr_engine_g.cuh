@@ -243,8 +243,10 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passAG(Job j) {
   const int wlo = st->win_lo, whi = st->win_hi;
   const XParm PN = xparm(st->xm_norm, j.xh);
   const XParm PE = xparm(wlo - 1023, j.xh);
-  const XRange RN = xrange(PN), RE = xrange(PE);
   const u32 hwlo = (u32)wlo << 20, hwhi = (u32)whi << 20;
+  const XRange RN = xrange(PN);
+  XRange RE = xrange(PE);
+  RE.lo = RE.lo < hwlo ? RE.lo : hwlo;  // (without a window, wlo = 0, nothing is below it)
   HistBin* gN = j.histN + (size_t)comp * HBINS;
   HistBin* gE = j.histE + (size_t)comp * HBINS;
   u64* list = list_ptr(j, comp, 0);
