@@ -131,6 +131,15 @@ struct Eng {
       }
       return;
     }
+    if constexpr (!MF) {
+      // lanes past the tile read its last pencil (their values are never used): a
+      // zero written beside a load in flight has waited for it (N = 5, 50,001
+      // elements, 3 components: pass B 322 us, 285 so)
+      const double* p = tile + (lane < pv ? lane : pv - 1) * n;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) u[s] = __builtin_nontemporal_load(p + s);
+      return;
+    }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const int PI = pencil(s, lane), ax = axis(s, lane);
@@ -452,6 +461,7 @@ struct PassALds {
   u64 key[4][CAPB];
   u32 idx[4][CAPB];
   u32 ecnt[4][16];
+  XLow low[PREC == P_FP64 ? 2 : 1][4];  // FP64 path: norm terms, energies
   long long red[4][8];
 };
 
@@ -500,6 +510,10 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
   __syncthreads();
   XAcc an = {0.0, 0.0, 0.0}, ae = {0.0, 0.0, 0.0};
   XRun rn = xrun(PN), re = xrun(PE);  // FP64 path
+  if constexpr (EXACT) {
+    xlow_clear(&L.low[0][wv], lane);
+    xlow_clear(&L.low[1][wv], lane);
+  }
   double pe = 0.0;  // fixed-order sum of the energies below the window
   double pn = 0.0;  // MFMA paths: fixed-order sum of the norm terms
   u64 hi_tot = 0ull;
@@ -554,13 +568,15 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
     // norm terms: every term split exactly on the FP64 path; on the MFMA
     // paths each lane sums its terms in a fixed FP64 order and only the lane
     // totals are added exactly (as for the energies and the error terms)
-    bool odd = false;  // a term out of the running sums' range
+    u64 odd = 0ull;  // lanes with a term out of the running sums' range
+    double xs[EXACT ? NS : 1];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const bool v = G::valid(s, lane, ne);
       const double x = v ? wq[s] * (u[s] * u[s]) : 0.0;
       if constexpr (EXACT) {
-        odd = (xrun_left(rn, RN, x) && v) || odd;
+        xs[s] = x;
+        odd |= __builtin_amdgcn_ballot_w64(xrun_left(rn, RN, x) && v);
         // one slot at a time: interleaving them would hold every slot's
         // temporaries at once and cut the occupancy
         __builtin_amdgcn_sched_barrier(0);
@@ -569,14 +585,9 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
       }
     }
     if constexpr (EXACT) {
-      if (ballot(odd)) {  // rare: one vote a tile keeps this out of the slots' way
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const double x = G::valid(s, lane, ne) ? wq[s] * (u[s] * u[s]) : 0.0;
-          if (!xin(RN, x)) slow_bin(gN, x);
-        }
-      }
-      odd = false;
+      if (odd)  // (one vote a tile keeps this out of the slots' way)
+        xlow_tile<EPW * G::n2, NS, true>(L.low[0], xlow_m(PN.m, j.xh), gN, L.buf, xs, [&](double x) { return !xin(RN, x); });
+      odd = 0ull;
     }
     if constexpr (EXACT) pin(rn);
     typename G::wt x1[NS];
@@ -628,9 +639,10 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
         }
       }
       if constexpr (EXACT) {  // (the running sums' range ends at the window)
+        xs[s] = en;
         const bool tiny = hw < RE.lo;
         xrun_add(re, hw < hwlo && !tiny ? en : 0.0);
-        odd = (tiny && v) || odd;
+        odd |= __builtin_amdgcn_ballot_w64(tiny && v);
       } else {
         pe += hw < hwlo ? en : 0.0;  // (zero in masked slots)
       }
@@ -638,13 +650,8 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
     }
     if constexpr (EXACT) pin(re);
     if constexpr (EXACT) {
-      if (ballot(odd)) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const double en = G::valid(s, lane, ne) ? wq[s] * (c[s] * c[s]) : 0.0;
-          if (hi_word(en) < RE.lo) slow_bin(gE, en);
-        }
-      }
+      if (odd)
+        xlow_tile<EPW * G::n2, NS, true>(L.low[1], xlow_m(PE.m, j.xh), gE, L.buf, xs, [&](double x) { return hi_word(x) < RE.lo; });
     }
     if (hmax >= 0x7ff00000u) slow_bin(gE, __builtin_inf());  // Inf/NaN: counted in the flag bin
     hi_tot += hc;
@@ -687,6 +694,10 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
   v[6] = lane == 0 ? (long long)hi_tot : 0ll;
   block_sum_i64<7>(v, L.red, tid);
   if (tid < 7) j.slotsA[((size_t)comp * j.gA + vb) * 8 + tid] = L.red[0][tid];
+  if constexpr (EXACT) {
+    if (tid == 0) xlow_out(L.low[0], gN, xlow_m(QN.m, j.xh));
+    if (tid == 64 && wlo < whi) xlow_out(L.low[1], gE, xlow_m(QE.m, j.xh));
+  }
 }
 
 template <int N, int PREC>
@@ -702,6 +713,7 @@ struct PassBLds {
   TabLds tab;
   u64 bm[4][16];
   u32 wp[4][16];
+  XLow low[4];  // FP64 path: error terms
   long long red[4][8];
   __int128 r3[4][3];
   int last;
@@ -736,6 +748,7 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
   XAcc ar = {0.0, 0.0, 0.0};
   const XRange RR = xrange(PR);  // FP64 path
   XRun rr = xrun(PR);
+  if constexpr (EXACT) xlow_clear(&L.low[wv], lane);
   double pr = 0.0;  // fixed-order sum of the error terms
   bool bad = false;
   const double* ub = j.u + (size_t)comp * j.comp_stride;
@@ -874,13 +887,15 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
       for (int s = 0; s < NS; ++s) G::bitmap_or(bm, ballot(keep[s]), s, ne, lane);
       asm volatile("" ::: "memory");
       // bitmap words out, exclusive word prefixes inside each element
-      if (lane < ne * W) {
-        const u64 wd = bm[lane];
-        gbm[e0 * W + lane] = wd;
-        const int ee = lane / W, w = lane % W;
+      int wl = lane;
+      if constexpr (EXACT) asm volatile("" : "+v"(wl));  // (no address made from it is kept across tiles)
+      if (wl < ne * W) {
+        const u64 wd = bm[wl];
+        gbm[e0 * W + wl] = wd;
+        const int ee = wl / W, w = wl % W;
         u32 pre = 0u;
         for (int k = 0; k < w; ++k) pre += (u32)__popcll(bm[ee * W + k]);
-        wp[lane] = pre;
+        wp[wl] = pre;
         if (w == W - 1) {
           const u64 expect = eptr[e0 + ee + 1] - eptr[e0 + ee];
           if ((u64)(pre + (u32)__popcll(wd)) != expect) bad = true;
@@ -910,6 +925,7 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
 #pragma unroll
     for (int s = 0; s < NS; ++s) cm[s] = keep[s] ? c[s] : 0.0;
     G::inverse(cm, ut, L.buf[wv], mt, j.tab, lane);
+    if constexpr (EXACT && N == 7) __builtin_amdgcn_sched_barrier(0);  // (interleaved, both would spill)
     // quadrature weights of the slots, the same way
     if (j.jac) {
 #pragma unroll
@@ -918,14 +934,16 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
 #pragma unroll
       for (int s = 0; s < NS; ++s) wq[s] = L.tab.w3[s][lane];
     }
-    bool odd = false;
+    u64 odd = 0ull;
+    double xs[EXACT ? NS : 1];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const bool v = G::valid(s, lane, ne);
       const double d = u[s] - ut[s];
       const double x = v ? wq[s] * (d * d) : 0.0;
       if constexpr (EXACT) {
-        odd = (xrun_left(rr, RR, x) && v) || odd;
+        xs[s] = x;
+        odd |= ballot(xrun_left(rr, RR, x) && x != 0.0);
         __builtin_amdgcn_sched_barrier(0);
       } else {
         pr += x;
@@ -933,14 +951,8 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
     }
     if constexpr (EXACT) pin(rr);
     if constexpr (EXACT) {
-      if (ballot(odd)) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const double d = u[s] - ut[s];
-          const double x = G::valid(s, lane, ne) ? wq[s] * (d * d) : 0.0;
-          if (!xin(RR, x)) slow_bin(gR, x);
-        }
-      }
+      if (odd)
+        xlow_tile<EPW * G::n2, NS, false>(L.low, xlow_m(PR.m, j.xh), gR, L.buf, xs, [&](double x) { return !xin(RR, x); });
     }
   }
   if (ballot(bad)) {
@@ -957,6 +969,9 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
   xints(ar, QR, v);
   block_sum_i64<3>(v, L.red, tid);
   if (tid < 3) j.slotsB[((size_t)comp * j.gB + vb) * 4 + tid] = L.red[0][tid];
+  if constexpr (EXACT) {
+    if (tid == 0) xlow_out(L.low, gR, xlow_m(QR.m, j.xh));
+  }
   if (!tail || !last_block(j.done + D_PASSB * 8 + comp, &L.last, nvb)) return;
   passB_tail(j, comp, L.r3);
 }
@@ -1147,6 +1162,7 @@ struct QuantWLds {
   double w3[8][64], sq[8][64];  // quadrature weights of field slots, sqrt(g3) of coefficient slots
   u64 bm[4][16];
   u32 wp[4][16];
+  XLow low[4];
   long long red[4][8];
 };
 
@@ -1175,6 +1191,7 @@ __global__ __launch_bounds__(256, 3) void k_quantW(Job j) {
   const XParm PR = xparm(j.qxm[comp], j.xh);
   const XRange RR = xrange(PR);
   XRun rr = xrun(PR);
+  xlow_clear(&L.low[wv], lane);
   HistBin* gR = j.histR + (size_t)comp * HBINS;
   bool big = false;
   double un[NS];
@@ -1205,24 +1222,20 @@ __global__ __launch_bounds__(256, 3) void k_quantW(Job j) {
       return (q * step) / sq;
     });
     G::inverse(cm, ut, L.buf[wv], mt, j.tab, lane);
-    bool odd = false;
+    u64 odd = 0ull;
+    double xs[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const bool v = G::valid(s, lane, ne);
       const double d = u[s] - ut[s];
       const double x = v ? L.w3[s][lane] * (d * d) : 0.0;
-      odd = (xrun_left(rr, RR, x) && v) || odd;
+      xs[s] = x;
+      odd |= ballot(xrun_left(rr, RR, x) && x != 0.0);
       __builtin_amdgcn_sched_barrier(0);
     }
     pin(rr);
-    if (ballot(odd)) {
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const double d = u[s] - ut[s];
-        const double x = G::valid(s, lane, ne) ? L.w3[s][lane] * (d * d) : 0.0;
-        if (!xin(RR, x)) slow_bin(gR, x);
-      }
-    }
+    if (odd)
+      xlow_tile<EPW * G::n2, NS, false>(L.low, xlow_m(PR.m, j.xh), gR, L.buf, xs, [&](double x) { return !xin(RR, x); });
   }
   if (big) atomicOr(&j.ticket[1], 1u);
   const XParm QR = xparm(again(PR.m), j.xh);
@@ -1230,6 +1243,7 @@ __global__ __launch_bounds__(256, 3) void k_quantW(Job j) {
   xints(xrun_sums(rr, QR), QR, v);
   block_sum_i64<3>(v, L.red, tid);
   if (tid < 3) j.slotsB[((size_t)comp * j.gB + blockIdx.x) * 4 + tid] = L.red[0][tid];
+  if (tid == 0) xlow_out(L.low, gR, xlow_m(QR.m, j.xh));
 }
 
 // Grid of a decompression: gx workgroups per component cover its tiles once;

@@ -221,6 +221,9 @@ __global__ __launch_bounds__(256, 2) void k_sampleG(Job j) {
   }
 }
 
+// slots of terms out of the running sums' range that are staged at a time
+constexpr int XL_CH = 4;
+
 // ---- pass A -------------------------------------------------------------------
 template <int N>
 struct PassALdsG {
@@ -228,6 +231,8 @@ struct PassALdsG {
   u64 key[4][CAPB];
   u32 idx[4][CAPB];
   u32 ecnt[4];
+  XLow low[2][4];  // norm terms, energies
+  double far[4][64 * XL_CH];
   long long red[4][8];
 };
 
@@ -261,6 +266,8 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passAG(Job j) {
   u32 ncap = 0u;
   double u[PER];
   if (tid < 4) L.ecnt[tid] = 0u;
+  xlow_clear(&L.low[0][wv], lane);
+  xlow_clear(&L.low[1][wv], lane);
   long long t = blockIdx.x;
   auto fetch = [&](long long tt) {
     const long long e0 = tt * EPI;
@@ -274,16 +281,26 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passAG(Job j) {
     int dt = tid;  // (per-tile copy: the indexes made from it are not kept across tiles)
     asm volatile("" : "+v"(dt));
     // norm terms of the dense values
-    bool odd = false;
+    u64 odd = 0ull;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int idx = dt + 256 * k;
       const bool v = idx < ne * n3;
       const double x = v ? jw(j.jac, e0 + idx / n3, w3[k]) * (u[k] * u[k]) : 0.0;
-      if (xrun_left(rn, RN, x) && v) slow_bin(gN, x);
+      odd |= __builtin_amdgcn_ballot_w64(xrun_left(rn, RN, x) && v);
       __builtin_amdgcn_sched_barrier(0);
     }
     pin(rn);
+    if (odd) {
+      double xn[PER];
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        const int idx = dt + 256 * k;
+        xn[k] = idx < ne * n3 ? jw(j.jac, e0 + idx / n3, w3[k]) * (u[k] * u[k]) : 0.0;
+      }
+      xlow_tile<64, XL_CH, true>(L.low[0], xlow_m(PN.m, j.xh), gN, L.far, xn, [&](double x) { return !xin(RN, x); });
+    }
+    odd = 0ull;
     G::store(L.w, u, dt);
     if (t + gridDim.x < tiles) fetch(t + gridDim.x);
     double c[n];
@@ -313,16 +330,15 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passAG(Job j) {
       }
       const bool tiny = hw < RE.lo;
       xrun_add(re, hw < hwlo && !tiny ? en : 0.0);
-      odd = (tiny && act) || odd;
+      odd |= __builtin_amdgcn_ballot_w64(tiny && act);
       __builtin_amdgcn_sched_barrier(0);
     }
     pin(re);
-    if (ballot(odd)) {
+    if (odd) {
+      double xe[n];
 #pragma unroll
-      for (int r = 0; r < n; ++r) {
-        const double en = act ? (je * g3[r]) * (c[r] * c[r]) : 0.0;
-        if (hi_word(en) < RE.lo) slow_bin(gE, en);
-      }
+      for (int r = 0; r < n; ++r) xe[r] = act ? (je * g3[r]) * (c[r] * c[r]) : 0.0;
+      xlow_tile<64, XL_CH, true>(L.low[1], xlow_m(PE.m, j.xh), gE, L.far, xe, [&](double x) { return hi_word(x) < RE.lo; });
     }
     if (hmax >= 0x7ff00000u) slow_bin(gE, __builtin_inf());  // Inf/NaN: counted in the flag bin
     hi_tot += hmine;
@@ -349,6 +365,8 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passAG(Job j) {
   v[6] = (long long)hi_tot;
   block_sum_i64<7>(v, L.red, tid);
   if (tid < 7) j.slotsA[((size_t)comp * j.gA + blockIdx.x) * 8 + tid] = L.red[0][tid];
+  if (tid == 0) xlow_out(L.low[0], gN, xlow_m(QN.m, j.xh));
+  if (tid == 64 && wlo < whi) xlow_out(L.low[1], gE, xlow_m(QE.m, j.xh));
 }
 
 // ---- pass B -------------------------------------------------------------------
@@ -357,6 +375,8 @@ struct PassBLdsG {
   double w[EngG<N>::LDSW];
   u64 bm[64];  // the tile's bitmap words
   u32 wp[64];  // kept values before each word
+  XLow low[4];  // error terms
+  double far[4][64 * XL_CH];
   long long red[4][8];
 };
 
@@ -365,7 +385,7 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passBG(Job j) {
   typedef EngG<N> G;
   constexpr int n = G::n, n2 = G::n2, n3 = G::n3, EPI = G::EPI, PER = G::PER, W = G::W;
   __shared__ PassBLdsG<N> L;
-  const int tid = threadIdx.x, lane = tid & 63, comp = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, comp = blockIdx.y;
   const int el = tid / n2, a = (tid % n2) / n, b = tid % n;
   CompState* st = j.st + comp;
   if (st->flags & ST_MISS) return;
@@ -386,6 +406,7 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passBG(Job j) {
   XRun rr = xrun(PR);
   bool bad = false;
   if (tid < 64) L.bm[tid] = 0ull;
+  xlow_clear(&L.low[wv], lane);
   double un[PER];
   long long t = blockIdx.x;
   auto fetch = [&](long long tt) {
@@ -458,16 +479,21 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passBG(Job j) {
     G::load(ub + e0 * n3, ne * n3, u, tid);
     __syncthreads();
     // error terms of the dense values
+    u64 odd = 0ull;
+    double xs[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int idx = dt + 256 * k;
       const bool v = idx < ne * n3;
       const double d = v ? u[k] - L.w[G::at(idx)] : 0.0;
       const double x = v ? jw(j.jac, e0 + idx / n3, w3[k]) * (d * d) : 0.0;
-      if (xrun_left(rr, RR, x) && v) slow_bin(gR, x);
+      xs[k] = x;
+      odd |= __builtin_amdgcn_ballot_w64(xrun_left(rr, RR, x) && v);
       __builtin_amdgcn_sched_barrier(0);
     }
     pin(rr);
+    if (odd)
+      xlow_tile<64, XL_CH, true>(L.low, xlow_m(PR.m, j.xh), gR, L.far, xs, [&](double x) { return !xin(RR, x); });
   }
   if (ballot(bad)) {
     if (lane == 0) atomicOr(&st->flags, ST_LIST);
@@ -477,6 +503,7 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passBG(Job j) {
   xints(xrun_sums(rr, QR), QR, v);
   block_sum_i64<3>(v, L.red, tid);
   if (tid < 3) j.slotsB[((size_t)comp * j.gB + blockIdx.x) * 4 + tid] = L.red[0][tid];
+  if (tid == 0) xlow_out(L.low, gR, xlow_m(QR.m, j.xh));
 }
 
 // ---- reading kept values back ----------------------------------------------------
@@ -578,6 +605,8 @@ __global__ __launch_bounds__(256, 2) void k_decompG(Job j, void* out) {
 // components: 266 -> 92 us.
 template <int N>
 struct QuantLdsG : WordLdsG<N> {
+  XLow low[4];  // error terms
+  double far[4][64 * XL_CH];
   long long red[4][8];
 };
 
@@ -602,6 +631,7 @@ __global__ __launch_bounds__(256, 2) void k_quantG(Job j) {
   g_weights<G>(j.tab, w3, sq, tid, a, b);
 #pragma unroll
   for (int r = 0; r < n; ++r) sq[r] = __builtin_sqrt(sq[r]);
+  xlow_clear(&L.low[tid >> 6], tid & 63);
   bool big = false;
   u64 wnext = 0ull, bnext = 0ull;
   auto fetch = [&](long long tt) {
@@ -632,16 +662,20 @@ __global__ __launch_bounds__(256, 2) void k_quantG(Job j) {
     });
     G::inverse(L.w, j.tab, el, a, b, act, cm);
     __syncthreads();
+    u64 odd = 0ull;
+    double xs[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int idx = tid + 256 * k;
       const bool v = idx < ne * n3;
       const double d = v ? u[k] - L.w[G::at(idx)] : 0.0;
-      const double x = w3[k] * (d * d);
-      if (xrun_left(rr, RR, x) && v) slow_bin(gR, x);
+      xs[k] = w3[k] * (d * d);
+      odd |= __builtin_amdgcn_ballot_w64(xrun_left(rr, RR, xs[k]) && v);
       __builtin_amdgcn_sched_barrier(0);
     }
     pin(rr);
+    if (odd)
+      xlow_tile<64, XL_CH, true>(L.low, xlow_m(PR.m, j.xh), gR, L.far, xs, [&](double x) { return !xin(RR, x); });
   }
   if (big) atomicOr(&j.ticket[1], 1u);
   const XParm QR = xparm(again(PR.m), j.xh);
@@ -649,6 +683,7 @@ __global__ __launch_bounds__(256, 2) void k_quantG(Job j) {
   xints(xrun_sums(rr, QR), QR, v);
   block_sum_i64<3>(v, L.red, tid);
   if (tid < 3) j.slotsB[((size_t)comp * j.gB + blockIdx.x) * 4 + tid] = L.red[0][tid];
+  if (tid == 0) xlow_out(L.low, gR, xlow_m(QR.m, j.xh));
 }
 
 // ---- launchers ------------------------------------------------------------------

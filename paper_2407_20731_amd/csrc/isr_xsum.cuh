@@ -5,8 +5,9 @@
 // fixed grids by error-free extraction against powers of two (Rump, Ogita and
 // Oishi, "Accurate floating-point summation part I", SIAM J. Sci. Comput.
 // 31(1), 2008, Alg. 3.2) and keeps three FP64 running sums, which stay exact
-// while a lane adds at most 2^(h-1) terms.  A term far below M, or above M,
-// goes to the global exponent bins.
+// while a lane adds at most 2^(h-1) terms.  Terms far below M go to a second set
+// of sums (XLow) and only what is left of them, or above M, to the global
+// exponent bins.
 // Workgroups publish the three sums as integers; the consumer adds them up
 // as 128-bit integers and writes the exact total into exponent bins.  On the
 // FP64 path every term is split this way; on the MFMA paths a lane first adds
@@ -78,10 +79,10 @@ DEV void slow_bin(HistBin* g, double v) {
 // range, so the third sum takes it as it is.  At most 2^(h-1) terms: the
 // accumulators stay in their binades (a1 in [2^(m+h), 1.5 2^(m+h)], grid u1;
 // a2 within 2^(m+2h-54) of 1.5 2^(m+2h-53), grid 2 u2) and |a3| stays within
-// 2^52 u3.  Terms outside the range go to the exact bins (at h = 12 those
-// below 2^-71 of the bound: a few in ten thousand error terms of a smooth
-// field).  N = 7, 65,536 elements, FP64: pass A 517 -> 360 us, pass B 517 ->
-// 468 us, with the registers that the shorter sums free.
+// 2^52 u3.  Terms outside the range (at h = 12 those below 2^-71 of the bound)
+// are left to XLow: next to none of a noisy field's, a quarter to three quarters of
+// a smooth field's energies.  N = 7, 65,536 elements, FP64: pass A 517 -> 360 us,
+// pass B 517 -> 468 us, with the registers that the shorter sums free.
 struct XRun {
   double a1, a2, a3;
 };
@@ -115,8 +116,8 @@ DEV void xrun_add(XRun& A, double y) {
 // MFMA paths, one add a term, that is the better order: 196 us against 216.)
 DEV void pin(XRun& A) { asm volatile("" : "+v"(A.a1), "+v"(A.a2), "+v"(A.a3)); }
 
-// Adds x when it is in range; otherwise true: x belongs in the exact bins
-// (nothing to do for a zero).
+// Adds x when it is in range; otherwise true: unless it is zero, x belongs in the
+// sums below (XLow) or in the exact bins.
 DEV bool xrun_left(XRun& A, const XRange& R, double x) {
   const bool in = xin(R, x);
   xrun_add(A, in ? x : 0.0);
@@ -262,6 +263,99 @@ DEV u64 total_words(const __int128 (&K)[3], int m, int h) {
   u64 w = part_at(z.w[0], z.w[1], sh);
   wb_add(w, part_at(z.w[2], 0ull, sh + 128));
   return w;
+}
+
+// Terms below the running sums' range: a second set of three sums with M' =
+// 2^xlow_m, held by the wave in LDS as 128-bit integers and fed a tile at a time.
+// Smooth fields live on it (the energies that are rounding noise, the errors of
+// elements that keep everything): a global atomic or three each into the exact
+// bins, on a few dozen of them, made the request 164 ms at N = 9, 32,768
+// elements, Taylor-Green, FP64, 3 components, where it takes 1.95 ms so (noisy
+// field: 1.54); N = 7, 65,536 elements 72.4 -> 1.33 ms (0.92).  A term below this
+// range too (2^-74 of M') still goes to the bins.
+constexpr int XL_H = 11;  // at most 2^10 terms a tile: sixteen a lane
+
+struct XLow {
+  u64 w[3][2];
+};
+
+DEV int xlow_m(int m, int h) { return m + 3 * h - 107; }
+DEV void xlow_clear(XLow* L, int lane) {
+  if (lane < 6) L->w[lane >> 1][lane & 1] = 0ull;
+}
+
+// The thread's number hidden from the compiler (no address made from it is kept
+// across tiles).
+DEV int again_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// One tile's terms x, of the first LANES lanes (zero in the others), into this
+// wave's sums of low[4], those with out(x) (by the whole wave).  m: xlow_m.
+// ZEROS: called for tiles that only have exact zeros there too.  By way of the
+// wave's LDS buffer, CH slots at a time and in a rolled loop: unrolled on
+// registers this branch took the prefetched tile's (N = 7, 65,536 elements, noisy
+// field: the request 911 us without the branch, 1217 with it unrolled, 917 so).
+template <int LANES, int CH, bool ZEROS, int CNT, int LDSW, class OUT>
+DEV void xlow_tile(XLow* low, int m, HistBin* g, double (*bufs)[LDSW], const double (&x)[CNT], OUT out) {
+  static_assert(CH * LANES <= LDSW, "the terms fit the wave's buffer");
+  static_assert(CNT * 64 <= 1 << (XL_H - 1), "the wave's sums of a tile are exact");
+  if constexpr (ZEROS) {
+    bool any = false;
+#pragma unroll
+    for (int s = 0; s < CNT; ++s) any = (out(x[s]) && x[s] != 0.0) || any;
+    if (!ballot(any)) return;
+  }
+  const int tid = again_tid(), lane = tid & 63;
+  double* buf = bufs[tid >> 6];
+  m = again(m);
+  const XParm P = xparm(m < XM_MIN ? XM_MIN : m, XL_H);
+  XRange R = xrange(P);
+  if (m < XM_MIN) R.span = 0u;  // (no room for normal units: every term to the bins)
+  XRun A = xrun(P);
+#pragma unroll
+  for (int c = 0; c < CNT; c += CH) {
+    const int k = CNT - c < CH ? CNT - c : CH;
+#pragma unroll
+    for (int s = 0; s < k; ++s)
+      if (LANES == 64 || lane < LANES) buf[LANES * s + lane] = x[c + s];
+    asm volatile("" ::: "memory");
+#pragma unroll 1
+    for (int s = 0; s < k; ++s) {
+      double v = LANES == 64 || lane < LANES ? buf[LANES * s + lane] : 0.0;
+      v = out(v) ? v : 0.0;
+      if (xrun_left(A, R, v)) slow_bin(g, v);
+    }
+    asm volatile("" ::: "memory");
+  }
+  // multiples of a unit, below 2^53 of it: the wave's sums are exact too
+  const XAcc S = xrun_sums(A, P);
+  const double a1 = wave_sum_dpp(S.a1), a2 = wave_sum_dpp(S.a2), a3 = wave_sum_dpp(S.a3);
+  const int e = lane == 0 ? P.m + P.h - 52 : (lane == 1 ? P.m + 2 * P.h - 106 : P.m + 3 * P.h - 159);
+  const long long k = (long long)ldexp(lane == 0 ? a1 : (lane == 1 ? a2 : a3), -e);
+  XLow* L = low + (tid >> 6);
+  if (lane < 3) {
+    const u64 lo = L->w[lane][0] + (u64)k;
+    L->w[lane][1] += (u64)(k >> 63) + (lo < (u64)k ? 1ull : 0ull);
+    L->w[lane][0] = lo;
+  }
+}
+
+// The four waves' sums into the exact bins, all of it in bins below M' (by one
+// thread, behind a barrier).
+DEV void xlow_out(const XLow* L, HistBin* g, int m) {
+  __int128 K[3];
+  u64 any = 0ull;
+  for (int k = 0; k < 3; ++k) {
+    K[k] = 0;
+    for (int w = 0; w < 4; ++w) {
+      K[k] += (__int128)(((unsigned __int128)L[w].w[k][1] << 64) | L[w].w[k][0]);
+      any |= L[w].w[k][0] | L[w].w[k][1];
+    }
+  }
+  if (any) emit_total(g, K, m, XL_H, m + 1022);
 }
 
 DEV long long wave_sum_i64(long long v) { return (long long)wave_sum64((u64)v); }

@@ -1,19 +1,37 @@
 """FP64 terms far below the running sums' range: fields that have many of them
 take about as long as noisy ones, which have next to none (as an atomic each
 they took 15 to 100 times as long, so that the factor allowed is no matter of
-the machine's load)."""
+the machine's load), and their sums are exact."""
 
+import math
 import time
 
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import synth
+from oracle import elemcut as P
+from oracle import quantize as Q
 from paper_2407_20731_amd import isr
 
 pytestmark = pytest.mark.gpu
 
 SLOWER = 5.0
+
+
+def _taylor_green(n_elem, order):
+    """Taylor-Green vortex [3, E, n, n, n] on cubes of edge 2 pi / 8, no noise."""
+    n = order + 1
+    nx, ny, _ = synth.mesh_dims(n_elem)
+    h, e = 2.0 * math.pi / 8, np.arange(n_elem)
+    xi = (synth.gll_points(order) + 1.0) / 2 * h
+    x = ((e % nx) * h).reshape(-1, 1, 1, 1) + xi.reshape(1, 1, 1, n)
+    y = ((e // nx % ny) * h).reshape(-1, 1, 1, 1) + xi.reshape(1, 1, n, 1)
+    z = ((e // (nx * ny)) * h).reshape(-1, 1, 1, 1) + xi.reshape(1, n, 1, 1)
+    return np.stack([np.sin(x) * np.cos(y) * np.cos(z), -np.cos(x) * np.sin(y) * np.cos(z),
+                     0.5 * np.cos(x) * np.cos(y) * np.sin(z)])
 
 
 def _seconds(ctx, u, order, tol):
@@ -32,3 +50,63 @@ def test_keep_everything_takes_no_longer(order):
     u = torch.from_numpy(synth.field((1 << 19) // (order + 1) ** 3, order)).cuda()
     with isr.Context(device=0) as ctx:
         assert _seconds(ctx, u, order, -1.0) < SLOWER * _seconds(ctx, u, order, 1e-3)
+
+
+@pytest.mark.parametrize("order", [3, 6, 7, 8, 9, 12, 15])
+def test_smooth_fields_take_no_longer(order):
+    E = (1 << 19) // (order + 1) ** 3
+    noisy = torch.from_numpy(synth.field(E, order)).cuda()
+    smooth = torch.from_numpy(_taylor_green(E, order)).cuda()
+    with isr.Context(device=0) as ctx:
+        assert _seconds(ctx, smooth, order, 1e-3) < SLOWER * _seconds(ctx, noisy, order, 1e-3)
+
+
+# exact sums with terms in, below and far below the second range, and where that
+# range has no room; bit for bit against the oracle
+CASES = [(1, 37), (2, 22), (3, 9), (4, 7), (5, 4), (6, 3), (7, 5), (8, 7), (9, 5), (10, 3), (11, 2), (12, 2), (13, 2),
+         (14, 2), (15, 2)]
+
+
+def _fields(order, n_elem):
+    rng = np.random.default_rng(31 * order + n_elem)
+    u = _taylor_green(n_elem, order)
+    shape = u.shape[1:]
+    noise = rng.standard_normal(shape)
+    rest = noise * 2.0 ** -rng.choice([0, 30, 45, 60, 80, 120, 200, 400], size=(n_elem, 1, 1, 1)).astype(np.float64)
+    spread = noise * 2.0 ** rng.integers(-110, 1, size=shape)
+    return {"smooth": u, "rest": rest[None], "spread": spread[None], "spread, small": spread[None] * 2.0 ** -380,
+            "smooth, large": u * 2.0 ** 250, "smooth, small": u * 2.0 ** -400}
+
+
+@pytest.mark.parametrize("order,n_elem", CASES)
+@pytest.mark.parametrize("jac", [False, True])
+def test_exact_sums(order, n_elem, jac):
+    J = np.linspace(0.25, 8.0, n_elem) if jac else None
+    dj = torch.from_numpy(J).cuda() if jac else None
+    with isr.Context(device=0) as ctx:
+        for name, u in _fields(order, n_elem).items():
+            u = np.ascontiguousarray(u)
+            for tol in (1e-3, 0.3, -1.0):
+                ref = oracle.compress(u, order, tol, jac=J, keep_arrays=True)
+                blob = ctx.compress(torch.from_numpy(u).cuda(), order, tol, "fp64", jac=dj)
+                s, bm = blob.stats, blob.arrays().bitmap
+                for c, r in enumerate(ref.comps):
+                    got = (s["norm2"][c], s["tau"][c], s["dropped"][c], s["err2"][c], s["kept"][c])
+                    assert got == (r.U2, r.tau, r.dropped, r.err2, r.kept), (name, tol, c)
+                    assert np.array_equal(bm[c], r.bitmap), (name, tol, c)
+                blob.free()
+
+
+@pytest.mark.parametrize("order,n_elem", [(1, 37), (4, 7), (7, 5), (9, 5), (15, 2)])
+def test_exact_sums_of_the_variants(order, n_elem):
+    with isr.Context(device=0) as ctx:
+        for name, u in _fields(order, n_elem).items():
+            if name.endswith("small") or name.endswith("large"):
+                continue
+            u = np.ascontiguousarray(u)
+            d = torch.from_numpy(u).cuda()
+            for blob, ref in ((ctx.compress_quantized(d, order, 1e-3, 0.5), Q.compress_quantized(u, order, 1e-3, 0.5)),
+                              (ctx.compress_elemcut(d, order, 1e-3), P.compress_elemcut(u, order, 1e-3))):
+                for h, r in zip(blob.arrays().comps, ref):
+                    assert (h["U2"], h["dropped"], h["err2"], h["kept"]) == (r.U2, r.dropped, r.err2, r.kept), name
+                blob.free()
