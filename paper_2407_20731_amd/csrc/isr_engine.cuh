@@ -42,9 +42,12 @@
 #include "isr_xsum.cuh"
 
 // Minimum resident workgroups per CU the streaming passes are compiled for
-// (bounds their registers: 4 -> 128 VGPRs, 3 -> 168, 2 -> 256).  Measured on
-// the 65,536-element N = 7 snapshot: the FP64 transforms want 2 (fewer
-// workgroups beat spilling), the MFMA paths 3.
+// (bounds their registers: 4 -> 128 VGPRs, 3 -> 168, 2 -> 256).  FP64 four: the
+// table entries sit in scalar registers, so the passes fit 128 (with three or two
+// both take 1 to 3 % longer at N = 7, and as long at the other orders; pass B of N = 5
+// with two, 9,710 elements, 69 us for 61).  But pass B of N = 6 three: with four it
+// spills 37 registers (6,115 elements, 3 components: the request 291 us for 276).
+// MFMA paths three.
 #ifndef ISR_FAST_MINB_F64
 #define ISR_FAST_MINB_F64 4
 #endif
@@ -54,6 +57,11 @@
 #define ISR_FAST_MINB (PREC == P_FP64 ? ISR_FAST_MINB_F64 : ISR_FAST_MINB_MIX)
 
 namespace isr {
+
+template <int N, int PREC>
+constexpr int fast_minb_b() {
+  return PREC == P_FP64 && N != 6 ? ISR_FAST_MINB_F64 : 3;
+}
 
 template <bool C, class A, class B>
 struct Pick {
@@ -977,7 +985,7 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
 }
 
 template <int N, int PREC>
-__global__ __launch_bounds__(256, ISR_FAST_MINB) void k_passB(Job j) {
+__global__ __launch_bounds__(256, (fast_minb_b<N, PREC>())) void k_passB(Job j) {
   __shared__ PassBLds<N, PREC> L;
   passB_body<N, PREC>(j, blockIdx.y, blockIdx.x, gridDim.x, L, false);
 }
