@@ -243,10 +243,13 @@ Sizes plan_sizes(const isr_field* f, int tile, bool full_lists, bool stream) {
     const long long epw = wide ? shape_epi(f->order) : fast_epw(f->order, z.tile);
     const long long ftiles = (f->n_elem + epw - 1) / epw;
     // at most 1024 sampled elements, or 256 tiles if that is more (at N = 5 with
-    // four elements a tile 1024 tiles took 43 us, these take 20).  Rounded up:
-    // the grid holds that many tiles at once, and one more is another round
-    // (N = 9, BF16, 20,000 elements: 1053 tiles 50 us, 1000 tiles 34)
-    const long long most = std::max<long long>(256, 1024 / epw);
+    // four elements a tile 1024 tiles took 43 us, these take 20); 1024 tiles of up
+    // to 256 values (orders 1..4: with 256 of them the window missed the threshold
+    // in 59 of 4,320 smooth and noisy requests, with 1024 in 28; a miss costs a
+    // millisecond and more, the larger sample 4 to 7 us).  Rounded up: the grid
+    // holds that many tiles at once, and one more is another round (N = 9, BF16,
+    // 20,000 elements: 1053 tiles 50 us, 1000 tiles 34)
+    const long long most = epw * n3 <= 256 ? 1024 : std::max<long long>(256, 1024 / epw);
     z.sample_stride = std::max<long long>(1, (ftiles + most - 1) / most);
     // workgroup tiles: in the room that list 1 leaves where that holds them, so
     // that the footprint stays that of the general pipeline
