@@ -309,11 +309,18 @@ hipError_t launch_count(const Job& j, int grid_x, hipStream_t s);
 hipError_t launch_scan(const Job& j, hipStream_t s);
 constexpr int SCAN_CHUNK = 1024;  // elements per chunk of the element-offset scan
 // The phases from the gather to the offsets of pass B in one workgroup per
-// component (k_chain) instead of nine launches: up to 2^19 values, where a
-// request takes as long either way (N = 7, FP32, with decompression: 64
-// elements 104 us against 113, 512 elements 128 against 138, 1,000 elements 154
-// against 158), and as many elements as its counters in LDS hold.
-inline bool chain_small(u64 nv, long long n_elem) { return nv <= (1ull << 19) && n_elem <= SCAN_CHUNK; }
+// component (k_chain) instead of nine launches, for as many elements as its
+// counters in LDS hold.  That workgroup walks the candidate list four times, so
+// the line depends on how long the list can get.  Below 2^17 values the chain is
+// the faster way for any list (N = 7, 128 elements, 3 components: noisy field at
+// tol 1e-3 124 us against 135, white noise at 0.5, most values in the list, 173
+// against 182).  At 2^17 to 2^18 values it still is where the tolerance is tight,
+// and the list with it (N = 7, 512 elements: noisy 153 against 156, white noise at
+// 0.01 169 against 171), but not at a loose one (white noise at 0.1 249 against
+// 219, at 0.5 326 against 260); above (1,024 elements) it is slower on both.
+inline bool chain_small(u64 nv, long long n_elem, double tol) {
+  return n_elem <= SCAN_CHUNK && (nv < (1ull << 17) || (nv <= (1ull << 18) && tol <= 1e-2));
+}
 hipError_t launch_chain(const Job& j, hipStream_t s);
 inline int scan_grid_elems(long long n_elem) {  // its workgroups per component
   const long long nch = (n_elem + SCAN_CHUNK - 1) / SCAN_CHUNK;

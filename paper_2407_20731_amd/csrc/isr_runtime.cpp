@@ -411,7 +411,7 @@ static int enqueue_fast(isr_ctx* c, const Job& j0, const Sizes& z, hipStream_t s
   rec(0);
   HIPCHK(launch_fast(F_PASSA, prec, j, j.gA, s));
   rec(1);
-  if (chain_small(z.nv, j.n_elem)) {
+  if (chain_small(z.nv, j.n_elem, j.tol)) {
     HIPCHK(launch_chain(j, s));
     rec(2);
     rec(3);
