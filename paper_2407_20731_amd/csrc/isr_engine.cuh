@@ -1345,6 +1345,10 @@ int resident_fast_prec(int kind, int order) {
       e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)k_passA<NN, PREC>, 256, 0);    \
     else if (kind == F_PASSB)                                                                            \
       e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)k_passB<NN, PREC>, 256, 0);    \
+    if constexpr (PREC == P_FP64) {                                                                      \
+      if (kind == F_QUANT)                                                                               \
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)k_quantW<NN>, 256, 0);        \
+    }                                                                                                    \
     break;
     ISR_FAST_ORDERS(CASE)
 #undef CASE

@@ -751,6 +751,7 @@ inline int resident_fast_g(int kind, int order) {
   case NN:                                                                                              \
     return resident_wgs(kind == F_SAMPLE  ? (const void*)k_sampleG<NN>                                  \
                         : kind == F_PASSA ? (const void*)k_passAG<NN>                                   \
+                        : kind == F_QUANT ? (const void*)k_quantG<NN>                                   \
                                           : (const void*)k_passBG<NN>);
     ISR_FAST_ORDERS_G(CASE)
 #undef CASE

@@ -219,7 +219,7 @@ hipError_t launch_refsel(const Job& j, int grid_x, hipStream_t s);  // levels 2.
 
 // Streaming path: wave tiles (isr_engine.cuh), dense tiles, large orders, and
 // workgroup tiles for FP64 above order 7.
-enum FastKind { F_SAMPLE = 0, F_PASSA = 1, F_PASSB = 2 };
+enum FastKind { F_SAMPLE = 0, F_PASSA = 1, F_PASSB = 2, F_QUANT = 3 };  // F_QUANT: FP64, residency only
 enum DoneSlot { D_SAMPLE = 0, D_GATHER = 1, D_COUNT = 2, D_PASSB = 3, D_REFSEL = 4 };  // D_REFSEL + level
 constexpr int FAST_MAX_ORDER = 7;     // wave tiles, every precision
 constexpr int FAST_MAX_ORDER_MF = 11; // FP32 / BF16 (large-order engine, isr_engine_l.cuh)

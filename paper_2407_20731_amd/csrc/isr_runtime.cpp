@@ -357,7 +357,8 @@ struct FastGrids {
   int gs, gl, rgx, gsc;  // sample, list passes (gather, count), refinement levels, offset scans
 };
 
-static FastGrids fast_setup(isr_ctx* c, Job& j, const Sizes& z) {
+// last: the kernel that j.gB and the per-workgroup sums are for, F_PASSB or F_QUANT.
+static FastGrids fast_setup(isr_ctx* c, Job& j, const Sizes& z, int last = F_PASSB) {
   const int nc = j.ncomp, prec = j.precision;
   const bool wide = wide_order(j.order, prec);
   const long long epw = wide ? shape_epi(j.order) : fast_epw(j.order, j.tile);
@@ -370,7 +371,7 @@ static FastGrids fast_setup(isr_ctx* c, Job& j, const Sizes& z) {
     return (int)std::max<long long>(1, std::min<long long>(g, FAST_GMAX));
   };
   j.gA = grid(F_PASSA);
-  j.gB = grid(F_PASSB);
+  j.gB = grid(last);
   // terms per lane: values per lane per tile (n at most in a workgroup tile)
   // times tiles per wave (workgroup)
   const long long per_wave = (ftiles + tpw * std::min(j.gA, j.gB) - 1) / (tpw * std::min(j.gA, j.gB));
@@ -1939,7 +1940,7 @@ int run_compress_quantized(isr_ctx* c, const isr_field* f, double share, isr_blo
   double* err_dev = (double*)(scr + hist_bytes + 256);
   // error terms into running sums bounded as pass B's
   j.slotsB = (long long*)(scr + hist_bytes + 512);
-  fast_setup(c, j, plan_sizes(f, 0));
+  fast_setup(c, j, plan_sizes(f, 0), F_QUANT);
   for (int k = 0; k < nc; ++k) {
     const double U2 = b->comp[k].U2;
     const int m = Bf[k] > 0.0 ? std::ilogb(Bf[k]) + 6 : (U2 > 0.0 ? std::ilogb(U2) - 80 : -876);

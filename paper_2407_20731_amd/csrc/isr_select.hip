@@ -313,9 +313,9 @@ hipError_t launch_fast(int kind, int precision, const Job& j, int gx, hipStream_
 }
 
 int resident_fast(int kind, int precision, int order, int tile) {
-  static int cache[3][3][16];
-  static int dcache[3][3][16][65];
-  if (kind < 0 || kind > 2 || precision < 0 || precision > 2 || !fast_order(order, precision)) return 1;
+  static int cache[4][3][16];
+  static int dcache[4][3][16][65];
+  if (kind < 0 || kind > 3 || (kind == F_QUANT && precision != ISR_PREC_FP64) || precision < 0 || precision > 2 || !fast_order(order, precision)) return 1;
   if (tile > 0) {
     if (precision == ISR_PREC_FP64 || tile > 64 || !dense_shape(order, tile)) return 1;
     int& d = dcache[kind][precision][order][tile];
