@@ -2016,9 +2016,9 @@ int run_compress_quantized(isr_ctx* c, const isr_field* f, double share, isr_blo
 }
 
 
-// Per-element cut: every element cut alone at ((tol*tol)*U2_e)*s_c; pass 3
-// of the general pipeline compacts, inverts and measures the exact error;
-// s_c follows the plain budget repair while rounding leaves rel above tol.
+// Per-element cut: every element cut alone at ((tol*tol)*U2_e)*s_c; the offset
+// scan and pass B of the streaming path compact, invert and measure the exact
+// error; s_c follows the plain budget repair while rounding leaves rel above tol.
 int run_compress_elemcut(isr_ctx* c, const isr_field* f, isr_blob** out, isr_stats* st) {
   *out = nullptr;
   int rc = check_field(f);
@@ -2049,11 +2049,12 @@ int run_compress_elemcut(isr_ctx* c, const isr_field* f, isr_blob** out, isr_sta
   const size_t o_zero = al(o_st + (size_t)nc * sizeof(CompState));  // digits, error bins
   const size_t o_hist = al(o_zero + elemcut_digit_bytes(nc));
   const size_t zero_end = al(o_hist + (size_t)nc * HBINS * sizeof(HistBin));
-  // kept counts, their scan and the error sums of pass B
-  const size_t o_cnt = al(zero_end), o_chunk = al(o_cnt + (size_t)nc * E * 4);
-  const size_t o_slots = al(o_chunk + (size_t)nc * ((E + SCAN_CHUNK - 1) / SCAN_CHUNK) * 8);
-  // (pass B has at most E workgroups a component)
-  const size_t scr_bytes = o_slots + (size_t)nc * std::min<long long>(FAST_GMAX, E) * 4 * 8;
+  // The error sums of pass B (at most E workgroups a component) take the
+  // coefficients' place, which the selection has read by then (and a repair
+  // computes again); without coefficients they have their own.
+  const bool own_coef = f->order != 7;
+  const size_t o_slots = own_coef ? o_coef : zero_end;
+  const size_t scr_bytes = zero_end + (own_coef ? 0 : (size_t)nc * std::min<long long>(FAST_GMAX, E) * 4 * 8);
   char* scr = b->dev ? (char*)c->arena->alloc(scr_bytes) : nullptr;
   if (!b->dev || !scr) {
     if (b->dev) c->arena->free(b->dev);
@@ -2086,16 +2087,15 @@ int run_compress_elemcut(isr_ctx* c, const isr_field* f, isr_blob** out, isr_sta
   j.values = b->values();
   j.voff = b->voff();
   j.tau_elem = (const double*)(scr + o_tau);
-  j.cnt = (u32*)(scr + o_cnt);
-  j.chunk = (u64*)(scr + o_chunk);
+  // kept counts and their scan: in the place of the values (at least 64 B an
+  // element), which pass B writes after the last of them is read
+  j.chunk = (u64*)b->values();
+  j.cnt = (u32*)((u64*)b->values() + (size_t)nc * ((E + SCAN_CHUNK - 1) / SCAN_CHUNK));
   j.nchunk = (E + SCAN_CHUNK - 1) / SCAN_CHUNK;
   j.slotsB = (long long*)(scr + o_slots);
   fast_setup(c, j, plan_sizes(f, 0));  // pass B's grid and headroom
   double* coef = (double*)(scr + o_coef);
   const int gfwd = (int)std::min<long long>(tiles * nc, (long long)c->num_cu * 8);
-  // (at N = 7 the selection transforms the elements itself)
-  if (f->order != 7 && launch_pass(K_FORWARD, ISR_PREC_FP64, j, gfwd, s, coef) != hipSuccess)
-    return give_up(fail(ISR_EDEVICE, "forward transform failed: %s", hipGetErrorString(hipGetLastError())));
   const int gsel = (int)std::max<long long>(1, std::min<long long>((E * nc + 3) / 4, (long long)c->num_cu * 8));
   double scale[ISR_MAX_COMP];
   for (int k = 0; k < ISR_MAX_COMP; ++k) scale[k] = 1.0;
@@ -2108,7 +2108,9 @@ int run_compress_elemcut(isr_ctx* c, const isr_field* f, isr_blob** out, isr_sta
       hs[k].n_values = (u64)(E * n3);
       hs[k].bstar = -1;
     }
-    if (hipMemcpyAsync(j.st, hs, nc * sizeof(CompState), hipMemcpyHostToDevice, s) != hipSuccess ||
+    // (at N = 7 the selection transforms the elements itself)
+    if ((own_coef && launch_pass(K_FORWARD, ISR_PREC_FP64, j, gfwd, s, coef) != hipSuccess) ||
+        hipMemcpyAsync(j.st, hs, nc * sizeof(CompState), hipMemcpyHostToDevice, s) != hipSuccess ||
         launch_zero(scr + o_zero, zero_end - o_zero, s) != hipSuccess ||
         launch_elemcut(j, coef, (double*)(scr + o_tau), (u64*)(scr + o_zero), scale, gsel, s) != hipSuccess ||
         launch_scan(j, s) != hipSuccess || launch_fast(F_PASSB, ISR_PREC_FP64, j, j.gB, s) != hipSuccess ||
