@@ -808,7 +808,7 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
     for (int s = 0; s < NS; ++s) {
       const bool v = G::valid(s, lane, ne);
       const double en = v ? wq[s] * (c[s] * c[s]) : 0.0;
-      keep[s] = v && en >= tau;
+      keep[s] = v && !(en < tau);  // (a NaN is kept: pass A counts it among the energies above)
     }
     if constexpr (G::n == 8) {
       // one element per tile and one 64-bit word per index r: the words come

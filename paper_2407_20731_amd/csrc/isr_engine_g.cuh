@@ -434,7 +434,7 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passBG(Job j) {
 #pragma unroll
     for (int r = 0; r < n; ++r) {
       const double en = (je * g3[r]) * (c[r] * c[r]);
-      if (act && en >= tau) {
+      if (act && !(en < tau)) {  // (a NaN is kept: pass A counts it among the energies above)
         keep |= 1u << r;
         const int f = r * n2 + ab;
         atomicOr((unsigned long long*)&L.bm[el * W + (f >> 6)], 1ull << (f & 63));
