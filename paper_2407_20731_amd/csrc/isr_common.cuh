@@ -40,14 +40,17 @@ DEV u64 bcast64(u64 v, int src) {
   u32 hi = (u32)__builtin_amdgcn_readlane((int)(u32)(v >> 32), src);
   return ((u64)hi << 32) | lo;
 }
-// v with lane DST's value replaced by the uniform s
+// v with lane DST's value replaced by the uniform s.  The compiler puts two wait
+// states between a vector instruction that writes a scalar register (a compare, a
+// lane read) and one that reads it, but does not look into inline assembly.
 template <int DST>
 DEV u64 writelane64(u64 s, u64 v) {
   u32 lo = (u32)v, hi = (u32)(v >> 32);
   const u32 slo = (u32)__builtin_amdgcn_readfirstlane((int)(u32)s);
   const u32 shi = (u32)__builtin_amdgcn_readfirstlane((int)(u32)(s >> 32));
-  asm("v_writelane_b32 %0, %1, %2" : "+v"(lo) : "s"(slo), "n"(DST));
-  asm("v_writelane_b32 %0, %1, %2" : "+v"(hi) : "s"(shi), "n"(DST));
+  asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4"
+      : "+v"(lo), "+v"(hi)
+      : "s"(slo), "s"(shi), "n"(DST));
   return ((u64)hi << 32) | lo;
 }
 DEV u64 shfl64(u64 v, int src) {
