@@ -53,11 +53,6 @@ DEV u64 writelane64(u64 s, u64 v) {
       : "s"(slo), "s"(shi), "n"(DST));
   return ((u64)hi << 32) | lo;
 }
-DEV u64 shfl64(u64 v, int src) {
-  u32 lo = (u32)__shfl((int)(u32)v, src);
-  u32 hi = (u32)__shfl((int)(u32)(v >> 32), src);
-  return ((u64)hi << 32) | lo;
-}
 DEV u64 shfl_xor64(u64 v, int m) {
   u32 lo = (u32)__shfl_xor((int)(u32)v, m);
   u32 hi = (u32)__shfl_xor((int)(u32)(v >> 32), m);

@@ -12,18 +12,18 @@
 //             (known up front: no look-back), inverse of the kept set, error
 //             sum; the last workgroup of a component finalizes it
 //
-// Exact sums without atomics: every lane splits each non-negative term x <= M
-// into three parts on fixed grids (error-free extraction against fixed powers
-// of two, Rump, Ogita and Oishi, "Accurate floating-point summation part I",
-// SIAM J. Sci. Comput. 31(1), 2008, Alg. 3.2) and keeps three FP64 running
-// sums that stay exact; the rare term that leaves a remainder (far below M or
-// above M) goes to the global exponent bins instead.  Workgroups publish
-// their three integer sums; the consumer turns the totals into exact bins.
-// The norm sum is exact on every path, so U2 is that of the FP64 field.  The
-// FP64 path sums the energies and the error terms the same way; the MFMA
-// paths, whose energies already carry the transform error, add them in a
-// fixed order per lane instead (one FP64 add a term) and split only each
-// lane's total on the grids, so their results stay deterministic.
+// Exact sums without atomics (isr_xsum.cuh): a non-negative term x <= M is split
+// into three parts on fixed grids by error-free extraction (Rump, Ogita and
+// Oishi, "Accurate floating-point summation part I", SIAM J. Sci. Comput. 31(1),
+// 2008, Alg. 3.2), added to three FP64 sums that stay exact.  On the FP64 path
+// every norm, energy and error term is split, against running sums biased to the
+// middle of a binade; terms far below M have a second set of sums, kept by the
+// wave in LDS, and what is outside that too (or above M) goes to the global
+// exponent bins.  The MFMA paths, whose energies already carry the transform
+// error, add terms in a fixed order per lane (one FP64 add a term) and split each
+// lane's total against fixed powers of two, so that their results stay
+// deterministic.  Workgroups publish their three integer sums; the consumer turns
+// the totals into exact bins.
 //
 // Transforms on MFMA use a block-diagonal trick for n <= 8: a 16x16 tile
 // holds two 8x8 copies of the 1D matrix, the K dimension pairs the contracted
@@ -388,7 +388,6 @@ DEV void sample_body(const Job& j, int comp, int vb, int nvb, SampleLds<N, PREC>
   typename G::Mats mt;
   G::init(mt, j.tab, lane);
   tab_load<G>(L.tab, j.tab, tid);
-  __syncthreads();
   __syncthreads();
   const long long E = j.n_elem, tiles = (E + EPW - 1) / EPW;
   const long long ss = j.sample_stride > 0 ? j.sample_stride : 1;

@@ -235,7 +235,9 @@ Sizes plan_sizes(const isr_field* f, int tile, bool full_lists, bool stream) {
   z.off_done = take(16 * 8 * sizeof(u32));
   z.zero_bytes = o;
   z.list_cap = full_lists || z.nv <= (1ull << 20) ? z.nv : std::max<u64>(z.nv / 8, 1ull << 20);
-  z.off_lists = take((size_t)nc * 2 * z.list_cap * 8);  // lists 0, then lists 1 (at most CAP entries each)
+  // lists 0, then lists 1 (at most CAP entries each); the room beyond those counts
+  // in the footprint by which requests are admitted and refused
+  z.off_lists = take((size_t)nc * 2 * z.list_cap * 8);
   z.fast = stream && fast_order(f->order, f->precision);
   z.tile = z.fast && f->precision != ISR_PREC_FP64 && dense_shape(f->order, tile) ? tile : 0;
   if (z.fast) {
