@@ -17,11 +17,11 @@
 // Oishi, "Accurate floating-point summation part I", SIAM J. Sci. Comput. 31(1),
 // 2008, Alg. 3.2), added to three FP64 sums that stay exact.  On the FP64 path
 // every norm, energy and error term is split, against running sums biased to the
-// middle of a binade; terms far below M have a second set of sums, kept by the
-// wave in LDS, and what is outside that too (or above M) goes to the global
-// exponent bins.  The MFMA paths, whose energies already carry the transform
-// error, add terms in a fixed order per lane (one FP64 add a term) and split each
-// lane's total against fixed powers of two, so that their results stay
+// middle of a binade; a tile's terms far below M are summed in the same manner
+// against bounds of their own into digits in LDS, and only a term above M goes to
+// the global exponent bins.  The MFMA paths, whose energies already carry the
+// transform error, add terms in a fixed order per lane (one FP64 add a term) and
+// split each lane's total against fixed powers of two, so that their results stay
 // deterministic.  Workgroups publish their three integer sums; the consumer turns
 // the totals into exact bins.
 //
@@ -468,7 +468,7 @@ struct PassALds {
   u64 key[4][CAPB];
   u32 idx[4][CAPB];
   u32 ecnt[4][16];
-  XLow low[PREC == P_FP64 ? 2 : 1][4];  // FP64 path: norm terms, energies
+  XFar far[PREC == P_FP64 ? 2 : 1];  // FP64 path: norm terms, energies
   long long red[4][8];
 };
 
@@ -514,13 +514,13 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
   typename G::Mats mt;
   G::init(mt, j.tab, lane);
   tab_load<G>(L.tab, j.tab, tid);
+  if constexpr (EXACT) {
+    xfar_clear(L.far[0], tid);
+    xfar_clear(L.far[1], tid);
+  }
   __syncthreads();
   XAcc an = {0.0, 0.0, 0.0}, ae = {0.0, 0.0, 0.0};
   XRun rn = xrun(PN), re = xrun(PE);  // FP64 path
-  if constexpr (EXACT) {
-    xlow_clear(&L.low[0][wv], lane);
-    xlow_clear(&L.low[1][wv], lane);
-  }
   double pe = 0.0;  // fixed-order sum of the energies below the window
   double pn = 0.0;  // MFMA paths: fixed-order sum of the norm terms
   u64 hi_tot = 0ull;
@@ -593,7 +593,7 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
     }
     if constexpr (EXACT) {
       if (odd)  // (one vote a tile keeps this out of the slots' way)
-        xlow_tile<EPW * G::n2, NS, true>(L.low[0], xlow_m(PN.m, j.xh), gN, L.buf, xs, [&](double x) { return !xin(RN, x); });
+        xfar_tile<EPW * G::n2, NS, true>(L.far[0], xfar_m(PN.m, j.xh), gN, L.buf, xs, [&](double x) { return !xin(RN, x); });
       odd = 0ull;
     }
     if constexpr (EXACT) pin(rn);
@@ -658,7 +658,7 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
     if constexpr (EXACT) pin(re);
     if constexpr (EXACT) {
       if (odd)
-        xlow_tile<EPW * G::n2, NS, true>(L.low[1], xlow_m(PE.m, j.xh), gE, L.buf, xs, [&](double x) { return hi_word(x) < RE.lo; });
+        xfar_tile<EPW * G::n2, NS, true>(L.far[1], xfar_m(PE.m, j.xh), gE, L.buf, xs, [&](double x) { return hi_word(x) < RE.lo; });
     }
     if (hmax >= 0x7ff00000u) slow_bin(gE, __builtin_inf());  // Inf/NaN: counted in the flag bin
     hi_tot += hc;
@@ -702,8 +702,8 @@ DEV void passA_body(const Job& j, int comp, int vb, int nvb, PassALds<N, PREC>& 
   block_sum_i64<7>(v, L.red, tid);
   if (tid < 7) j.slotsA[((size_t)comp * j.gA + vb) * 8 + tid] = L.red[0][tid];
   if constexpr (EXACT) {
-    if (tid == 0) xlow_out(L.low[0], gN, xlow_m(QN.m, j.xh));
-    if (tid == 64 && wlo < whi) xlow_out(L.low[1], gE, xlow_m(QE.m, j.xh));
+    xfar_out(L.far[0], gN, tid);
+    if (wlo < whi) xfar_out(L.far[1], gE, tid - 64);
   }
 }
 
@@ -720,7 +720,7 @@ struct PassBLds {
   TabLds tab;
   u64 bm[4][16];
   u32 wp[4][16];
-  XLow low[4];  // FP64 path: error terms
+  XFar far;  // FP64 path: error terms
   long long red[4][8];
   __int128 r3[4][3];
   int last;
@@ -751,11 +751,11 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
   typename G::Mats mt;
   G::init(mt, j.tab, lane);
   tab_load<G>(L.tab, j.tab, tid);
+  if constexpr (EXACT) xfar_clear(L.far, tid);
   __syncthreads();
   XAcc ar = {0.0, 0.0, 0.0};
   const XRange RR = xrange(PR);  // FP64 path
   XRun rr = xrun(PR);
-  if constexpr (EXACT) xlow_clear(&L.low[wv], lane);
   double pr = 0.0;  // fixed-order sum of the error terms
   bool bad = false;
   const double* ub = j.u + (size_t)comp * j.comp_stride;
@@ -959,7 +959,7 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
     if constexpr (EXACT) pin(rr);
     if constexpr (EXACT) {
       if (odd)
-        xlow_tile<EPW * G::n2, NS, false>(L.low, xlow_m(PR.m, j.xh), gR, L.buf, xs, [&](double x) { return !xin(RR, x); });
+        xfar_tile<EPW * G::n2, NS, false>(L.far, xfar_m(PR.m, j.xh), gR, L.buf, xs, [&](double x) { return !xin(RR, x); });
     }
   }
   if (ballot(bad)) {
@@ -976,9 +976,7 @@ DEV void passB_body(const Job& j, int comp, int vb, int nvb, PassBLds<N, PREC>& 
   xints(ar, QR, v);
   block_sum_i64<3>(v, L.red, tid);
   if (tid < 3) j.slotsB[((size_t)comp * j.gB + vb) * 4 + tid] = L.red[0][tid];
-  if constexpr (EXACT) {
-    if (tid == 0) xlow_out(L.low, gR, xlow_m(QR.m, j.xh));
-  }
+  if constexpr (EXACT) xfar_out(L.far, gR, tid);
   if (!tail || !last_block(j.done + D_PASSB * 8 + comp, &L.last, nvb)) return;
   passB_tail(j, comp, L.r3);
 }
@@ -1169,7 +1167,7 @@ struct QuantWLds {
   double w3[8][64], sq[8][64];  // quadrature weights of field slots, sqrt(g3) of coefficient slots
   u64 bm[4][16];
   u32 wp[4][16];
-  XLow low[4];
+  XFar far;  // error terms
   long long red[4][8];
 };
 
@@ -1186,6 +1184,7 @@ __global__ __launch_bounds__(256, 3) void k_quantW(Job j) {
     L.w3[s][l] = v ? j.tab.w3[G::w3i(s, l)] : 0.0;
     L.sq[s][l] = v ? __builtin_sqrt(j.tab.g3[G::g3i(s, l)]) : 1.0;
   }
+  xfar_clear(L.far, tid);
   __syncthreads();
   const typename G::Mats mt{};
   const long long E = j.n_elem, tiles = (E + EPW - 1) / EPW, nw = (long long)gridDim.x * 4;
@@ -1198,7 +1197,6 @@ __global__ __launch_bounds__(256, 3) void k_quantW(Job j) {
   const XParm PR = xparm(j.qxm[comp], j.xh);
   const XRange RR = xrange(PR);
   XRun rr = xrun(PR);
-  xlow_clear(&L.low[wv], lane);
   HistBin* gR = j.histR + (size_t)comp * HBINS;
   bool big = false;
   double un[NS];
@@ -1242,7 +1240,7 @@ __global__ __launch_bounds__(256, 3) void k_quantW(Job j) {
     }
     pin(rr);
     if (odd)
-      xlow_tile<EPW * G::n2, NS, false>(L.low, xlow_m(PR.m, j.xh), gR, L.buf, xs, [&](double x) { return !xin(RR, x); });
+      xfar_tile<EPW * G::n2, NS, false>(L.far, xfar_m(PR.m, j.xh), gR, L.buf, xs, [&](double x) { return !xin(RR, x); });
   }
   if (big) atomicOr(&j.ticket[1], 1u);
   const XParm QR = xparm(again(PR.m), j.xh);
@@ -1250,7 +1248,7 @@ __global__ __launch_bounds__(256, 3) void k_quantW(Job j) {
   xints(xrun_sums(rr, QR), QR, v);
   block_sum_i64<3>(v, L.red, tid);
   if (tid < 3) j.slotsB[((size_t)comp * j.gB + blockIdx.x) * 4 + tid] = L.red[0][tid];
-  if (tid == 0) xlow_out(L.low, gR, xlow_m(QR.m, j.xh));
+  xfar_out(L.far, gR, tid);
 }
 
 // Grid of a decompression: gx workgroups per component cover its tiles once;

@@ -222,7 +222,7 @@ __global__ __launch_bounds__(256, 2) void k_sampleG(Job j) {
 }
 
 // slots of terms out of the running sums' range that are staged at a time
-constexpr int XL_CH = 4;
+constexpr int XF_CH = 8;
 
 // ---- pass A -------------------------------------------------------------------
 template <int N>
@@ -231,8 +231,8 @@ struct PassALdsG {
   u64 key[4][CAPB];
   u32 idx[4][CAPB];
   u32 ecnt[4];
-  XLow low[2][4];  // norm terms, energies
-  double far[4][64 * XL_CH];
+  XFar far[2];  // norm terms, energies
+  double stage[4][64 * XF_CH];
   long long red[4][8];
 };
 
@@ -266,8 +266,9 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passAG(Job j) {
   u32 ncap = 0u;
   double u[PER];
   if (tid < 4) L.ecnt[tid] = 0u;
-  xlow_clear(&L.low[0][wv], lane);
-  xlow_clear(&L.low[1][wv], lane);
+  xfar_clear(L.far[0], tid);
+  xfar_clear(L.far[1], tid);
+  __syncthreads();
   long long t = blockIdx.x;
   auto fetch = [&](long long tt) {
     const long long e0 = tt * EPI;
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passAG(Job j) {
         const int idx = dt + 256 * k;
         xn[k] = idx < ne * n3 ? jw(j.jac, e0 + idx / n3, w3[k]) * (u[k] * u[k]) : 0.0;
       }
-      xlow_tile<64, XL_CH, true>(L.low[0], xlow_m(PN.m, j.xh), gN, L.far, xn, [&](double x) { return !xin(RN, x); });
+      xfar_tile<64, XF_CH, true>(L.far[0], xfar_m(PN.m, j.xh), gN, L.stage, xn, [&](double x) { return !xin(RN, x); });
     }
     odd = 0ull;
     G::store(L.w, u, dt);
@@ -338,7 +339,7 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passAG(Job j) {
       double xe[n];
 #pragma unroll
       for (int r = 0; r < n; ++r) xe[r] = act ? (je * g3[r]) * (c[r] * c[r]) : 0.0;
-      xlow_tile<64, XL_CH, true>(L.low[1], xlow_m(PE.m, j.xh), gE, L.far, xe, [&](double x) { return hi_word(x) < RE.lo; });
+      xfar_tile<64, XF_CH, true>(L.far[1], xfar_m(PE.m, j.xh), gE, L.stage, xe, [&](double x) { return hi_word(x) < RE.lo; });
     }
     if (hmax >= 0x7ff00000u) slow_bin(gE, __builtin_inf());  // Inf/NaN: counted in the flag bin
     hi_tot += hmine;
@@ -365,8 +366,8 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passAG(Job j) {
   v[6] = (long long)hi_tot;
   block_sum_i64<7>(v, L.red, tid);
   if (tid < 7) j.slotsA[((size_t)comp * j.gA + blockIdx.x) * 8 + tid] = L.red[0][tid];
-  if (tid == 0) xlow_out(L.low[0], gN, xlow_m(QN.m, j.xh));
-  if (tid == 64 && wlo < whi) xlow_out(L.low[1], gE, xlow_m(QE.m, j.xh));
+  xfar_out(L.far[0], gN, tid);
+  if (wlo < whi) xfar_out(L.far[1], gE, tid - 64);
 }
 
 // ---- pass B -------------------------------------------------------------------
@@ -375,8 +376,8 @@ struct PassBLdsG {
   double w[EngG<N>::LDSW];
   u64 bm[64];  // the tile's bitmap words
   u32 wp[64];  // kept values before each word
-  XLow low[4];  // error terms
-  double far[4][64 * XL_CH];
+  XFar far;  // error terms
+  double stage[4][64 * XF_CH];
   long long red[4][8];
 };
 
@@ -385,7 +386,7 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passBG(Job j) {
   typedef EngG<N> G;
   constexpr int n = G::n, n2 = G::n2, n3 = G::n3, EPI = G::EPI, PER = G::PER, W = G::W;
   __shared__ PassBLdsG<N> L;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, comp = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63, comp = blockIdx.y;
   const int el = tid / n2, a = (tid % n2) / n, b = tid % n;
   CompState* st = j.st + comp;
   if (st->flags & ST_MISS) return;
@@ -406,7 +407,7 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passBG(Job j) {
   XRun rr = xrun(PR);
   bool bad = false;
   if (tid < 64) L.bm[tid] = 0ull;
-  xlow_clear(&L.low[wv], lane);
+  xfar_clear(L.far, tid);  // (before the first tile's first barrier)
   double un[PER];
   long long t = blockIdx.x;
   auto fetch = [&](long long tt) {
@@ -493,7 +494,7 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passBG(Job j) {
     }
     pin(rr);
     if (odd)
-      xlow_tile<64, XL_CH, true>(L.low, xlow_m(PR.m, j.xh), gR, L.far, xs, [&](double x) { return !xin(RR, x); });
+      xfar_tile<64, XF_CH, true>(L.far, xfar_m(PR.m, j.xh), gR, L.stage, xs, [&](double x) { return !xin(RR, x); });
   }
   if (ballot(bad)) {
     if (lane == 0) atomicOr(&st->flags, ST_LIST);
@@ -503,7 +504,7 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passBG(Job j) {
   xints(xrun_sums(rr, QR), QR, v);
   block_sum_i64<3>(v, L.red, tid);
   if (tid < 3) j.slotsB[((size_t)comp * j.gB + blockIdx.x) * 4 + tid] = L.red[0][tid];
-  if (tid == 0) xlow_out(L.low, gR, xlow_m(QR.m, j.xh));
+  xfar_out(L.far, gR, tid);
 }
 
 // ---- reading kept values back ----------------------------------------------------
@@ -605,8 +606,8 @@ __global__ __launch_bounds__(256, 2) void k_decompG(Job j, void* out) {
 // components: 266 -> 92 us.
 template <int N>
 struct QuantLdsG : WordLdsG<N> {
-  XLow low[4];  // error terms
-  double far[4][64 * XL_CH];
+  XFar far;  // error terms
+  double stage[4][64 * XF_CH];
   long long red[4][8];
 };
 
@@ -631,7 +632,7 @@ __global__ __launch_bounds__(256, 2) void k_quantG(Job j) {
   g_weights<G>(j.tab, w3, sq, tid, a, b);
 #pragma unroll
   for (int r = 0; r < n; ++r) sq[r] = __builtin_sqrt(sq[r]);
-  xlow_clear(&L.low[tid >> 6], tid & 63);
+  xfar_clear(L.far, tid);  // (before the first tile's first barrier)
   bool big = false;
   u64 wnext = 0ull, bnext = 0ull;
   auto fetch = [&](long long tt) {
@@ -675,7 +676,7 @@ __global__ __launch_bounds__(256, 2) void k_quantG(Job j) {
     }
     pin(rr);
     if (odd)
-      xlow_tile<64, XL_CH, true>(L.low, xlow_m(PR.m, j.xh), gR, L.far, xs, [&](double x) { return !xin(RR, x); });
+      xfar_tile<64, XF_CH, true>(L.far, xfar_m(PR.m, j.xh), gR, L.stage, xs, [&](double x) { return !xin(RR, x); });
   }
   if (big) atomicOr(&j.ticket[1], 1u);
   const XParm QR = xparm(again(PR.m), j.xh);
@@ -683,7 +684,7 @@ __global__ __launch_bounds__(256, 2) void k_quantG(Job j) {
   xints(xrun_sums(rr, QR), QR, v);
   block_sum_i64<3>(v, L.red, tid);
   if (tid < 3) j.slotsB[((size_t)comp * j.gB + blockIdx.x) * 4 + tid] = L.red[0][tid];
-  if (tid == 0) xlow_out(L.low, gR, xlow_m(QR.m, j.xh));
+  xfar_out(L.far, gR, tid);
 }
 
 // ---- launchers ------------------------------------------------------------------

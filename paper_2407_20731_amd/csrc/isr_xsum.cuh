@@ -5,9 +5,8 @@
 // fixed grids by error-free extraction against powers of two (Rump, Ogita and
 // Oishi, "Accurate floating-point summation part I", SIAM J. Sci. Comput.
 // 31(1), 2008, Alg. 3.2) and keeps three FP64 running sums, which stay exact
-// while a lane adds at most 2^(h-1) terms.  Terms far below M go to a second set
-// of sums (XLow) and only what is left of them, or above M, to the global
-// exponent bins.
+// while a lane adds at most 2^(h-1) terms.  Terms far below M are summed by
+// themselves (XFar); terms above it go to the global exponent bins.
 // Workgroups publish the three sums as integers; the consumer adds them up
 // as 128-bit integers and writes the exact total into exponent bins.  On the
 // FP64 path every term is split this way; on the MFMA paths a lane first adds
@@ -80,7 +79,7 @@ DEV void slow_bin(HistBin* g, double v) {
 // accumulators stay in their binades (a1 in [2^(m+h), 1.5 2^(m+h)], grid u1;
 // a2 within 2^(m+2h-54) of 1.5 2^(m+2h-53), grid 2 u2) and |a3| stays within
 // 2^52 u3.  Terms outside the range (at h = 12 those below 2^-71 of the bound)
-// are left to XLow: next to none of a noisy field's, a quarter to three quarters of
+// are left to XFar: next to none of a noisy field's, a quarter to three quarters of
 // a smooth field's energies.  N = 7, 65,536 elements, FP64: pass A 517 -> 360 us,
 // pass B 517 -> 468 us, with the registers that the shorter sums free.
 struct XRun {
@@ -117,7 +116,7 @@ DEV void xrun_add(XRun& A, double y) {
 DEV void pin(XRun& A) { asm volatile("" : "+v"(A.a1), "+v"(A.a2), "+v"(A.a3)); }
 
 // Adds x when it is in range; otherwise true: unless it is zero, x belongs in the
-// sums below (XLow) or in the exact bins.
+// sums below (XFar) or, too large, in the exact bins.
 DEV bool xrun_left(XRun& A, const XRange& R, double x) {
   const bool in = xin(R, x);
   xrun_add(A, in ? x : 0.0);
@@ -265,23 +264,31 @@ DEV u64 total_words(const __int128 (&K)[3], int m, int h) {
   return w;
 }
 
-// Terms below the running sums' range: a second set of three sums with M' =
-// 2^xlow_m, held by the wave in LDS as 128-bit integers and fed a tile at a time.
-// Smooth fields live on it (the energies that are rounding noise, the errors of
-// elements that keep everything): a global atomic or three each into the exact
-// bins, on a few dozen of them, made the request 164 ms at N = 9, 32,768
-// elements, Taylor-Green, FP64, 3 components, where it takes 1.95 ms so (noisy
-// field: 1.54); N = 7, 65,536 elements 72.4 -> 1.33 ms (0.92).  A term below this
-// range too (2^-74 of M') still goes to the bins.
-constexpr int XL_H = 11;  // at most 2^10 terms a tile: sixteen a lane
+// Terms below the running sums' range, a tile's at a time: three sums as above, over
+// the whole wave, take those within 77 binades of the range's end; if terms are left,
+// the largest of them sets the bound of the next three, and so on.  Each total goes
+// into 32-bit digits in LDS, of the workgroup, which cover all exponents.
+// Smooth fields live on this (energies that are rounding noise, and the noise of the
+// noise where the field does not vary along an axis; errors of elements that keep
+// everything): a global atomic or three each into the exact bins, on a few dozen
+// of them, made the request 164 ms at N = 9, 32,768 elements, Taylor-Green, FP64, 3
+// components, where it takes 2.15 ms so (noisy field: 1.53); N = 7, 65,536 elements
+// 72.4 -> 1.38 ms (0.92).  One second set of three sums alone took 1.95 and 1.33 ms,
+// but left what is far below that range too to the bins: 393 elements of N = 10,
+// Taylor-Green in a plane, 1235 us where it takes 221 (noisy 190); 719 of N = 8,
+// noisy X 1e-150, per-element cut 26.3 ms where it takes 0.17.
+constexpr int XF_H = 10;    // at most 2^9 terms: eight a lane
+constexpr int XF_DIG = 62;  // terms below 2^XM_MAX
 
-struct XLow {
-  u64 w[3][2];
+DEV int xfar_m(int m, int h) { return m + 3 * h - 107; }
+
+struct XFar {
+  u64 d[XF_DIG];  // digit k counts 2^(32 k) X units of 2^-1075 (room for 2^32 carries)
 };
 
-DEV int xlow_m(int m, int h) { return m + 3 * h - 107; }
-DEV void xlow_clear(XLow* L, int lane) {
-  if (lane < 6) L->w[lane >> 1][lane & 1] = 0ull;
+// (by the whole workgroup, ahead of a barrier)
+DEV void xfar_clear(XFar& F, int tid) {
+  if (tid < XF_DIG) F.d[tid] = 0ull;
 }
 
 // The thread's number hidden from the compiler (no address made from it is kept
@@ -292,16 +299,76 @@ DEV int again_tid() {
   return t;
 }
 
-// One tile's terms x, of the first LANES lanes (zero in the others), into this
-// wave's sums of low[4], those with out(x) (by the whole wave).  m: xlow_m.
-// ZEROS: called for tiles that only have exact zeros there too.  By way of the
-// wave's LDS buffer, CH slots at a time and in a rolled loop: unrolled on
-// registers this branch took the prefetched tile's (N = 7, 65,536 elements, noisy
-// field: the request 911 us without the branch, 1217 with it unrolled, 917 so).
+// The k slots of terms in the wave's LDS buffer (the first LANES lanes; zero in the
+// others), those with out(x), by the whole wave; m: the running sums take from 2^m on.
+template <int LANES, class OUT>
+DEV void xfar_sum(XFar& F, HistBin* g, const double* buf, int k, int lane, int m, OUT out) {
+  auto term = [&](int s) {
+    const double v = LANES == 64 || lane < LANES ? buf[LANES * s + lane] : 0.0;
+    return out(v) ? v : 0.0;
+  };
+  u64 limit = dbits(pow2(m));  // terms not yet taken are below
+#pragma unroll 1
+  for (bool first = true;; first = false) {
+    const int up = m < XM_MIN ? 256 : 0;  // (scaled, exactly, so that every unit is normal)
+    const XParm P = xparm(m + up, XF_H);
+    const XRange R = xrange(P);
+    const double scale = pow2(up);
+    XRun A = xrun(P);
+    bool rest = false;
+#pragma unroll 1
+    for (int s = 0; s < k; ++s) {
+      const double v = term(s);
+      const u64 b = dbits(v);
+      if (first && b >= limit) slow_bin(g, v);  // (above the running sums' range, Inf, NaN)
+      const double y = b < limit ? v * scale : 0.0;
+      const bool in = xin(R, y);
+      xrun_add(A, in ? y : 0.0);
+      rest = (!in && y != 0.0) || rest;
+    }
+    // multiples of a unit, below 2^53 of it: the wave's sums are exact too
+    const XAcc S = xrun_sums(A, P);
+    const XAcc T = {wave_sum_dpp(S.a1), wave_sum_dpp(S.a2), wave_sum_dpp(S.a3)};
+    long long K[3];
+    xints(T, P, K);
+    I192 z = {{0ull, 0ull, 0ull}};
+    i192_add_shl(z, (__int128)K[0], 107 - 2 * XF_H);
+    i192_add_shl(z, (__int128)K[1], 53 - XF_H);
+    i192_add_shl(z, (__int128)K[2], 0);
+    int at = m + 3 * XF_H + 916;  // u3 in X units; z has no bits below the first of those
+    for (; at < 0; ++at) {
+      z.w[0] = (z.w[0] >> 1) | (z.w[1] << 63);
+      z.w[1] = (z.w[1] >> 1) | (z.w[2] << 63);
+      z.w[2] >>= 1;
+    }
+    const int r = at & 63;
+    const u64 w0 = z.w[0] << r, w1 = r ? (z.w[1] << r) | (z.w[0] >> (64 - r)) : z.w[1],
+              w2 = r ? (z.w[2] << r) | (z.w[1] >> (64 - r)) : z.w[2], w3 = r ? z.w[2] >> (64 - r) : 0ull;
+    const u64 w = lane < 4 ? (lane < 2 ? w0 : w1) : (lane < 6 ? w2 : w3);
+    const u64 digit = lane & 1 ? w >> 32 : w & 0xffffffffull;
+    if (lane < 8 && digit) atomicAdd((unsigned long long*)&F.d[2 * (at >> 6) + lane], (unsigned long long)digit);
+    if (!ballot(rest)) return;
+    limit = dbits(ldexp(1.0, m + 3 * XF_H - 107));
+    u64 mk = 0ull;
+#pragma unroll 1
+    for (int s = 0; s < k; ++s) {
+      const u64 b = dbits(term(s));
+      mk = b < limit && b > mk ? b : mk;
+    }
+    m = (int)(wave_max_dpp(mk) >> 52) - 1022;  // every term left is below 2^m
+  }
+}
+
+// One tile's terms x of the first LANES lanes (zero in the others), those with
+// out(x).  m: xfar_m of the running sums.  ZEROS: called for tiles that only have
+// exact zeros there too.  By way of the wave's LDS buffer, CH slots at a time, and
+// in rolled loops: unrolled on registers this branch took the prefetched tile's
+// (N = 7, 65,536 elements, noisy field: the request 911 us without the branch, 1217
+// with it unrolled, 917 so).
 template <int LANES, int CH, bool ZEROS, int CNT, int LDSW, class OUT>
-DEV void xlow_tile(XLow* low, int m, HistBin* g, double (*bufs)[LDSW], const double (&x)[CNT], OUT out) {
+DEV void xfar_tile(XFar& F, int m, HistBin* g, double (*bufs)[LDSW], const double (&x)[CNT], OUT out) {
   static_assert(CH * LANES <= LDSW, "the terms fit the wave's buffer");
-  static_assert(CNT * 64 <= 1 << (XL_H - 1), "the wave's sums of a tile are exact");
+  static_assert(CH * 64 <= 1 << (XF_H - 1), "the wave's sums are exact");
   if constexpr (ZEROS) {
     bool any = false;
 #pragma unroll
@@ -310,11 +377,6 @@ DEV void xlow_tile(XLow* low, int m, HistBin* g, double (*bufs)[LDSW], const dou
   }
   const int tid = again_tid(), lane = tid & 63;
   double* buf = bufs[tid >> 6];
-  m = again(m);
-  const XParm P = xparm(m < XM_MIN ? XM_MIN : m, XL_H);
-  XRange R = xrange(P);
-  if (m < XM_MIN) R.span = 0u;  // (no room for normal units: every term to the bins)
-  XRun A = xrun(P);
 #pragma unroll
   for (int c = 0; c < CNT; c += CH) {
     const int k = CNT - c < CH ? CNT - c : CH;
@@ -322,40 +384,20 @@ DEV void xlow_tile(XLow* low, int m, HistBin* g, double (*bufs)[LDSW], const dou
     for (int s = 0; s < k; ++s)
       if (LANES == 64 || lane < LANES) buf[LANES * s + lane] = x[c + s];
     asm volatile("" ::: "memory");
-#pragma unroll 1
-    for (int s = 0; s < k; ++s) {
-      double v = LANES == 64 || lane < LANES ? buf[LANES * s + lane] : 0.0;
-      v = out(v) ? v : 0.0;
-      if (xrun_left(A, R, v)) slow_bin(g, v);
-    }
+    xfar_sum<LANES>(F, g, buf, k, lane, again(m), out);
     asm volatile("" ::: "memory");
-  }
-  // multiples of a unit, below 2^53 of it: the wave's sums are exact too
-  const XAcc S = xrun_sums(A, P);
-  const double a1 = wave_sum_dpp(S.a1), a2 = wave_sum_dpp(S.a2), a3 = wave_sum_dpp(S.a3);
-  const int e = lane == 0 ? P.m + P.h - 52 : (lane == 1 ? P.m + 2 * P.h - 106 : P.m + 3 * P.h - 159);
-  const long long k = (long long)ldexp(lane == 0 ? a1 : (lane == 1 ? a2 : a3), -e);
-  XLow* L = low + (tid >> 6);
-  if (lane < 3) {
-    const u64 lo = L->w[lane][0] + (u64)k;
-    L->w[lane][1] += (u64)(k >> 63) + (lo < (u64)k ? 1ull : 0ull);
-    L->w[lane][0] = lo;
   }
 }
 
-// The four waves' sums into the exact bins, all of it in bins below M' (by one
-// thread, behind a barrier).
-DEV void xlow_out(const XLow* L, HistBin* g, int m) {
-  __int128 K[3];
-  u64 any = 0ull;
-  for (int k = 0; k < 3; ++k) {
-    K[k] = 0;
-    for (int w = 0; w < 4; ++w) {
-      K[k] += (__int128)(((unsigned __int128)L[w].w[k][1] << 64) | L[w].w[k][0]);
-      any |= L[w].w[k][0] | L[w].w[k][1];
-    }
-  }
-  if (any) emit_total(g, K, m, XL_H, m + 1022);
+// The workgroup's digits into the exact bins, each in a bin below its own magnitude
+// (by the whole workgroup, behind a barrier).
+DEV void xfar_out(const XFar& F, HistBin* g, int tid) {
+  if ((u32)tid >= (u32)XF_DIG) return;
+  const u64 v = F.d[tid];
+  if (tid == 0)
+    add_piece(g, 1, v >> 1);
+  else
+    add_piece(g, 32 * tid - 20, (unsigned __int128)v << 20);
 }
 
 DEV long long wave_sum_i64(long long v) { return (long long)wave_sum64((u64)v); }

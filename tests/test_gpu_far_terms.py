@@ -110,3 +110,61 @@ def test_exact_sums_of_the_variants(order, n_elem):
                 for h, r in zip(blob.arrays().comps, ref):
                     assert (h["U2"], h["dropped"], h["err2"], h["kept"]) == (r.U2, r.dropped, r.err2, r.kept), name
                 blob.free()
+
+
+def _far_fields(order, n_elem):
+    """Fields whose terms lie at many exponents: constant along an axis (the noise
+    of the noise), constant on each element, far below one."""
+    n = order + 1
+    rng = np.random.default_rng(7 * order + n_elem)
+    plane = _taylor_green(n_elem, order)[:1] + np.zeros((3, 1, 1, 1, 1))
+    plane[:] = plane[:, :, :1]  # (does not vary along the slowest axis)
+    steps = np.repeat(rng.standard_normal((3, n_elem, 1, 1, 1)), n ** 3, axis=-1).reshape(3, n_elem, n, n, n)
+    return {"plane": plane, "steps": steps, "tiny": synth.field(n_elem, order) * 1e-150}
+
+
+@pytest.mark.parametrize("order", [1, 3, 4, 6, 7, 8, 10, 12, 15])
+def test_far_terms_of_all_exponents_take_no_longer(order):
+    E = (1 << 19) // (order + 1) ** 3
+    noisy = torch.from_numpy(synth.field(E, order)).cuda()
+    with isr.Context(device=0) as ctx:
+        for call in ("compress", "compress_quantized", "compress_elemcut"):
+            def seconds(u):
+                best = float("inf")
+                for _ in range(5):
+                    torch.cuda.synchronize()
+                    t = time.perf_counter()
+                    if call == "compress":
+                        ctx.compress(u, order, 1e-3, "fp64").free()
+                    elif call == "compress_quantized":
+                        ctx.compress_quantized(u, order, 1e-3, 0.5).free()
+                    else:
+                        ctx.compress_elemcut(u, order, 1e-3).free()
+                    torch.cuda.synchronize()
+                    best = min(best, time.perf_counter() - t)
+                return best
+
+            bound = SLOWER * seconds(noisy)
+            for name, u in _far_fields(order, E).items():
+                assert seconds(torch.from_numpy(np.ascontiguousarray(u)).cuda()) < bound, (call, name)
+
+
+@pytest.mark.parametrize("order,n_elem", CASES)
+def test_far_terms_of_all_exponents_are_exact(order, n_elem):
+    rng = np.random.default_rng(order)
+    wide = rng.standard_normal((1, n_elem) + (order + 1,) * 3) * 2.0 ** rng.integers(
+        -500, 1, size=(1, n_elem) + (order + 1,) * 3)
+    fields = {**_far_fields(order, n_elem), "wide": wide, "wide, large": wide * 2.0 ** 380}
+    with isr.Context(device=0) as ctx:
+        for name, u in fields.items():
+            u = np.ascontiguousarray(u)
+            d = torch.from_numpy(u).cuda()
+            todo = [(ctx.compress(d, order, tol, "fp64"), oracle.compress(u, order, tol, keep_arrays=True).comps)
+                    for tol in (1e-3, -1.0)]
+            if not name.startswith("wide"):
+                todo += [(ctx.compress_quantized(d, order, 1e-3, 0.5), Q.compress_quantized(u, order, 1e-3, 0.5)),
+                         (ctx.compress_elemcut(d, order, 1e-3), P.compress_elemcut(u, order, 1e-3))]
+            for blob, ref in todo:
+                for h, r in zip(blob.arrays().comps, ref):
+                    assert (h["U2"], h["dropped"], h["err2"], h["kept"]) == (r.U2, r.dropped, r.err2, r.kept), name
+                blob.free()
