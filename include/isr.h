@@ -166,8 +166,9 @@ typedef struct {
                                     sampled window); 2: the same, inside the
                                     persistent batch launch; 0: general
                                     pipeline (orders without a streaming path,
-                                    or the window missed and the request was
-                                    rerun) */
+                                    a window that missed and the request was
+                                    rerun, or FP64 of order 8 to 15 with a
+                                    budget for every energy) */
 } isr_stats;
 
 /* Create a context on cfg->device (cfg may be NULL: device 0, defaults).

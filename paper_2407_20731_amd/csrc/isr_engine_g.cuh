@@ -236,6 +236,17 @@ struct PassALdsG {
   long long red[4][8];
 };
 
+// Whether the sample has left a component without a window (all sampled energies
+// zero, or all within the budget): the request then goes to the general pipeline
+// as a whole, and no component's pass is worth its time (N = 8, 5,753 elements, one of
+// 3 components all zero: 1054 -> 925 us; 89 elements: 302 -> 253).
+DEV bool no_window(const Job& j) {
+  if (j.tol < 0.0) return false;
+  for (int c = 0; c < j.ncomp; ++c)
+    if (j.st[c].win_lo >= j.st[c].win_hi) return true;
+  return false;
+}
+
 template <int N>
 __global__ __launch_bounds__(256, wide_minb<N>()) void k_passAG(Job j) {
   typedef EngG<N> G;
@@ -244,7 +255,13 @@ __global__ __launch_bounds__(256, wide_minb<N>()) void k_passAG(Job j) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, comp = blockIdx.y;
   const int el = tid / n2, a = (tid % n2) / n, b = tid % n;
   CompState* st = j.st + comp;
-  if (st->flags & ST_MISS) return;
+  if (no_window(j)) {
+    if (blockIdx.x == 0 && tid == 0) {
+      atomicOr(&st->flags, ST_MISS);
+      st->resolved = 1;
+    }
+    return;
+  }
   const int wlo = st->win_lo, whi = st->win_hi;
   const XParm PN = xparm(st->xm_norm, j.xh);
   const XParm PE = xparm(wlo - 1023, j.xh);

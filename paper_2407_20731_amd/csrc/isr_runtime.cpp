@@ -207,6 +207,19 @@ static long long shape_epi(int order) {
   return 256 / n2 > 0 ? 256 / n2 : 1;
 }
 
+// General pipeline: a 1/32 sample of the tiles predicts the boundary bin when
+// there are enough tiles.  (After a missed window only workgroup tiles take it:
+// where their sample finds a component all zero the passes over the others are yet
+// to come.)
+static long long general_stride(const Sizes& z) { return z.tiles >= 1024 ? 32 : 0; }
+
+// Whether a request starts on the streaming path.  Workgroup tiles: not where the
+// budget holds every energy, as only the general pipeline gives tau = +inf (N = 8,
+// 719 elements, 3 components, tol = 1: 409 us with the attempt, 324 without).
+static bool starts_streaming(const isr_field* f, const Sizes& z, double cut_scale = 1.0) {
+  return z.fast && !(wide_order(f->order, f->precision) && f->tol >= 0.0 && (f->tol * f->tol) * cut_scale >= 1.0);
+}
+
 Sizes plan_sizes(const isr_field* f, int tile, bool full_lists, bool stream) {
   Sizes z;
   const long long n = f->order + 1, n3 = n * n * n;
@@ -227,8 +240,7 @@ Sizes plan_sizes(const isr_field* f, int tile, bool full_lists, bool stream) {
   z.off_histL = take((size_t)(NLEV - 1) * nc * RBINS * sizeof(HistBin));
   z.off_histEs = take((size_t)nc * HBINS * sizeof(HistBin));
   z.off_histNs = take((size_t)nc * HBINS * sizeof(HistBin));
-  // a 1/32 sample of the tiles predicts the boundary bin when there are enough tiles
-  z.sample_stride = z.tiles >= 1024 ? 32 : 0;
+  z.sample_stride = general_stride(z);
   z.off_st = take((size_t)nc * sizeof(CompState));
   z.off_ticket = take(256);
   z.off_lookback = take((size_t)nc * z.tiles * 8);
@@ -699,7 +711,8 @@ int task_begin(isr_ctx* c, const isr_field* f, hipStream_t s, bool timing, Task*
   t->j = make_job(c, f, t->z, t->scratch, blob_ptrs(t->b));
   t->j.cut_scale = t->cut_scale;
   t->j.hs_out = host_state_dev(c, t->hs);
-  t->fast = t->z.fast;
+  t->fast = starts_streaming(f, t->z, t->cut_scale);
+  if (!t->fast) t->j.sample_stride = general_stride(t->z);
   t->timing = timing;
   if (timing)
     for (auto& e : t->ev) (void)hipEventCreate(&e);
@@ -717,14 +730,14 @@ int task_step(Task* t, isr_blob** out) {
   int flags = 0;
   for (int k = 0; k < f->ncomp; ++k) flags |= hs[k].flags;
   if (t->fast && (flags & ST_MISS)) {
-    // the threshold fell outside the sampled window: run the general pipeline
-    // (no sample window this time), keeping any budget override
+    // the threshold fell outside the sampled window: run the general pipeline,
+    // keeping any budget override
     if (t->timing) {
       float ms = 0.f;
       if (hipEventElapsedTime(&ms, t->ev[7], t->ev[6]) == hipSuccess) t->st.phase_ms[7] += ms;
     }
     t->fast = false;
-    t->j.sample_stride = 0;
+    t->j.sample_stride = wide_order(f->order, f->precision) ? general_stride(t->z) : 0;
     int rc = task_enqueue(t);
     if (rc) {
       task_release(t);
@@ -1111,7 +1124,7 @@ int run_batch(isr_ctx* c, const isr_field* fs, int count, isr_blob** outs, isr_s
     outs[i] = nullptr;
     Snap& x = sn[i];
     x.z = plan_sizes(&fs[i], 0, true, !wide_order(fs[i].order, fs[i].precision));
-    x.z.sample_stride = x.z.tiles >= 1024 ? 32 : 0;  // the batch kernel runs the general passes
+    x.z.sample_stride = general_stride(x.z);  // the batch kernel runs the general passes
     x.scratch = (char*)c->arena->alloc(x.z.scratch_bytes);
     x.b = x.scratch ? new_blob(c, &fs[i], x.z) : nullptr;
     x.hs = grab_host_state(c);
@@ -1808,7 +1821,8 @@ int run_compress_noalloc(isr_ctx* c, const isr_field* f, char* scratch, size_t s
   Job j = make_job(c, f, z, scratch, bp);
   hipStream_t s = (hipStream_t)f->stream;
   CompState* hs = c->st_host;
-  bool fast = z.fast;
+  bool fast = starts_streaming(f, z);
+  if (!fast) j.sample_stride = general_stride(z);
   int iters = 0;
   for (;;) {
     rc = enqueue_pipeline(c, j, z, s, nullptr, fast);
@@ -1819,7 +1833,7 @@ int run_compress_noalloc(isr_ctx* c, const isr_field* f, char* scratch, size_t s
     for (int k = 0; k < nc; ++k) flags |= hs[k].flags;
     if (fast && (flags & ST_MISS)) {  // threshold outside the sampled window: general pipeline
       fast = false;
-      j.sample_stride = 0;
+      j.sample_stride = wide_order(f->order, f->precision) ? general_stride(z) : 0;
       continue;
     }
     rc = status_from_flags(flags);
