@@ -1159,7 +1159,7 @@ __global__ __launch_bounds__(256, 4) void k_decompW(Job j, void* out) {
 // in flight, the error terms into running exact sums instead of LDS histogram
 // atomics.  The per-workgroup sums go to j.slotsB; j.qxm: log2 of the bound on
 // the error terms per component.  10,007 elements, N = 7, 3 components: 218 ->
-// 83 us.
+// 65 us (83 on pass B's grid, a third larger than what is resident of this kernel).
 template <int N>
 struct QuantWLds {
   typedef Eng<N, P_FP64> G;

@@ -12,8 +12,8 @@
 // are in flight while a tile is transformed.  What bounds it: FP64 VALU issue
 // (6 n multiplies and additions a value and transform) and the LDS round trips
 // between its barriers.
-// N = 9, 4,097 elements, 3 components: pass A 185 + 59 (second pass) -> 87 us,
-// pass B 577 -> 124 us, the request with its decompression 1,006 -> 384 us.
+// N = 9, 4,097 elements, 3 components: pass A 185 + 59 (second pass) -> 90 us,
+// pass B 577 -> 121 us, the request with its decompression 1,006 -> 377 us.
 //
 // Rows (n values along i) are n | 1 doubles apart in LDS: for even n the
 // pencils along i would otherwise meet in few banks (n = 16: two).  Field
@@ -620,7 +620,7 @@ __global__ __launch_bounds__(256, 2) void k_decompG(Job j, void* out) {
 // ---- quantised variant ------------------------------------------------------------
 // The codes of the kept values and the error they leave, as k_quantW
 // (isr_engine.cuh) does for the smaller orders.  N = 9, 3,333 elements, 3
-// components: 266 -> 92 us.
+// components: 266 -> 71 us.
 template <int N>
 struct QuantLdsG : WordLdsG<N> {
   XFar far;  // error terms

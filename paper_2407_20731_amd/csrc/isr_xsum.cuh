@@ -80,8 +80,8 @@ DEV void slow_bin(HistBin* g, double v) {
 // a2 within 2^(m+2h-54) of 1.5 2^(m+2h-53), grid 2 u2) and |a3| stays within
 // 2^52 u3.  Terms outside the range (at h = 12 those below 2^-71 of the bound)
 // are left to XFar: next to none of a noisy field's, a quarter to three quarters of
-// a smooth field's energies.  N = 7, 65,536 elements, FP64: pass A 517 -> 360 us,
-// pass B 517 -> 468 us, with the registers that the shorter sums free.
+// a smooth field's energies.  N = 7, 65,536 elements, FP64: pass A 517 -> 342 us,
+// pass B 517 -> 441 us, with the registers that the shorter sums free.
 struct XRun {
   double a1, a2, a3;
 };

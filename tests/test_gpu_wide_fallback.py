@@ -34,8 +34,8 @@ def test_a_budget_for_everything_makes_no_attempt(order):
                 assert _device_ms(blob)["fallback"] == 0.0
 
 
-# the attempt: sampling and launches that return at once, measured at about a
-# fifth of a whole streaming request of this size; it was nearly all of one
+# the attempt: sampling and launches that return at once, measured at a quarter to a
+# third of a whole streaming request of this size; it was nine tenths of one
 @pytest.mark.parametrize("order", [8, 9, 12, 15])
 def test_a_zero_component_ends_the_attempt_at_the_sample(order):
     u = synth.field((1 << 22) // (order + 1) ** 3, order)
