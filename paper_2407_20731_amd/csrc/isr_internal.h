@@ -317,7 +317,9 @@ constexpr int SCAN_CHUNK = 1024;  // elements per chunk of the element-offset sc
 // against 182).  At 2^17 to 2^18 values it still is where the tolerance is tight,
 // and the list with it (N = 7, 512 elements: noisy 153 against 156, white noise at
 // 0.01 169 against 171), but not at a loose one (white noise at 0.1 249 against
-// 219, at 0.5 326 against 260); above (1,024 elements) it is slower on both.
+// 219, at 0.5 326 against 260).  Up to 2^19 values (N = 6 to 15) it is 5 to 15 us
+// faster on noisy fields, but as much as 145 us slower on white noise at 0.1 and 5 to
+// 50 us on fields whose noise lies at the tolerance, also a tight one.
 inline bool chain_small(u64 nv, long long n_elem, double tol) {
   return n_elem <= SCAN_CHUNK && (nv < (1ull << 17) || (nv <= (1ull << 18) && tol <= 1e-2));
 }
